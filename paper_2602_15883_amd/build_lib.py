@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -20,7 +21,11 @@ DEVICE_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
                 "-munsafe-fp-atomics"]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-result"]
 
-SOURCES = ["ddpinn_kernels.hip", "ddpinn_api.cpp"]
+# (source, defines): the network kernels are compiled once per dimension (and
+# activation), in parallel
+SOURCES = ([("ddpinn_step.hip", [f"-DDDP_DIM={d}", f"-DDDP_ACT={a}"]) for d in (3, 2) for a in (1, 0)] +
+           [("ddpinn_query.hip", [f"-DDDP_DIM={d}"]) for d in (2, 3)] +
+           [("ddpinn_wide.hip", []), ("ddpinn_kernels.hip", []), ("ddpinn_api.cpp", [])])
 
 
 def _run(cmd):
@@ -34,19 +39,22 @@ def _run(cmd):
 def build(verbose: bool = False) -> str:
     """Compile every source and link libddpinn.so (always rebuilds)."""
     os.makedirs(BUILD, exist_ok=True)
-    objs = []
-    for src in SOURCES:
+    def one(entry):
+        src, defs = entry
         path = os.path.join(CSRC, src)
-        obj = os.path.join(BUILD, src + ".o")
+        obj = os.path.join(BUILD, src + "".join(defs).replace("-D", ".") + ".o")
         if src.endswith(".hip"):
-            cmd = [HIPCC, *DEVICE_FLAGS, "-I", INCLUDE, "-I", CSRC, "-c", path, "-o", obj]
+            cmd = [HIPCC, *DEVICE_FLAGS, *defs, "-I", INCLUDE, "-I", CSRC, "-c", path, "-o", obj]
         else:
             cmd = [HIPCC, "-x", "c++", *HOST_FLAGS, "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", INCLUDE,
                    "-I", CSRC, "-c", path, "-o", obj]
         out = _run(cmd)
         if verbose and out.strip():
             print(out)
-        objs.append(obj)
+        return obj
+
+    with ThreadPoolExecutor(max_workers=8) as pool:   # the compilers run as child processes
+        objs = list(pool.map(one, SOURCES))
     tmp = LIB + ".tmp"
     _run([HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp, *objs])
     os.replace(tmp, LIB)

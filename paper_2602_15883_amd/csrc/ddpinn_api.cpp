@@ -77,8 +77,10 @@ Shape make_shape(int dim, int W, int H) {
   sh.H = H;
   sh.Wp = (W + 15) / 16 * 16;
   sh.NW = sh.Wp / 16;
+  sh.s3 = split_fits(dim, sh.NW) ? 1 : 0;
+  sh.t3 = sh.NW <= kMaxWaves ? 1 : 0;
   sh.NWV = std::min(sh.NW, kMaxWaves);
-  sh.Kq = (W + 3) / 4;
+  sh.Kq = sh.t3 ? sh.Wp / 4 : (W + 3) / 4;   // t3: neurons at their own positions
   sh.P = (int32_t)nparams(dim, W, H);
   const int64_t Wp = sh.Wp, D = sh.D;
   // packed offsets
@@ -92,11 +94,14 @@ Shape make_shape(int dim, int W, int H) {
   }
   // fragment buffer
   o = 0;
-  sh.f_hid = o; o += 2 * (int64_t)(H - 1) * Wp * Wp;
+  sh.f_hid = o; o += sh.t3 ? 0 : 2 * (int64_t)(H - 1) * Wp * Wp;
   sh.f_w1 = o;  o += Wp * D;
   sh.f_b = o;   o += (int64_t)H * Wp;
   sh.f_wo = o;  o += D * Wp;
   sh.f_bo = o;  o += 4;
+  sh.f_hid3 = o = (o + 63) / 64 * 64;
+  sh.hid3_layer = (sh.t3 ? 2LL : 1LL) * sh.NW * ((sh.NW + 1) / 2) * 768;
+  o += sh.s3 ? (H - 1) * sh.hid3_layer : 0;
   sh.frag_floats = (o + 63) / 64 * 64;
   // slab
   o = 0;
@@ -495,7 +500,8 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   c->n_chunks = (max_seg_sub + kSlabChunk - 1) / kSlabChunk;
   const int stash_wg = std::max(c->n_wg, 1);
   const int NCB = (2 * sh.dim + 2) * (c->tile_points / 16);
-  c->stash_per_wg = (int64_t)sh.NW * sh.H * NCB * 256;
+  // t3: z_H stays in registers
+  c->stash_per_wg = (int64_t)sh.NW * (sh.t3 ? sh.H - 1 : sh.H) * NCB * 256;
 
   // exchange capacity: every ghost point in a half tile, plus one partial tile per face
   int64_t xcap = 0;

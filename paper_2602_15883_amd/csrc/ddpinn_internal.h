@@ -55,8 +55,9 @@ struct Shape {
   int32_t dim, D, W, H, Wp, NW;   // D = dim+1 inputs/outputs; Wp = W padded to 16; NW = Wp/16 row blocks
   int32_t P;                      // packed parameter count
   int32_t act;                    // activation: 0 tanh, 1 sin
-  int32_t NWV;                    // waves per workgroup, min(NW, kMaxWaves): wave w owns row
-                                  // block w and, when NW > kMaxWaves, row block w + NWV
+  int32_t NWV;                    // waves per workgroup, min(NW, kMaxWaves)
+  int32_t s3;                     // queries and exchange on bf16 triples (ddpinn_split.h)
+  int32_t t3;                     // the training step on bf16 triples (implies s3)
   int32_t split;                  // two row blocks per wave and the step's LDS plan does not
                                   // fit: one forward activation stack, backward by column halves
   int32_t Kq;                     // ceil(W/4): K-steps of the hidden-layer GEMMs (hidden neurons
@@ -69,6 +70,10 @@ struct Shape {
   int64_t f_b;     // b_1..b_H padded [H][Wp]
   int64_t f_wo;    // W_{H+1} padded [D][Wp]
   int64_t f_bo;    // b_{H+1} [4]
+  int64_t f_hid3;  // hidden layers as bf16 triples (ddpinn_split.h): layer l (2..H) at f_hid3 +
+                   // (l-2)*hid3_layer: fragments [row block][K block][part][64 lanes][8 bf16] of
+                   // W_l, then (t3; hid3_layer/2 further) of its transpose
+  int64_t hid3_layer;
   int64_t frag_floats;
   // gradient slab (per segment)
   int64_t s_hid;   // dW_l (l = 2..H) in accumulator order at s_hid + (l-2)*Wp*Wp
@@ -217,6 +222,24 @@ hipError_t launch_exchange(const ExchangeArgs& a, int n_wg, hipStream_t s);
 hipError_t launch_anchor_points(const float* x, int64_t n, int D, const float* x_anc, float* xa, hipStream_t s);
 hipError_t launch_master_counts(const SubDev* subs, const int32_t* counts, int n_sub, int32_t* out, hipStream_t s);
 hipError_t launch_evaluate(const EvalArgs& a, hipStream_t s);
+
+// Kernels on bf16 triples (ddpinn_step.hip, ddpinn_query.hip): one instance
+// file per dimension (and activation).  One row block of 16 neurons per wave up to
+// eight waves; above 128 neurons (queries and exchange) eight waves, the first NW - 8 of them
+// with two row blocks (waves w and w + 4 share a SIMD, which so holds at most
+// one row block more than another).
+template <int DIM, int ACT> const void* split_step_ptr(int tile_points, int NW);
+template <int DIM> const void* split_query_ptr(int mode, int act, int small, int NW);
+template <int DIM> const void* split_exchange_ptr(int act, int NW);
+// Kernels on FP32 MFMA (ddpinn_wide.hip): the step above 128 neurons, queries of
+// 3D networks above 208
+const void* wide_step_ptr(int dim, int act, int split, int Wp);
+const void* wide_query_ptr(int mode, int act, int small);
+const void* wide_exchange_ptr(int act);
+int wide_step_lds_floats(const Shape& sh);
+int wide_query_lds_floats(const Shape& sh, int small);
+// whether a query tile's activation stack of triples fits in LDS (all 2D networks, 3D up to 208 neurons)
+bool split_fits(int dim, int NW);
 
 // Kernel entry points and their LDS needs (for graph nodes and occupancy).
 const void* step_kernel_ptr(const Shape& sh, int tile_points);

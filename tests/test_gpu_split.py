@@ -1,0 +1,67 @@
+"""Contractions on bf16 triples: the step (up to 128 neurons), the queries and the
+exchange (up to 256 in 2D, 208 in 3D) against the FP64 oracle at the edges of
+their tiles: one and two row blocks, an even and an odd number of them (the last K block
+holds 16 neurons), the last and the first width of a range, ragged point tiles, both activations."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from parity import assert_close, channel_tolerances, oracle_loss_grad, rel_report
+
+torch = pytest.importorskip("torch")
+
+CASES = [(2, 1, 2, "tanh", 1), (2, 16, 3, "sin", 16), (3, 17, 3, "tanh", 17), (2, 32, 2, "sin", 33),
+         (3, 33, 4, "sin", 40), (2, 48, 3, "tanh", 97), (3, 80, 2, "tanh", 15), (2, 112, 3, "tanh", 100),
+         (3, 112, 3, "sin", 50), (2, 127, 2, "sin", 64), (3, 128, 3, "tanh", 65), (2, 128, 16, "tanh", 31)]
+QUERY_ONLY = [(2, 129, 2, "tanh", 100), (2, 256, 3, "sin", 97), (3, 144, 2, "tanh", 129), (3, 208, 3, "sin", 130)]
+
+
+def test_triples_hold_every_fp32():
+    """Round-to-nearest bf16 of x, of the remainder, and what is left: the three
+    sum to x exactly (the split the kernels make of every operand)."""
+    rng = np.random.default_rng(0)
+    x = np.concatenate([rng.standard_normal(1 << 16) * 10.0 ** rng.uniform(-25, 25, 1 << 16),
+                        1.0 + np.arange(1 << 16) * 2.0 ** -23]).astype(np.float32)
+
+    def bf16(v):
+        u = v.view(np.uint32).astype(np.uint64)
+        return ((u + 0x7fff + ((u >> 16) & 1)) & 0xffff0000).astype(np.uint32).view(np.float32)
+
+    h = bf16(x)
+    m = bf16(x - h)
+    lo = bf16((x - h) - m)
+    assert np.array_equal((h.astype(np.float64) + m + lo).astype(np.float32), x)
+    assert np.array_equal((x - h) - m, lo)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dim,W,H,act,npde", CASES + QUERY_ONLY)
+def test_split_kernels_against_oracle(orc, dim, W, H, act, npde):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2602_15883_amd as P
+    print(f"split dim={dim} W={W} H={H} act={act} n={npde}", flush=True)
+    orc.set_activation(act)
+    try:
+        pb = wl.tiny(dim=dim, width=W, depth=H, n_pde=npde, n_obs=5 + npde, n_gh=7, n_anc=1, seed=3 * W + H)
+        pb.activation = act
+        # rounding of a chain of H contractions over W terms and back, twice differentiated
+        tol = 16 * H * np.sqrt(W + 16) * 2.0 ** -24 * 4
+        ctx = P.context_from_problem(pb, device="cuda")
+        try:
+            loss, g = ctx.step(1, update=False, want_grad=True)
+            torch.cuda.synchronize()
+            Lr, gr = oracle_loss_grad(orc, pb)
+            for name, a, b in (("loss", loss.cpu().numpy()[0], Lr), ("grad", g.cpu().numpy()[0], gr)):
+                assert rel_report(a, b)[1] <= tol, (name, rel_report(a, b), tol)
+            x = pb.subs[0].pde_x
+            xt = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+            ref = orc.channels(dim, W, H, pb.subs[0].theta, x)
+            ch = ctx.query(xt, sub=0, what="channels").cpu().numpy().reshape(len(x), 2 * dim + 2, dim + 1)
+            for c, t in enumerate(channel_tolerances(dim)):
+                assert_close(ch[:, c], ref[:, c], t, f"channel {c}")
+            assert_close(ctx.query(xt, sub=0, what="value").cpu().numpy(), ref[:, 0], 1e-5, "value")
+        finally:
+            ctx.close()
+    finally:
+        orc.set_activation("tanh")
