@@ -233,29 +233,56 @@ __global__ void route_zero_kernel(int32_t* counts, int32_t* cursor, int n_sub) {
 // the few subdomain counters.)
 constexpr int kRouteBlock = 256;
 
-__device__ __forceinline__ int route_point(const RouteArgs& a, int64_t i) {
+// The boxes are read from LDS (staged once per block): a point tests up to
+// n_sub boxes in turn, and each test read from global memory cost its latency.
+constexpr int kRouteLdsSubs = 512;   // 32 bytes each; more boxes are read from global memory
+
+__device__ __forceinline__ const float* stage_boxes(const RouteArgs& a, float* lbox) {
+  if (a.n_sub > kRouteLdsSubs) return a.boxes;
+  for (int k = threadIdx.x; k < 8 * a.n_sub; k += blockDim.x) lbox[k] = a.boxes[k];
+  return lbox;
+}
+
+__device__ __forceinline__ int route_point(const RouteArgs& a, const float* boxes, int64_t i) {
   const float* x = a.x + i * a.D;
+  const float c[4] = {x[0], x[1], x[2], a.D > 3 ? x[3] : 0.f};
   for (int s = 0; s < a.n_sub; ++s) {
-    const float* lo = a.boxes + s * 8;
+    const float* lo = boxes + s * 8;
     const float* hi = lo + 4;
     bool in = true;
-    for (int q = 0; q < a.D; ++q) {
-      const float c = x[q];
-      const bool ok = (c >= lo[q]) && (c < hi[q] || (c == hi[q] && hi[q] == a.gmax[q]));
-      if (!ok) { in = false; break; }
-    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      in &= q >= a.D || ((c[q] >= lo[q]) && (c[q] < hi[q] || (c[q] == hi[q] && hi[q] == a.gmax[q])));
     if (in) return s;
   }
   return -1;
 }
 
+// offsets = exclusive sums of counts, by one wave
+__device__ __forceinline__ void route_offsets(const int* counts, int n_sub, int* offsets) {
+  if (threadIdx.x >= 64) return;
+  int base = 0;
+  for (int s0 = 0; s0 < n_sub; s0 += 64) {
+    const int s = s0 + threadIdx.x, c = s < n_sub ? counts[s] : 0;
+    int v = c;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(v, o, 64);
+      if ((int)threadIdx.x >= o) v += u;
+    }
+    if (s < n_sub) offsets[s] = base + v - c;
+    base += __shfl(v, 63, 64);
+  }
+  if (threadIdx.x == 0) offsets[n_sub] = base;
+}
+
 __global__ __launch_bounds__(kRouteBlock) void route_count_kernel(const RouteArgs a) {
-  extern __shared__ int hist[];   // [n_sub]
+  extern __shared__ int hist[];   // [n_sub], then the boxes
   for (int s = threadIdx.x; s < a.n_sub; s += blockDim.x) hist[s] = 0;
+  const float* boxes = stage_boxes(a, reinterpret_cast<float*>(hist + a.n_sub));
   __syncthreads();
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < a.n) {
-    const int found = route_point(a, i);
+    const int found = route_point(a, boxes, i);
     a.sub_id[i] = found;
     if (found >= 0) atomicAdd(&hist[found], 1);
     else
@@ -266,26 +293,22 @@ __global__ __launch_bounds__(kRouteBlock) void route_count_kernel(const RouteArg
     if (hist[s]) atomicAdd(a.counts + s, hist[s]);
 }
 
-__global__ void route_offsets_kernel(const RouteArgs a) {
-  if (threadIdx.x == 0) {
-    int32_t acc = 0;
-    for (int s = 0; s < a.n_sub; ++s) { a.offsets[s] = acc; acc += a.counts[s]; }
-    a.offsets[a.n_sub] = acc;
-  }
-}
-
+// every block takes the offsets from the counts itself; block 0 writes them out
 __global__ __launch_bounds__(kRouteBlock) void route_scatter_kernel(const RouteArgs a) {
-  extern __shared__ int sh[];   // hist[n_sub], base[n_sub]
+  extern __shared__ int sh[];   // hist[n_sub], base[n_sub + 1]
   int* hist = sh;
   int* base = sh + a.n_sub;
   for (int s = threadIdx.x; s < a.n_sub; s += blockDim.x) hist[s] = 0;
+  route_offsets(a.counts, a.n_sub, base);
   __syncthreads();
+  if (blockIdx.x == 0)
+    for (int s = threadIdx.x; s <= a.n_sub; s += blockDim.x) a.offsets[s] = base[s];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int s = (i < a.n) ? a.sub_id[i] : -1;
   const int rank = (s >= 0) ? atomicAdd(&hist[s], 1) : 0;
   __syncthreads();
   for (int q = threadIdx.x; q < a.n_sub; q += blockDim.x)
-    base[q] = hist[q] ? a.offsets[q] + atomicAdd(a.cursor + q, hist[q]) : 0;
+    if (hist[q]) base[q] += atomicAdd(a.cursor + q, hist[q]);
   __syncthreads();
   if (s >= 0) a.perm[base[s] + rank] = (int32_t)i;
 }
@@ -298,10 +321,11 @@ constexpr int kRouteSmallPerThread = 8;
 constexpr int kRouteSmallMax = kRouteSmallThreads * kRouteSmallPerThread;   // points
 
 __global__ __launch_bounds__(kRouteSmallThreads) void route_small_kernel(const RouteArgs a) {
-  extern __shared__ int sh[];   // hist[n_sub], base[n_sub]
+  extern __shared__ int sh[];   // hist[n_sub], base[n_sub + 1], then the boxes
   int* hist = sh;
   int* base = sh + a.n_sub;
   for (int s = threadIdx.x; s < a.n_sub; s += blockDim.x) hist[s] = 0;
+  const float* boxes = stage_boxes(a, reinterpret_cast<float*>(base + a.n_sub + 1));
   __syncthreads();
   int sid[kRouteSmallPerThread];
 #pragma unroll
@@ -309,7 +333,7 @@ __global__ __launch_bounds__(kRouteSmallThreads) void route_small_kernel(const R
     const int64_t i = threadIdx.x + (int64_t)k * kRouteSmallThreads;
     sid[k] = -1;
     if (i < a.n) {
-      const int found = route_point(a, i);
+      const int found = route_point(a, boxes, i);
       sid[k] = found;
       a.sub_id[i] = found;
       if (found >= 0) atomicAdd(&hist[found], 1);
@@ -318,15 +342,11 @@ __global__ __launch_bounds__(kRouteSmallThreads) void route_small_kernel(const R
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t acc = 0;
-    for (int s = 0; s < a.n_sub; ++s) {
-      base[s] = acc;
-      a.offsets[s] = acc;
-      a.counts[s] = hist[s];
-      acc += hist[s];
-    }
-    a.offsets[a.n_sub] = acc;
+  route_offsets(hist, a.n_sub, base);
+  __syncthreads();
+  for (int s = threadIdx.x; s <= a.n_sub; s += blockDim.x) {
+    a.offsets[s] = base[s];
+    if (s < a.n_sub) a.counts[s] = hist[s];
   }
   __syncthreads();
 #pragma unroll
@@ -429,19 +449,29 @@ __global__ void eval_err_kernel(const EvalArgs a) {
   }
 }
 
-// err[q] (velocity components), err[dim] (velocity vector), err[dim+1] (p)
-__global__ void eval_final_kernel(const EvalArgs a) {
-  if (threadIdx.x != 0) return;
-  const int D = a.D, dim = D - 1;
+// err[q] (velocity components), err[dim] (velocity vector), err[dim+1] (p).
+// One block; each thread sums a fixed share of the chunk sums and the shares
+// are added in a fixed order.
+__global__ __launch_bounds__(256) void eval_final_kernel(const EvalArgs a) {
+  __shared__ float red[256];
+  const int D = a.D, dim = D - 1, n = a.n_snap * a.nblk;
   float num[4] = {0.f, 0.f, 0.f, 0.f}, den[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < a.n_snap; ++k)
-    for (int b = 0; b < a.nblk; ++b) {
-      const float* e = a.epart + ((size_t)k * a.nblk + b) * 2 * (D + 1);
-      for (int q = 0; q < D; ++q) {
+  for (int k = threadIdx.x; k < n; k += blockDim.x) {
+    const float* e = a.epart + (size_t)k * 2 * (D + 1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q < D) {
         num[q] += e[2 * q];
         den[q] += e[2 * q + 1];
       }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (q < D) {
+      num[q] = block_sum256(num[q], red);
+      den[q] = block_sum256(den[q], red);
     }
+  if (threadIdx.x != 0) return;
   float nv = 0.f, dv = 0.f;
   for (int q = 0; q < dim; ++q) {
     a.err_out[q] = sqrtf(num[q] / den[q]);
@@ -469,7 +499,7 @@ hipError_t launch_evaluate(const EvalArgs& a, hipStream_t s) {
   const dim3 grid(a.nblk, a.n_snap);
   hipLaunchKernelGGL(eval_means_kernel, grid, dim3(256), 0, s, a);
   hipLaunchKernelGGL(eval_err_kernel, grid, dim3(256), 0, s, a);
-  hipLaunchKernelGGL(eval_final_kernel, dim3(1), dim3(64), 0, s, a);
+  hipLaunchKernelGGL(eval_final_kernel, dim3(1), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -577,16 +607,15 @@ hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_route(const RouteArgs& a, hipStream_t s) {
+  const size_t box = a.n_sub <= kRouteLdsSubs ? 32 * (size_t)a.n_sub : 0, h = sizeof(int) * (size_t)a.n_sub;
   if (a.n <= kRouteSmallMax) {
-    hipLaunchKernelGGL(route_small_kernel, dim3(1), dim3(kRouteSmallThreads), 2 * sizeof(int) * (size_t)a.n_sub, s, a);
+    hipLaunchKernelGGL(route_small_kernel, dim3(1), dim3(kRouteSmallThreads), 2 * h + 4 + box, s, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(route_zero_kernel, dim3(1), dim3(256), 0, s, a.counts, a.cursor, a.n_sub);
   const unsigned nb = (unsigned)((a.n + kRouteBlock - 1) / kRouteBlock);
-  const size_t h = sizeof(int) * (size_t)a.n_sub;
-  if (nb) hipLaunchKernelGGL(route_count_kernel, dim3(nb), dim3(kRouteBlock), h, s, a);
-  hipLaunchKernelGGL(route_offsets_kernel, dim3(1), dim3(64), 0, s, a);
-  if (nb) hipLaunchKernelGGL(route_scatter_kernel, dim3(nb), dim3(kRouteBlock), 2 * h, s, a);
+  if (nb) hipLaunchKernelGGL(route_count_kernel, dim3(nb), dim3(kRouteBlock), h + box, s, a);
+  if (nb) hipLaunchKernelGGL(route_scatter_kernel, dim3(nb), dim3(kRouteBlock), 2 * h + 4, s, a);
   return hipGetLastError();
 }
 

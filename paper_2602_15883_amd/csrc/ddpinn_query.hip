@@ -46,6 +46,50 @@ __device__ __forceinline__ void split_forward(const Shape& sh, const float* fr, 
   __syncthreads();
 }
 
+// Up to 128 neurons and one column block per channel (SMALL): the weight
+// fragments and the bias of the next layer are requested before the current one's
+// products, so that a layer's chain holds no fetch from L2 or beyond.
+template <int DIM, int NCB, int MODE, int ACT>
+__device__ __forceinline__ void split_forward_small(const Shape& sh, const float* fr, char* lds, const SplitQueryLds& L,
+                                                    int w, int lane, int tid, int nthr) {
+  using M = ModeCfg<DIM, NCB, MODE>;
+  constexpr int D = DIM + 1, NKB = kMaxWaves / 2;
+  const int g = lane >> 4, j = lane & 15, Wp = sh.Wp, NW = sh.NW, KB = (NW + 1) >> 1, H = sh.H;
+  const LaneSlots ls = lane_slots(lane);
+  const uint32_t lane16 = (uint32_t)lane * 16u;
+  const float* xin = reinterpret_cast<const float*>(lds + L.xin);
+  const float* wf = fr + sh.f_hid3 + (size_t)w * KB * 3 * kFragFloats;
+  const float* bf = fr + sh.f_b + 16 * w + 4 * g;
+  LayerFrags<NKB> f, fn;
+  v4f acc[1][NCB], bias, biasn = zero4();
+  input_layer<DIM, NCB, MODE>(acc[0], fr + sh.f_w1, fr + sh.f_b, xin, w, g, j);
+  if (H > 1) {
+    load_layer<NKB>(wf, KB, lane16, fn);
+    biasn = ldg4(bf + Wp);
+  }
+  act_forward<DIM, NCB, MODE, ACT>(acc[0]);
+  for (int l = 2; l <= H; ++l) {
+    f = fn;
+    bias = biasn;
+    if (l < H) {
+      load_layer<NKB>(wf + (size_t)(l - 1) * sh.hid3_layer, KB, lane16, fn);
+      biasn = ldg4(bf + (size_t)l * Wp);
+    }
+    stack_store<1, NCB>(lds, w, NW, ls, acc);
+    __syncthreads();
+    gemm_layer<NCB, NKB>(lds, NW, ls, f, acc);
+#pragma unroll
+    for (int pb = 0; pb < M::NPB; ++pb) acc[0][pb] += bias;
+    act_forward<DIM, NCB, MODE, ACT>(acc[0]);
+    __syncthreads();
+  }
+  float* part = reinterpret_cast<float*>(lds);
+  output_partials<D, 1, NCB>(part, fr + sh.f_wo, Wp, w, w, g, j, acc);
+  __syncthreads();
+  output_sum<DIM, NCB, MODE>(part, 4 * sh.NWV, fr + sh.f_bo, reinterpret_cast<float*>(lds + L.ys), tid, nthr);
+  __syncthreads();
+}
+
 // WIDE: above 128 neurons (eight waves, some with two row blocks)
 template <int DIM, int NCB, int MODE, int ACT, int WIDE>
 __device__ __forceinline__ void split_forward_any(const Shape& sh, const float* fr, char* lds, const SplitQueryLds& L,
@@ -55,6 +99,8 @@ __device__ __forceinline__ void split_forward_any(const Shape& sh, const float* 
     if (split_rb0(w + 1, sh.NW, sh.NWV) - rb0 == 2)
       split_forward<DIM, NCB, MODE, ACT, 2, true>(sh, fr, lds, L, rb0, w, lane, tid, nthr);
     else split_forward<DIM, NCB, MODE, ACT, 1, true>(sh, fr, lds, L, rb0, w, lane, tid, nthr);
+  } else if constexpr (NCB <= 3) {
+    split_forward_small<DIM, NCB, MODE, ACT>(sh, fr, lds, L, w, lane, tid, nthr);
   } else {
     split_forward<DIM, NCB, MODE, ACT, 1, false>(sh, fr, lds, L, w, w, lane, tid, nthr);
   }
@@ -64,7 +110,7 @@ __device__ __forceinline__ void split_forward_any(const Shape& sh, const float* 
 // blocks, which halves (gradient mode) or divides by six (value mode) the
 // work on a tile's critical path; for requests too small to fill the chip.
 template <int DIM, int MODE, int ACT, int SMALL, int WIDE>
-__global__ __launch_bounds__(512, WIDE ? 2 : 4) void split_query_kernel(const QueryArgs a) {
+__global__ __launch_bounds__(512, WIDE || SMALL ? 2 : 4) void split_query_kernel(const QueryArgs a) {
   constexpr int D = DIM + 1, CF = 2 * DIM + 2;
   constexpr int CMODE = MODE == M_VALUE ? 1 : (MODE == M_GRAD ? DIM + 1 : CF);
   constexpr int NCB = SMALL ? CMODE : CF;

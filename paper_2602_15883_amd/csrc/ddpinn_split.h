@@ -265,6 +265,39 @@ __device__ __forceinline__ void gemm_neurons(const float* wf, const char* st, in
   if (NW & 1) products16<R, NCB, CG>(f.a, sp + ls.alone - ls.pair, acc);
 }
 
+// The same for one row block and few column blocks, with all the layer's weight
+// fragments in f (KB <= NKB): for launches too small to cover the latency of
+// fetching them as they are needed.
+template <int NKB>
+struct LayerFrags { v4f a[NKB][1][3]; };
+template <int NKB>
+__device__ __forceinline__ void load_layer(const float* wf, int KB, uint32_t lane16, LayerFrags<NKB>& f) {
+#pragma unroll
+  for (int k = 0; k < NKB; ++k)
+    if (k < KB) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) f.a[k][0][p] = ldg4u(wf + (size_t)(k * 3 + p) * kFragFloats, lane16);
+    }
+}
+template <int NCB, int NKB>
+__device__ __forceinline__ void gemm_layer(const char* st, int NW, const LaneSlots& ls, const LayerFrags<NKB>& f,
+                                           v4f (&acc)[1][NCB]) {
+  const int KF = NW >> 1;
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb) acc[0][cb] = zero4();
+#pragma unroll
+  for (int kb = 0; kb < NKB; ++kb) {
+    const char* sp = st + kb * NCB * 2 * kUnits3;
+    if (kb < KF) {
+      v8h b[NCB][3];
+      stack_operand<NCB>(sp + ls.pair, 0, b);
+      products32<1, NCB, NCB>(f.a[kb], b, 0, acc);
+    } else if (kb == KF && (NW & 1)) {
+      products16<1, NCB, NCB>(f.a[kb], sp + ls.alone, acc);
+    }
+  }
+}
+
 // Output layer: this wave's share of ys[o][col] = W_{H+1}[o] . h[col], one
 // partial sum per lane group, into part[(4 w + g)][o][col] (LDS); the h of the
 // last hidden layer never goes to LDS.
