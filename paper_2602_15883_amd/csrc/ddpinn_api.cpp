@@ -110,7 +110,8 @@ Shape make_shape(int dim, int W, int H) {
   sh.s_w1 = o;  o += Wp * D;
   sh.s_wo = o;  o += D * Wp;
   sh.s_bo = o;  o += 4;
-  sh.s_loss = o; o += 8;
+  sh.s_loss = o = (o + 63) / 64 * 64;   // the losses are one reduce block's
+  o += 8;
   sh.slab_floats = (o + 63) / 64 * 64;
   return sh;
 }
@@ -200,7 +201,7 @@ struct pinn_ctx {
   // per-subdomain launches
   std::vector<int> ps_wg, ps_nr, ps_wgb_off;
   int ps_items = 0, ps_seg = 0;
-  int n_slabs = 0, n_chunks = 1;
+  int n_slabs = 0;
   int64_t stash_per_wg = 0;
   // device regions inside the workspace
   SubDev* d_subs = nullptr;
@@ -214,11 +215,9 @@ struct pinn_ctx {
   float* d_slabs = nullptr;
   float* d_stash = nullptr;
   float* d_frag = nullptr;
-  float* d_partial = nullptr;
   float* d_loss_ws = nullptr;
   float* d_gbuf = nullptr;
   float* d_normpart = nullptr;
-  float* d_clip = nullptr;
   float* d_boxes = nullptr;
   ExchangeItem* d_xitems = nullptr;
   float** d_targets = nullptr;
@@ -239,8 +238,9 @@ struct pinn_ctx {
   // graph
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
-  hipGraphNode_t n_reduce = nullptr;   // Adam node (t, lr, update change per step)
-  hipGraphNode_t n_grad = nullptr;     // gradient node (output pointers change per step)
+  // the nodes whose t, lr, update flag and output pointers change per step
+  hipGraphNode_t n_reduce = nullptr;   // reduction (and Adam)
+  hipGraphNode_t n_clip = nullptr;     // Adam with clipping
   ReduceArgs rargs{};
   StepArgs sargs{};
   PrepArgs pargs{};
@@ -492,12 +492,6 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
     c->ps_items = (int)items_ps.size();
   }
   c->n_slabs = std::max(std::max(c->n_seg, c->ps_seg), 1);
-  int max_seg_sub = 1;
-  for (int s = 0; s < c->n_sub; ++s) {
-    max_seg_sub = std::max(max_seg_sub, seg_begin[s + 1] - seg_begin[s]);
-    max_seg_sub = std::max(max_seg_sub, seg_ps[s + 1] - seg_ps[s]);
-  }
-  c->n_chunks = (max_seg_sub + kSlabChunk - 1) / kSlabChunk;
   const int stash_wg = std::max(c->n_wg, 1);
   const int NCB = (2 * sh.dim + 2) * (c->tile_points / 16);
   // t3: z_H stays in registers
@@ -533,13 +527,10 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   const size_t o_seg_ps = take(sizeof(int32_t) * (c->n_sub + 1));
   const size_t o_slabs = take(sizeof(float) * (size_t)c->n_slabs * sh.slab_floats);
   const size_t o_stash = take(sizeof(float) * (size_t)stash_wg * c->stash_per_wg);
-  const size_t o_partial = take(sizeof(float) * (size_t)c->n_sub * c->n_chunks * sh.slab_floats);
   const size_t o_frag = take(sizeof(float) * (size_t)c->n_sub * sh.frag_floats);
   const size_t o_loss = take(sizeof(float) * 8 * c->n_sub);
-  const int n_gblk = (int)((sh.P + 255) / 256);
   const size_t o_gbuf = take(sizeof(float) * (size_t)c->n_sub * sh.P);
-  const size_t o_normpart = take(sizeof(float) * (size_t)c->n_sub * n_gblk);
-  const size_t o_clip = take(sizeof(float) * c->n_sub);
+  const size_t o_normpart = take(sizeof(float) * (size_t)c->n_sub * reduce_blocks(sh));
   const size_t o_boxes = take(sizeof(float) * 8 * c->n_sub);
   const size_t o_xitems = take(sizeof(ExchangeItem) * c->x_cap);
   const size_t o_targets = take(sizeof(float*) * c->n_sub);
@@ -563,11 +554,9 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   c->d_slabs = (float*)(ws + o_slabs);
   c->d_stash = (float*)(ws + o_stash);
   c->d_frag = (float*)(ws + o_frag);
-  c->d_partial = (float*)(ws + o_partial);
   c->d_loss_ws = (float*)(ws + o_loss);
   c->d_gbuf = (float*)(ws + o_gbuf);
   c->d_normpart = (float*)(ws + o_normpart);
-  c->d_clip = (float*)(ws + o_clip);
   c->d_boxes = (float*)(ws + o_boxes);
   c->d_xitems = (ExchangeItem*)(ws + o_xitems);
   c->d_targets = (float**)(ws + o_targets);
@@ -650,12 +639,9 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   c->rargs.subs = c->d_subs;
   c->rargs.seg_begin = c->d_seg_begin;
   c->rargs.slabs = c->d_slabs;
-  c->rargs.partial = c->d_partial;
-  c->rargs.n_chunks = c->n_chunks;
   c->rargs.loss_ws = c->d_loss_ws;
   c->rargs.gbuf = c->d_gbuf;
   c->rargs.normpart = c->d_normpart;
-  c->rargs.clip_scale = c->d_clip;
   c->rargs.clip = cfg->clip_norm;
   c->rargs.n_sub = c->n_sub;
   c->rargs.lr = cfg->lr;
@@ -687,40 +673,23 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
     c->rargs.t = 1;
     c->rargs.update = 0;
     void* ra[] = {&c->rargs};
-    hipKernelNodeParams kq{};
-    grid_slab_sum(c->rargs, &kq.gridDim, &kq.blockDim);
-    kq.func = (void*)slab_sum_kernel_ptr();
-    kq.kernelParams = ra;
-    hipGraphNode_t n25;
-    HIPCHECK(hipGraphAddKernelNode(&n25, gr, &n2, 1, &kq));
     hipKernelNodeParams kg{};
     grid_reduce(c->rargs, &kg.gridDim, &kg.blockDim);
-    kg.func = (void*)grad_kernel_ptr();
+    kg.func = (void*)reduce_kernel_ptr();
     kg.kernelParams = ra;
-    hipGraphNode_t ng;
-    HIPCHECK(hipGraphAddKernelNode(&ng, gr, &n25, 1, &kg));
-    c->n_grad = ng;
-    hipGraphNode_t last = ng;
-    int nblk = (int)kg.gridDim.x;
-    void* ca[] = {&c->rargs, &nblk};
+    HIPCHECK(hipGraphAddKernelNode(&n3, gr, &n2, 1, &kg));
+    c->n_reduce = n3;
     if (cfg->clip_norm > 0.f) {
       hipKernelNodeParams kc{};
-      kc.gridDim = dim3(c->n_sub);
-      kc.blockDim = dim3(256);
-      kc.func = (void*)clip_kernel_ptr();
+      grid_clip_adam(c->rargs, &kc.gridDim, &kc.blockDim);
+      int nblk = reduce_blocks(sh);
+      void* ca[] = {&c->rargs, &nblk};
+      kc.func = (void*)clip_adam_kernel_ptr();
       kc.kernelParams = ca;
-      hipGraphNode_t nc;
-      HIPCHECK(hipGraphAddKernelNode(&nc, gr, &ng, 1, &kc));
-      last = nc;
+      HIPCHECK(hipGraphAddKernelNode(&n4, gr, &n3, 1, &kc));
+      c->n_clip = n4;
     }
-    hipKernelNodeParams kr{};
-    grid_reduce(c->rargs, &kr.gridDim, &kr.blockDim);
-    kr.func = (void*)adam_kernel_ptr();
-    kr.kernelParams = ra;
-    HIPCHECK(hipGraphAddKernelNode(&n3, gr, &last, 1, &kr));
-    HIPCHECK(hipGraphAddKernelNode(&n4, gr, &n3, 1, &kp));
     c->graph = gr;
-    c->n_reduce = n3;
     HIPCHECK(hipGraphInstantiate(&c->gexec, gr, nullptr, nullptr, 0));
   }
   HIPCHECK(hipStreamSynchronize(s));
@@ -776,7 +745,6 @@ static pinn_status run_step_eager(pinn_ctx* c, bool per_sub, bool timed, hipStre
     ra.seg_begin = c->d_seg_ps;
   }
   HIPCHECK(launch_reduce(ra, s));
-  HIPCHECK(launch_prep(c->pargs, s));
   return PINN_OK;
 }
 
@@ -802,14 +770,18 @@ pinn_status pinn_step(pinn_ctx* c, int64_t t, uint32_t flags, float* loss_out, f
     void* ra[] = {&c->rargs};
     hipKernelNodeParams kg{};
     grid_reduce(c->rargs, &kg.gridDim, &kg.blockDim);
-    kg.func = (void*)grad_kernel_ptr();
+    kg.func = (void*)reduce_kernel_ptr();
     kg.kernelParams = ra;
-    HIPCHECK(hipGraphExecKernelNodeSetParams(c->gexec, c->n_grad, &kg));
-    hipKernelNodeParams kr{};
-    grid_reduce(c->rargs, &kr.gridDim, &kr.blockDim);
-    kr.func = (void*)adam_kernel_ptr();
-    kr.kernelParams = ra;
-    HIPCHECK(hipGraphExecKernelNodeSetParams(c->gexec, c->n_reduce, &kr));
+    HIPCHECK(hipGraphExecKernelNodeSetParams(c->gexec, c->n_reduce, &kg));
+    if (c->n_clip) {
+      int nblk = reduce_blocks(c->sh);
+      void* ca[] = {&c->rargs, &nblk};
+      hipKernelNodeParams kc{};
+      grid_clip_adam(c->rargs, &kc.gridDim, &kc.blockDim);
+      kc.func = (void*)clip_adam_kernel_ptr();
+      kc.kernelParams = ca;
+      HIPCHECK(hipGraphExecKernelNodeSetParams(c->gexec, c->n_clip, &kc));
+    }
     HIPCHECK(hipGraphLaunch(c->gexec, s));
   } else {
     pinn_status st = run_step_eager(c, per_sub, timed, s);

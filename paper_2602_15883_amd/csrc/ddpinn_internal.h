@@ -11,7 +11,7 @@ constexpr int kMaxWidth = 256;
 constexpr int kMaxWaves = 8;    // waves per workgroup of the network kernels
 constexpr int kMaxDepth = 16;
 constexpr int kMaxSub = 4096;
-constexpr int kSlabChunk = 16;   // slabs summed per thread in the first reduce stage
+constexpr int kSlabChunk = 16;   // slabs summed by one thread of the reduction
 
 // Per-subdomain device descriptor (copied into the workspace at create).
 struct SubDev {
@@ -109,14 +109,11 @@ struct ReduceArgs {
   const SubDev* subs;
   const int32_t* seg_begin; // [n_sub + 1] slab range of each subdomain
   const float* slabs;
-  float* partial;           // [n_sub][n_chunks][slab_floats] first-stage sums
-  int32_t n_chunks;         // ceil(max slabs of one subdomain / kSlabChunk)
   float* loss_out;          // [n_sub][7] or null
   float* grad_out;          // [n_sub][P] or null
   float* loss_ws;           // [n_sub][8] always written (finite check)
   float* gbuf;              // [n_sub][P] gradient
-  float* normpart;          // [n_sub][grid blocks] partial sums of g^2
-  float* clip_scale;        // [n_sub] min(1, clip / ||g||)
+  float* normpart;          // [n_sub][reduce blocks] partial sums of g^2 (clipping)
   int32_t n_sub;
   int32_t update;           // run Adam
   int64_t t;                // Adam step (1-based)
@@ -246,11 +243,10 @@ const void* step_kernel_ptr(const Shape& sh, int tile_points);
 const void* query_kernel_ptr(const Shape& sh, int what, int small = 0);   // what: Q_VALUE, Q_UVPW, Q_CHANNELS/Q_RESIDUAL
 const void* exchange_kernel_ptr(const Shape& sh);
 const void* prep_kernel_ptr();
-const void* slab_sum_kernel_ptr();
-const void* grad_kernel_ptr();
-const void* clip_kernel_ptr();
-const void* adam_kernel_ptr();
-void grid_slab_sum(const ReduceArgs& a, dim3* grid, dim3* block);
+const void* reduce_kernel_ptr();
+const void* clip_adam_kernel_ptr();
+int reduce_blocks(const Shape& sh);
+void grid_clip_adam(const ReduceArgs& a, dim3* grid, dim3* block);
 int step_lds_floats(const Shape& sh, int tile_points);
 int query_lds_floats(const Shape& sh, int small = 0);
 int step_value_points(int dim, int tile_points);

@@ -65,3 +65,28 @@ def test_split_kernels_against_oracle(orc, dim, W, H, act, npde):
             ctx.close()
     finally:
         orc.set_activation("tanh")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dim,W,H,act,clip", [(2, 50, 3, "tanh", 0.0), (3, 17, 2, "sin", 1e-3), (2, 112, 1, "tanh", 0.0),
+                                              (2, 150, 2, "sin", 0.5), (3, 200, 2, "tanh", 0.0), (3, 240, 2, "tanh", 1.0)])
+def test_adam_leaves_the_weight_copies_current(dim, W, H, act, clip):
+    """The update writes the parameters and the kernels' copies of them together:
+    a query after it equals one after the copies are rebuilt from theta, bitwise."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2602_15883_amd as P
+    print(f"copies dim={dim} W={W} H={H} clip={clip}", flush=True)
+    pb = wl.tiny(dim=dim, width=W, depth=H, n_pde=40, n_obs=9, n_gh=5, n_anc=2, seed=W)
+    pb.activation, pb.clip_norm = act, clip
+    x = torch.from_numpy(np.ascontiguousarray(pb.subs[0].pde_x)).cuda()
+    ctx = P.context_from_problem(pb, device="cuda", graph=clip == 0.0)
+    try:
+        before = ctx.query(x, sub=0, what="channels").clone()
+        ctx.step(1)
+        after = ctx.query(x, sub=0, what="channels").clone()
+        ctx.refresh()
+        assert torch.equal(after, ctx.query(x, sub=0, what="channels"))
+        assert not torch.equal(before, after)
+    finally:
+        ctx.close()
