@@ -78,7 +78,7 @@ Shape make_shape(int dim, int W, int H) {
   sh.Wp = (W + 15) / 16 * 16;
   sh.NW = sh.Wp / 16;
   sh.s3 = split_fits(dim, sh.NW) ? 1 : 0;
-  sh.t3 = sh.NW <= kMaxWaves ? 1 : 0;
+  sh.t3 = sh.s3;
   sh.NWV = std::min(sh.NW, kMaxWaves);
   sh.Kq = sh.t3 ? sh.Wp / 4 : (W + 3) / 4;   // t3: neurons at their own positions
   sh.P = (int32_t)nparams(dim, W, H);
@@ -102,6 +102,8 @@ Shape make_shape(int dim, int W, int H) {
   sh.f_hid3 = o = (o + 63) / 64 * 64;
   sh.hid3_layer = (sh.t3 ? 2LL : 1LL) * sh.NW * ((sh.NW + 1) / 2) * 768;
   o += sh.s3 ? (H - 1) * sh.hid3_layer : 0;
+  sh.f_wo3 = o;
+  o += sh.t3 ? ((sh.NW + 1) / 2) * 768 : 0;
   sh.frag_floats = (o + 63) / 64 * 64;
   // slab
   o = 0;
@@ -384,7 +386,7 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
 
   // two row blocks per wave: the column-split LDS plan when the plain one
   // does not fit
-  if (sh.NW > sh.NWV && (int64_t)step_lds_floats(sh, 16) * 4 > max_lds) c->sh.split = 1;
+  if (!sh.t3 && sh.NW > sh.NWV && (int64_t)step_lds_floats(sh, 16) * 4 > max_lds) c->sh.split = 1;
 
   // tile shape: 32-point collocation tiles when they fit in LDS with at
   // least the occupancy of 16-point tiles, unless fixed by the caller

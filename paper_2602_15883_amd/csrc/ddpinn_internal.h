@@ -74,6 +74,7 @@ struct Shape {
                    // (l-2)*hid3_layer: fragments [row block][K block][part][64 lanes][8 bf16] of
                    // W_l, then (t3; hid3_layer/2 further) of its transpose
   int64_t hid3_layer;
+  int64_t f_wo3;   // W_{H+1} as bf16 triples (t3): [K block][part][64 lanes][8 bf16], rows padded to 16
   int64_t frag_floats;
   // gradient slab (per segment)
   int64_t s_hid;   // dW_l (l = 2..H) in accumulator order at s_hid + (l-2)*Wp*Wp

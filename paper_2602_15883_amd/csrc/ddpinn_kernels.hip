@@ -11,6 +11,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "ddpinn_split.h"
 
 namespace ddp {
@@ -21,7 +23,8 @@ namespace ddp {
 // ---------------------------------------------------------------------------
 // threads: one per float ahead of f_hid3, then one per pair of bf16 triples
 __host__ __device__ inline int64_t prep_threads(const Shape& sh) {
-  return sh.f_hid3 + (sh.s3 ? (sh.t3 ? 2LL : 1LL) * (sh.H - 1) * sh.NW * ((sh.NW + 1) / 2) * 256 : 0);
+  const int64_t KB = (sh.NW + 1) / 2;
+  return sh.f_hid3 + (sh.s3 ? (sh.t3 ? 2 : 1) * (sh.H - 1) * sh.NW * KB * 256 : 0) + (sh.t3 ? KB * 256 : 0);
 }
 
 __global__ void prep_kernel(const PrepArgs a) {
@@ -40,9 +43,10 @@ __global__ void prep_kernel(const PrepArgs a) {
     int e = (int)(idx - sh.f_hid3);
     const int m = e / per;
     e -= m * per;
-    const int l = 2 + (sh.t3 ? m >> 1 : m), trans = sh.t3 ? m & 1 : 0;
+    const bool out = m == (sh.t3 ? 2 : 1) * (H - 1);   // W_{H+1}: its D rows
+    const int l = out ? H + 1 : 2 + (sh.t3 ? m >> 1 : m), trans = sh.t3 && !out ? m & 1 : 0;
     const int e2 = e & 3, lane = (e >> 2) & 63, t = e >> 8, kb = t % KB, rb = t / KB;
-    const int r = hid_neuron(sh, 16 * rb + (lane & 15));
+    const int r = out ? ((lane & 15) < D ? lane & 15 : -1) : hid_neuron(sh, 16 * rb + (lane & 15));
     float x[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -98,14 +102,25 @@ __global__ void prep_kernel(const PrepArgs a) {
 // Adam as three launches).
 // ---------------------------------------------------------------------------
 
+// row and column positions of element e of a layer's dW in the slab: tiles [row
+// block][column block][64 lanes][4], lane (g, j): row 4g + i, column j; the
+// kernels on triples (t3) keep the transpose so
+__device__ __forceinline__ void slab_tile_rc(const Shape& sh, int e, int& r, int& c) {
+  const int lane = (e >> 2) & 63, t = e >> 8, w = t / sh.NW, nb = t - w * sh.NW;
+  const int a = 16 * w + 4 * (lane >> 4) + (e & 3), b = 16 * nb + (lane & 15);
+  r = sh.t3 ? b : a;
+  c = sh.t3 ? a : b;
+}
+
 // packed parameter at a slab position (-1: padding or a loss sum)
 __device__ __forceinline__ int64_t slab_param(const Shape& sh, int64_t pos) {
   const int W = sh.W, Wp = sh.Wp, D = sh.D;
   if (pos < sh.s_b) {                          // dW_l in accumulator order
     const int per = Wp * Wp, l = 2 + (int)(pos / per);
     const int e = (int)(pos - (int64_t)(l - 2) * per);
-    const int i = e & 3, lane = (e >> 2) & 63, t = e >> 8, w = t / sh.NW, nb = t - w * sh.NW;
-    const int r = hid_neuron(sh, 16 * w + 4 * (lane >> 4) + i), c = hid_neuron(sh, 16 * nb + (lane & 15));
+    int rp, cp;
+    slab_tile_rc(sh, e, rp, cp);
+    const int r = hid_neuron(sh, rp), c = hid_neuron(sh, cp);
     return r >= 0 && c >= 0 ? sh.p_w[l] + (int64_t)r * W + c : -1;
   }
   if (pos < sh.s_w1) {
@@ -136,8 +151,8 @@ __device__ __forceinline__ void write_copies(const Shape& sh, float* fr, int64_t
     return;
   }
   const int per = Wp * Wp, li = (int)(pos / per), e = (int)(pos - (int64_t)li * per);
-  const int lane = (e >> 2) & 63, t = e >> 8, w = t / sh.NW, nb = t - w * sh.NW;
-  const int r = 16 * w + 4 * (lane >> 4) + (e & 3), c = 16 * nb + (lane & 15);
+  int r, c;
+  slab_tile_rc(sh, e, r, c);
   if (!sh.s3) {
     const int seg = Wp / 4, g = c / seg, q = c - g * seg;
     fr[sh.f_hid + (int64_t)li * 2 * per + (((int64_t)(r >> 4) * (Wp / 16) + (q >> 2)) * 64 + 16 * g + (r & 15)) * 4 + (q & 3)] = v;
@@ -548,7 +563,10 @@ int step_value_points(int dim, int tile_points) {
 
 // LDS of a compute unit
 constexpr int kLdsBytes = 160 * 1024;
-bool split_fits(int dim, int NW) { return split_query_lds(dim + 1, NW, NW < 8 ? NW : 8, 2 * dim + 2).total <= kLdsBytes; }
+bool split_fits(int dim, int NW) {
+  const int NCB = 2 * dim + 2;
+  return std::max(split_query_lds(dim + 1, NW, std::min(NW, 8), NCB).total, split_step_lds(dim + 1, NW, NCB).total) <= kLdsBytes;
+}
 
 static const void* split_step_any(int dim, int tile_points, int act, int NW) {
   if (dim == 2) return act == ACT_SIN ? split_step_ptr<2, ACT_SIN>(tile_points, NW) : split_step_ptr<2, ACT_TANH>(tile_points, NW);
@@ -687,7 +705,7 @@ hipError_t set_lds_limits(int bytes) {
   for (int dim = 2; dim <= 3; ++dim)
     for (int act = ACT_TANH; act <= ACT_SIN; ++act) {
       allow(split_step_any(dim, 32, act, 4));
-      for (int nw : {8}) allow(split_step_any(dim, 16, act, nw));
+      for (int nw : {8, 13}) allow(split_step_any(dim, 16, act, nw));
       for (int nw : {8, 16}) {
         for (int mode : {M_PDE, M_VALUE, M_GRAD}) {
           allow(split_query_any(dim, mode, act, 0, nw));

@@ -2,175 +2,322 @@
 // (ddpinn_split.h): forward with derivative channels, residuals, losses,
 // adjoint and weight gradients of one tile of points after another.
 //
-// A workgroup of up to four waves takes a tile through the whole step; wave w owns
-// the row blocks [rb0(w), rb0(w+1)) of every layer (two per wave up to 128
-// neurons, three or four above), all columns of the tile.  Two row blocks per
-// wave halve what the waves read from LDS against one: at one row block the LDS
-// reads of a contraction take as long as its matrix instructions, at two half as
-// long.  One activation stack is in LDS at a time:
-//   forward, layer l:   H_{l-1} -> Z_l = W_l H_{l-1} -> chain rule -> H_l
-//   backward, layer l:  Zbar_l  -> Hbar_{l-1} = W_l^T Zbar_l; every wave keeps the
-//                       operand fragments of its own Zbar_l rows in registers
-//                       H_{l-1} -> dW_l = Zbar_l H_{l-1}^T
-// so that the stack (6 bytes per value: 73 KiB for a 2D tile at 128 neurons, 96 KiB in 3D) leaves room
-// for two workgroups per compute unit in 2D, whose matrix and vector phases then
-// overlap.
+// A workgroup of up to eight waves takes a tile through the whole step; a wave owns
+// one row block of 16 neurons of every layer (two for the first waves above 128 neurons)
+// and all columns of the tile.
+//
+// Transposed tiles.  The activations enter the matrix instructions as the first
+// operand and the weights as the second, so a wave's accumulator fragment
+// acc[r][cb] holds, in lane (g, j) (g = lane / 16, j = lane % 16), neuron j of the
+// row block and columns 16 cb + 4g + i (i = 0..3).  Every channel of a (neuron,
+// point) pair sits in one lane, sums over a tile's columns stay in the lane (and
+// the four groups), and, for the weight gradient
+//   dW_l[m][n] = sum_col Zbar_l[m][col] H_{l-1}[n][col],
+// a wave's own rows of H_{l-1}, split, are its operand as they lie in the registers.
+// So only Zbar_l is in LDS in the backward (only H_{l-1} in the forward): one
+// stack of 6 bytes per value, and two barriers per layer; between them a wave runs its
+// recomputation of h, its share of dW and of Hbar_{l-1} = W_l^T Zbar_l and its adjoint on
+// its own, so that one wave's vector work overlaps another's matrix work.
+//
+// The LDS stack.  Unit (row block, column blocks 2 kc and 2 kc + 1, part): 1 KiB,
+// slot (g, j) of 16 bytes at 16 g + (j ^ c(g)): the lane's four columns of each of the two
+// column blocks (the even one first for g = 0, 3, second for g = 1, 2).  A
+// contraction over columns reads a slot as it lies (ds_read_b128); a contraction over neurons uses
+// the transposing read (ds_read_b64_tr_b16), which gives a lane one column and four neurons, once per
+// row block.
 #include <type_traits>
 
 #include "ddpinn_split.h"
 
 namespace ddp {
 
-// sum over the 16 lanes of a lane group, in every lane
-__device__ __forceinline__ float row_sum(float v) {
-  auto rot = [](float x, auto ctrl) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value,
-                                                                 0xf, 0xf, false));
-  };
-  v += rot(v, std::integral_constant<int, 0x128>{});   // row_ror:8
-  v += rot(v, std::integral_constant<int, 0x124>{});
-  v += rot(v, std::integral_constant<int, 0x122>{});
-  v += rot(v, std::integral_constant<int, 0x121>{});
+// sum over the four lane groups, in every lane
+__device__ __forceinline__ float group_sum(float v) {
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
   return v;
 }
-__device__ __forceinline__ v4f row_sum4(v4f v) { return v4f{row_sum(v[0]), row_sum(v[1]), row_sum(v[2]), row_sum(v[3])}; }
 
 __device__ __forceinline__ v4s lds_read_tr(const char* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS v4s*)(const LDS_AS char*)p);
 }
 
-// operand of a contraction over columns: one row block, column blocks 2 kc and
-// 2 kc + 1, one part; p: the unit of column block 2 kc plus the lane's slot,
-// stride: bytes from one column block's unit to the next
-__device__ __forceinline__ v8h col_operand(const char* p, int stride) {
-  const v4s lo = lds_read_tr(p), hi = lds_read_tr(p + stride);
-  return __builtin_bit_cast(v8h, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
+// byte offset of a unit from the stack's first
+template <int NCB>
+__device__ __forceinline__ constexpr int unit_at(int kc, int p) { return (3 * kc + p) * 2 * kUnit; }
+template <int NCB>
+struct Stack {
+  static constexpr int kRow = NCB / 2 * 3 * 2 * kUnit;   // bytes of a row block
+};
 
-// the wave's own row blocks of the stack as operands of a contraction over columns
-template <int R, int NCB>
-__device__ __forceinline__ void own_operands(const char* st, int rb0, int NW, const LaneSlots& ls, v8h (&za)[R][NCB / 2][3]) {
+// A lane's byte offsets: where it stores its columns of an even and of an odd column
+// block; its slot; and its transposing reads of the even and of the odd column
+// block, of the two row blocks in the K order of the weight fragments
+// (k_neuron: the odd row block first for lane groups 1 and 2) and of one alone.
+struct StepSlots { uint32_t put[2], slot, tr[2][2], tr1[2]; };
+template <int NCB>
+__device__ __forceinline__ StepSlots step_slots(int lane) {
+  const LaneSlots ls = lane_slots(lane);
+  const int h = slot_half(lane >> 4);
+  StepSlots s;
+  s.slot = ls.pair;
+  s.put[0] = ls.pair + ls.half;
+  s.put[1] = ls.pair + 8u - ls.half;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    bool alone;
-    const char* base = st + stack_row<NCB>(rb0 + r, NW, alone);
-    base += alone ? ls.alone_tr : ls.pair_tr + (((rb0 + r) & 1) ? 8u - ls.half_tr : ls.half_tr);
-    const int u = alone ? kUnit : 2 * kUnit;
-#pragma unroll
-    for (int kc = 0; kc < NCB / 2; ++kc)
-#pragma unroll
-      for (int p = 0; p < 3; ++p) za[r][kc][p] = col_operand(base + (6 * kc + p) * u, 3 * u);
+  for (int o = 0; o < 2; ++o) {
+    s.tr1[o] = ls.pair_tr + (o ? 8u - ls.half_tr : ls.half_tr);
+    s.tr[o][0] = s.tr1[o] + (uint32_t)(h ? Stack<NCB>::kRow : 0);
+    s.tr[o][1] = s.tr1[o] + (uint32_t)(h ? 0 : Stack<NCB>::kRow);
   }
+  return s;
 }
 
-// dw = the wave's dW rows times NT row blocks of H (base[t]: their units), over the
-// tile's columns
-template <int R, int NCB, int NT, int U>
-__device__ __forceinline__ void dw_group(const v8h (&za)[R][NCB / 2][3], const char* const (&base)[NT], v4f (&dw)[R][NT]) {
+// one fragment (column block cb), split, into the row block's units at st
+template <int NCB>
+__device__ __forceinline__ void put_cb(char* st, const StepSlots& ss, int cb, v4f v) {
+  v2u p[3];
+  split4(v, p);
 #pragma unroll
-  for (int kc = 0; kc < NCB / 2; ++kc) {
-    v8h b[NT][3];
+  for (int q = 0; q < 3; ++q) *reinterpret_cast<v2u*>(st + ss.put[cb & 1] + unit_at<NCB>(cb >> 1, q)) = p[q];
+}
+template <int R, int NCB>
+__device__ __forceinline__ void put_rows(char* st, const StepSlots& ss, const v4f (&a)[R][NCB]) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+  for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int p = 0; p < 3; ++p) b[t][p] = col_operand(base[t] + (6 * kc + p) * U, 3 * U);
-    __builtin_amdgcn_sched_barrier(0);
+    for (int cb = 0; cb < NCB; ++cb) put_cb<NCB>(st + r * Stack<NCB>::kRow, ss, cb, a[r][cb]);
+}
+
+// operand of a contraction over neurons: column blocks 2 kc, 2 kc + 1 of the K
+// block whose row blocks start at st
+template <int NCB>
+__device__ __forceinline__ void neuron_operand(const char* st, const StepSlots& ss, int kc, v8h (&a)[2][3]) {
 #pragma unroll
-    for (int q = 0; q < 6; ++q) {
+  for (int o = 0; o < 2; ++o)
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+    for (int p = 0; p < 3; ++p) {
+      const v4s lo = lds_read_tr(st + ss.tr[o][0] + unit_at<NCB>(kc, p)), hi = lds_read_tr(st + ss.tr[o][1] + unit_at<NCB>(kc, p));
+      a[o][p] = __builtin_bit_cast(v8h, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+}
+
+// acc[r][cb] = (weights of the wave's row blocks) x (stack), transposed tile.  f: the weight
+// fragments of the first K block; the next block's are requested before the
+// products of the current one, and so are the stack operands of the next two column
+// blocks (12 R matrix instructions of 16 cycles ahead).
+template <int R, int NCB>
+__device__ __forceinline__ void gemm_neurons_t(const float* wf, const char* st, int NW, const StepSlots& ss,
+                                               uint32_t lane16, Frags<R>& f, v4f (&acc)[R][NCB]) {
+  constexpr int NC = NCB / 2;
+  const int KF = NW >> 1, KB = (NW + 1) >> 1;
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-          dw[r][t] = mfma32(za[r][kc][kPartA[q]], b[t][kPartB[q]], (kc == 0 && q == 0) ? zero4() : dw[r][t]);
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) acc[r][cb] = zero4();
+  v8h a[2][3], an[2][3];
+  if (KF > 0) neuron_operand<NCB>(st, ss, 0, an);
+  for (int kb = 0; kb < KF; ++kb, st += 2 * Stack<NCB>::kRow) {
+    v4f w[R][3];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) w[r][p] = f.a[r][p];
+    load_frags<R>(wf, KB, kb + 1 < KB ? kb + 1 : kb, lane16, f);   // (the last one again at the end)
+#pragma unroll
+    for (int kc = 0; kc < NC; ++kc) {
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) a[o][p] = an[o][p];
+      if (kc + 1 < NC) neuron_operand<NCB>(st, ss, kc + 1, an);
+      else neuron_operand<NCB>(kb + 1 < KF ? st + 2 * Stack<NCB>::kRow : st, ss, 0, an);
       __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            acc[r][2 * kc + o] = mfma32(a[o][kPartB[q]], __builtin_bit_cast(v8h, w[r][kPartA[q]]), acc[r][2 * kc + o]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  if (NW & 1) {   // a last K block of 16 neurons
+#pragma unroll
+    for (int kc = 0; kc < NC; ++kc) {
+      v4s a4[2][3];
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) a4[o][p] = lds_read_tr(st + ss.tr1[o] + unit_at<NCB>(kc, p));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const v8s w8 = __builtin_bit_cast(v8s, f.a[r][kPartA[q]]);
+            acc[r][2 * kc + o] = mfma16(a4[o][kPartB[q]], __builtin_shufflevector(w8, w8, 0, 1, 2, 3), acc[r][2 * kc + o]);
+          }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   }
 }
 
-// dW of the wave's row blocks, two column blocks (row blocks of H) at a time, added
-// to the slab (sw: tiles [row block][NW][64 lanes][4] from the wave's first row
-// block); the old slab values are requested before the products they are added to
-template <int R, int NCB>
-__device__ __forceinline__ void gemm_columns(const v8h (&za)[R][NCB / 2][3], const char* st, int NW, const LaneSlots& ls,
-                                             uint32_t lane16, float* sw, bool first) {
-  constexpr int kNext = NCB * 2 * kUnits3;
-  auto add = [&](int nb, auto nt, auto unit, const char* const (&base)[decltype(nt)::value]) {
-    constexpr int NT = decltype(nt)::value;
-    v4f old[R][NT], dw[R][NT];
+// output layer: ys[o][col] = W_{H+1}[o] . h[col] (+ b_{H+1}[o] on value columns);
+// column blocks in turn over the waves
+template <int D, int NCB>
+__device__ __forceinline__ void output_t(const float* wof, const char* st, int NW, const StepSlots& ss, uint32_t lane16,
+                                         const float* bop, int nvb, float* ys, int w, int NWV, int g, int j) {
+  constexpr int NCOL = 16 * NCB;
+  const int KF = NW >> 1, KB = (NW + 1) >> 1;
+  for (int cb = w; cb < NCB; cb += NWV) {
+    const char* sc = st + unit_at<NCB>(cb >> 1, 0);
+    const uint32_t t0 = cb & 1 ? ss.tr[1][0] : ss.tr[0][0], t1 = cb & 1 ? ss.tr[1][1] : ss.tr[0][1];
+    v4f y = zero4();
+    for (int kb = 0; kb < KB; ++kb, sc += 2 * Stack<NCB>::kRow) {
+      Frags<1> f;
+      load_frags<1>(wof, KB, kb, lane16, f);
+      if (kb < KF) {
+        v8h a[3];
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+        for (int p = 0; p < 3; ++p) {
+          const v4s lo = lds_read_tr(sc + t0 + unit_at<NCB>(0, p)), hi = lds_read_tr(sc + t1 + unit_at<NCB>(0, p));
+          a[p] = __builtin_bit_cast(v8h, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
 #pragma unroll
-      for (int t = 0; t < NT; ++t) old[r][t] = first ? zero4() : ldg4u(sw + (size_t)(r * NW + nb + t) * 256, lane16);
-    dw_group<R, NCB, NT, decltype(unit)::value>(za, base, dw);
+        for (int q = 0; q < 6; ++q) y = mfma32(a[kPartB[q]], __builtin_bit_cast(v8h, f.a[0][kPartA[q]]), y);
+      } else {
+        const uint32_t t = cb & 1 ? ss.tr1[1] : ss.tr1[0];
+        v4s a[3];
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+        for (int p = 0; p < 3; ++p) a[p] = lds_read_tr(sc + t + unit_at<NCB>(0, p));
 #pragma unroll
-      for (int t = 0; t < NT; ++t) stg4u(sw + (size_t)(r * NW + nb + t) * 256, lane16, old[r][t] + dw[r][t]);
-  };
-  const char* base[2] = {st + ls.pair_tr + ls.half_tr, st + ls.pair_tr + 8 - ls.half_tr};
-  int nb = 0;
-  for (; nb + 2 <= NW; nb += 2) {
-    const char* const bt[2] = {base[0], base[1]};
-    add(nb, std::integral_constant<int, 2>{}, std::integral_constant<int, 2 * kUnit>{}, bt);
-    base[0] += kNext;
-    base[1] += kNext;
-  }
-  if (nb < NW) {
-    const char* const bt[1] = {st + (nb >> 1) * kNext + ls.alone_tr};
-    add(nb, std::integral_constant<int, 1>{}, std::integral_constant<int, kUnit>{}, bt);
-  }
-}
-
-// h of a pre-activation stack (SV: tanh(z0) in place of z0)
-template <int DIM, int NCB, int MODE, int ACT, bool SV>
-__device__ __forceinline__ void act_recompute(const v4f (&z)[NCB], v4f (&h)[NCB]) {
-  using M = ModeCfg<DIM, NCB, MODE>;
-  constexpr int NPB = M::NPB;
-#pragma unroll
-  for (int pb = 0; pb < NPB; ++pb)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float s, s1, s2;
-      act_d2s<ACT, SV>(z[pb][i], s, s1, s2);
-      h[pb][i] = s;
-      if constexpr (MODE == M_PDE) {
-#pragma unroll
-        for (int jj = 0; jj <= DIM; ++jj) h[(1 + jj) * NPB + pb][i] = s1 * z[(1 + jj) * NPB + pb][i];
-#pragma unroll
-        for (int jj = 0; jj < DIM; ++jj) {
-          const float z1 = z[(1 + jj) * NPB + pb][i];
-          h[(DIM + 2 + jj) * NPB + pb][i] = s2 * z1 * z1 + s1 * z[(DIM + 2 + jj) * NPB + pb][i];
+        for (int q = 0; q < 6; ++q) {
+          const v8s w8 = __builtin_bit_cast(v8s, f.a[0][kPartA[q]]);
+          y = mfma16(a[kPartB[q]], __builtin_shufflevector(w8, w8, 0, 1, 2, 3), y);
         }
       }
     }
+    if (j < D) {
+      if (cb < nvb) y += ldg(bop + j);
+      *reinterpret_cast<v4f*>(ys + j * NCOL + 16 * cb + 4 * g) = y;
+    }
+  }
 }
 
-// h of a stashed pre-activation stack (SV: tanh(z0) in place of z0), one channel
-// at a time straight into the LDS stack (few values live at once)
-template <int DIM, int NCB, int MODE, int ACT, bool SV, int U>
-__device__ __forceinline__ void act_store(char* base, const v4f (&z)[NCB]) {
+// h of a pre-activation stack (SV: tanh(z0) in place of z0), split, as the
+// operand of a contraction over columns; a pair of column blocks at a time
+template <int DIM, int NCB, int MODE, int ACT, bool SV>
+__device__ __forceinline__ void h_operand(const v4f (&z)[NCB], bool swap, v8h (&ha)[NCB / 2][3]) {
   using M = ModeCfg<DIM, NCB, MODE>;
   constexpr int NPB = M::NPB;
+  v4f s1[NPB], s2[NPB];   // (value mode: unused)
+  auto h_of = [&](int cb) -> v4f {
+    const int c = cb / NPB, pb = cb - c * NPB;
+    if (c == 0) {
+      v4f s;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float a0, a1, a2;
+        act_d2s<ACT, SV>(z[cb][i], a0, a1, a2);
+        s[i] = a0;
+        if constexpr (MODE == M_PDE) {
+          s1[pb][i] = a1;
+          s2[pb][i] = a2;
+        }
+      }
+      return s;
+    }
+    if constexpr (MODE == M_PDE) {
+      if (c <= DIM + 1) return s1[pb] * z[cb];
+      const v4f z1 = z[(c - DIM - 1) * NPB + pb];
+      return s2[pb] * z1 * z1 + s1[pb] * z[cb];
+    }
+    return zero4();
+  };
+#pragma unroll
+  for (int kc = 0; kc < NCB / 2; ++kc) {
+    v2u e[3], o[3];
+    split4(h_of(2 * kc), e);
+    split4(h_of(2 * kc + 1), o);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const uint32_t u[4] = {swap ? o[p][0] : e[p][0], swap ? o[p][1] : e[p][1], swap ? e[p][0] : o[p][0], swap ? e[p][1] : o[p][1]};
+      typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+      ha[kc][p] = __builtin_bit_cast(v8h, v4u{u[0], u[1], u[2], u[3]});
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// dW of one row block n of H (ha) against two row blocks m of Zbar at a time, added to the slab (sw:
+// tiles [NW][64 lanes][4] of row block n; lane (g, j): neuron 4g + i of n, neuron
+// j of m).  The old slab values are requested before the products they are added to.
+template <int NCB>
+__device__ __forceinline__ void gemm_columns_t(const v8h (&ha)[NCB / 2][3], const char* st, int NW, const StepSlots& ss,
+                                               uint32_t lane16, float* sw, bool first) {
+  const char* base = st + ss.slot;
+  auto add = [&](int mb, auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    v4f old[NT], dw[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) old[t] = first ? zero4() : ldg4u(sw + (size_t)(mb + t) * 256, lane16);
+#pragma unroll
+    for (int kc = 0; kc < NCB / 2; ++kc) {
+      v8h b[NT][3];
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          b[t][p] = *reinterpret_cast<const v8h*>(base + t * Stack<NCB>::kRow + unit_at<NCB>(kc, p));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          dw[t] = mfma32(ha[kc][kPartA[q]], b[t][kPartB[q]], (kc == 0 && q == 0) ? zero4() : dw[t]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) stg4u(sw + (size_t)(mb + t) * 256, lane16, old[t] + dw[t]);
+    base += NT * Stack<NCB>::kRow;
+  };
+  int mb = 0;
+  for (; mb + 2 <= NW; mb += 2) add(mb, std::integral_constant<int, 2>{});
+  if (mb < NW) add(mb, std::integral_constant<int, 1>{});
+}
+
+// input layer: z0 = W1 xi + b1 and the seeded channels, transposed tile
+template <int DIM, int NCB, int MODE>
+__device__ __forceinline__ void input_layer_t(v4f (&a)[NCB], const float* __restrict__ W1p,
+                                              const float* __restrict__ b1p, const float* xin, int rb, int g, int j) {
+  using M = ModeCfg<DIM, NCB, MODE>;
+  constexpr int D = DIM + 1, NPB = M::NPB;
+  const int r = 16 * rb + j;
+  float wr[D];
+#pragma unroll
+  for (int q = 0; q < D; ++q) wr[q] = ldg(W1p + r * D + q);
+  const float br = ldg(b1p + r);
 #pragma unroll
   for (int pb = 0; pb < NPB; ++pb) {
-    v4f sv, s1, s2;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float a0, a1, a2;
-      act_d2s<ACT, SV>(z[pb][i], a0, a1, a2);
-      sv[i] = a0;
-      s1[i] = a1;
-      s2[i] = a2;
+      const float* xp = xin + (16 * pb + 4 * g + i) * D;
+      float z = br;
+#pragma unroll
+      for (int q = 0; q < D; ++q) z += wr[q] * xp[q];
+      a[pb][i] = z;
     }
-    stack_put<U>(base, pb, sv);
     if constexpr (MODE == M_PDE) {
 #pragma unroll
-      for (int jj = 0; jj <= DIM; ++jj) stack_put<U>(base, (1 + jj) * NPB + pb, s1 * z[(1 + jj) * NPB + pb]);
+      for (int jj = 0; jj <= DIM; ++jj) a[(1 + jj) * NPB + pb] = v4f{wr[jj], wr[jj], wr[jj], wr[jj]};
 #pragma unroll
-      for (int jj = 0; jj < DIM; ++jj) {
-        const v4f z1 = z[(1 + jj) * NPB + pb];
-        stack_put<U>(base, (DIM + 2 + jj) * NPB + pb, s2 * z1 * z1 + s1 * z[(DIM + 2 + jj) * NPB + pb]);
-      }
+      for (int jj = 0; jj < DIM; ++jj) a[(DIM + 2 + jj) * NPB + pb] = zero4();
     }
   }
 }
@@ -184,7 +331,6 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
   constexpr int NCOL = 16 * NCB;
   using MP = ModeCfg<DIM, NCB, M_PDE>;
   using MV = ModeCfg<DIM, NCB, M_VALUE>;
-  constexpr bool LEAN = NCB > 6;   // few registers to spare: h one channel at a time
   constexpr bool SV = ACT == ACT_TANH;   // the stash keeps tanh(z0) in place of z0
 
   const Shape& sh = args.sh;
@@ -192,11 +338,12 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int lane = tid & 63, g = lane >> 4, j = lane & 15;
   const uint32_t lane16 = (uint32_t)lane * 16u;
-  const LaneSlots ls = lane_slots(lane);
+  const StepSlots ss = step_slots<NCB>(lane);
+  const bool swap = slot_half(g);
   const SplitStepLds L = split_step_lds(D, NW, NCB);
   float* ys = reinterpret_cast<float*>(lds + L.ys);
   float* xin = reinterpret_cast<float*>(lds + L.xin);
-  float* part = reinterpret_cast<float*>(lds);
+  char* mine = lds + rb0 * Stack<NCB>::kRow;   // the wave's row blocks in the stack
   // stash: z of (layer, row block, column block), 1 KiB wave fragments
   float* stash = args.stash + (size_t)blockIdx.x * args.stash_per_wg + (size_t)rb0 * NCB * 256;
   const size_t stash_l = (size_t)NW * NCB * 256;
@@ -268,8 +415,11 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
       // derivatives of tanh are polynomials.
       v4f acc[R][NCB];
       const int nvb = pde ? MP::NPB : MV::NPB;   // value-channel column blocks
+      auto act = [&](int r) {
+        if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc[r]);
+        else act_forward<DIM, NCB, M_VALUE, ACT>(acc[r]);
+      };
       // z_l in acc -> stash, then h_l in acc
-      v4f zl[R][NCB];   // z_H
       auto activate = [&](int l) {
         float* st = stash + (size_t)(l - 1) * stash_l;
 #pragma unroll
@@ -277,8 +427,7 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb)
             if (!SV || cb >= nvb) stg4u(st + (r * NCB + cb) * 256, lane16, acc[r][cb]);
-          if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc[r]);
-          else act_forward<DIM, NCB, M_VALUE, ACT>(acc[r]);
+          act(r);
           if (SV) {
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb)
@@ -286,41 +435,42 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
           }
         }
       };
-      auto activate_last = [&] {   // z_H in acc -> zl, h_H in acc
+      v4f zl[R][NCB];   // z_H
+      auto activate_last = [&] {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb) zl[r][cb] = acc[r][cb];
-          if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc[r]);
-          else act_forward<DIM, NCB, M_VALUE, ACT>(acc[r]);
+          act(r);
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb)
             if (SV && cb < nvb) zl[r][cb] = acc[r][cb];
         }
       };
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (pde) input_layer<DIM, NCB, M_PDE>(acc[r], fr + sh.f_w1, bp, xin, rb0 + r, g, j);
-        else input_layer<DIM, NCB, M_VALUE>(acc[r], fr + sh.f_w1, bp, xin, rb0 + r, g, j);
-      }
       const float* wf = fr + sh.f_hid3 + (size_t)rb0 * KB * 3 * kFragFloats;   // of W_2
       Frags<R> f;   // weight fragments and bias of the next contraction over neurons
-      v4f bias[R];
+      float bias[R];
       auto load_bias = [&](int l) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) bias[r] = ldg4(bp + (l - 1) * Wp + 16 * (rb0 + r) + 4 * g);
+        for (int r = 0; r < R; ++r) bias[r] = ldg(bp + (l - 1) * Wp + 16 * (rb0 + r) + j);
       };
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (pde) input_layer_t<DIM, NCB, M_PDE>(acc[r], fr + sh.f_w1, bp, xin, rb0 + r, g, j);
+        else input_layer_t<DIM, NCB, M_VALUE>(acc[r], fr + sh.f_w1, bp, xin, rb0 + r, g, j);
+      }
       if (H > 1) {
         load_frags<R>(wf, KB, 0, lane16, f);
         load_bias(2);
+        activate(1);
+      } else {
+        activate_last();
       }
-      if (H > 1) activate(1);
-      else activate_last();
       for (int l = 2; l <= H; ++l) {
-        stack_store<R, NCB>(lds, rb0, NW, ls, acc);
+        put_rows<R, NCB>(mine, ss, acc);
         __syncthreads();
         if (prio) __builtin_amdgcn_s_setprio(1);
-        gemm_neurons<R, NCB, true>(wf + (size_t)(l - 2) * sh.hid3_layer, lds, NW, ls, lane16, f, acc);
+        gemm_neurons_t<R, NCB>(wf + (size_t)(l - 2) * sh.hid3_layer, lds, NW, ss, lane16, f, acc);
         __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -330,17 +480,17 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
         if (l < H) {
           load_frags<R>(wf + (size_t)(l - 1) * sh.hid3_layer, KB, 0, lane16, f);
           load_bias(l + 1);
+          activate(l);
+        } else {
+          activate_last();
         }
-        if (l < H) activate(l);
-        else activate_last();
         __syncthreads();
       }
 
       // ---- output layer
-      output_partials<D, R, NCB>(part, Wop, Wp, rb0, w, g, j, acc);
+      put_rows<R, NCB>(mine, ss, acc);
       __syncthreads();
-      if (pde) output_sum<DIM, NCB, M_PDE>(part, 4 * sh.NWV, fr + sh.f_bo, ys, tid, nthr);
-      else output_sum<DIM, NCB, M_VALUE>(part, 4 * sh.NWV, fr + sh.f_bo, ys, tid, nthr);
+      output_t<D, NCB>(fr + sh.f_wo3, lds, NW, ss, lane16, fr + sh.f_bo, nvb, ys, w, sh.NWV, g, j);
       __syncthreads();
 
       // ---- residuals, losses and output seeds ybar = dL/dy, in place of y
@@ -440,41 +590,36 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
 
       // ---- output layer adjoint: dW_{H+1} (h_H is in acc), db_{H+1}, hbar_H.
       // The small gradients (dW_{H+1}, db_l, dW_1) are summed over the tile's
-      // columns and added to the slab by the lanes j = 0.
-      auto load_z = [&](int l, int r, v4f (&z)[NCB]) {
-        const float* st = stash + (size_t)(l - 1) * stash_l + (size_t)r * NCB * 256;
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) z[cb] = ldg4u(st + cb * 256, lane16);
-      };
+      // columns and added to the slab by the lanes g = 0.
       {
-        float* so = slab + sh.s_wo + 16 * rb0 + 4 * g;
+        float* so = slab + sh.s_wo + 16 * rb0 + j;
         v4f hb[R][NCB];
 #pragma unroll
         for (int o = 0; o < D; ++o) {
-          v4f old[R], wo[R], s[R];
+          float old[R], wo[R], s[R];
 #pragma unroll
           for (int r = 0; r < R; ++r) {
-            old[r] = (j == 0 && !first) ? ldg4(so + o * Wp + 16 * r) : zero4();
-            wo[r] = ldg4(Wop + o * Wp + 16 * (rb0 + r) + 4 * g);
-            s[r] = zero4();
+            old[r] = (g == 0 && !first) ? ldg(so + o * Wp + 16 * r) : 0.f;
+            wo[r] = ldg(Wop + o * Wp + 16 * (rb0 + r) + j);
+            s[r] = 0.f;
           }
           float b = 0.f;
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb) {
-            const float yv = ys[o * NCOL + 16 * cb + j];
-            if (cb < nvb) b += yv;
+            const v4f yv = *reinterpret_cast<const v4f*>(ys + o * NCOL + 16 * cb + 4 * g);
+            if (cb < nvb) b += (yv[0] + yv[1]) + (yv[2] + yv[3]);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-              s[r] += yv * acc[r][cb];
+              s[r] += (yv[0] * acc[r][cb][0] + yv[1] * acc[r][cb][1]) + (yv[2] * acc[r][cb][2] + yv[3] * acc[r][cb][3]);
               hb[r][cb] = o == 0 ? wo[r] * yv : hb[r][cb] + wo[r] * yv;
             }
           }
 #pragma unroll
           for (int r = 0; r < R; ++r) {
-            s[r] = row_sum4(s[r]);
-            if (j == 0) stg4(so + o * Wp + 16 * r, old[r] + s[r]);
+            s[r] = group_sum(s[r]);
+            if (g == 0) stg(so + o * Wp + 16 * r, old[r] + s[r]);
           }
-          b = row_sum(b);
+          b = group_sum(b);
           if (tid == o) dbo += b;
           asm volatile("" : "+v"(dbo));   // now: its terms would be kept until the tile's end
         }
@@ -483,107 +628,86 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb) acc[r][cb] = hb[r][cb];
       }
-      // Layer l, one row block after another: H_l into the LDS stack (below H);
-      // acc = hbar_l -> zbar_l; db_l and, at l = 1, dW_1.
-      auto adjoint = [&](int l, v4f (&zn)[NCB], auto last) {   // zn: z_l of the first row block, if not last
-        float* sb = slab + sh.s_b + (size_t)(l - 1) * Wp + 16 * rb0 + 4 * g;
+      // adjoint of layer l, row block r: acc[r] = hbar_l -> zbar_l; db_l and, at l = 1, dW_1
+      auto adjoint = [&](int l, int r, const v4f (&z)[NCB]) {
+        float* sb = slab + sh.s_b + (size_t)(l - 1) * Wp + 16 * (rb0 + r) + j;
+        const float old = (g == 0 && !first) ? ldg(sb) : 0.f;
+        if (pde) act_adjoint<DIM, NCB, M_PDE, ACT, SV>(acc[r], z);
+        else act_adjoint<DIM, NCB, M_VALUE, ACT, SV>(acc[r], z);
+        float s = 0.f;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          v4f zs[NCB];
+        for (int cb = 0; cb < NCB; ++cb)
+          if (cb < nvb) s += (acc[r][cb][0] + acc[r][cb][1]) + (acc[r][cb][2] + acc[r][cb][3]);
+        s = group_sum(s);
+        if (g == 0) stg(sb, old + s);
+        if (l > 1) return;
+        // dW1[n][q] += sum_pts zbar0 xi_q + zbar_q (first-derivative channel q)
+        float* s1 = slab + sh.s_w1 + (size_t)(16 * (rb0 + r) + j) * D;
+        float v[D];
 #pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) zs[cb] = decltype(last)::value ? zl[r][cb] : zn[cb];
-          const v4f old = (j == 0 && !first) ? ldg4(sb + 16 * r) : zero4();
-          if constexpr (!decltype(last)::value) {
-            bool alone;
-            char* base = stack_row_slot<NCB>(lds, rb0 + r, NW, ls, alone);
-            if constexpr (LEAN) {
-              if (alone) {
-                if (pde) act_store<DIM, NCB, M_PDE, ACT, SV, kUnit>(base, zs);
-                else act_store<DIM, NCB, M_VALUE, ACT, SV, kUnit>(base, zs);
-              } else {
-                if (pde) act_store<DIM, NCB, M_PDE, ACT, SV, 2 * kUnit>(base, zs);
-                else act_store<DIM, NCB, M_VALUE, ACT, SV, 2 * kUnit>(base, zs);
-              }
-            } else {
-              v4f h[NCB];
-              if (pde) act_recompute<DIM, NCB, M_PDE, ACT, SV>(zs, h);
-              else act_recompute<DIM, NCB, M_VALUE, ACT, SV>(zs, h);
-              stack_store_row<NCB>(lds, rb0 + r, NW, ls, h);
+        for (int q = 0; q < D; ++q) v[q] = 0.f;
+        if (pde) {
+#pragma unroll
+          for (int pb = 0; pb < MP::NPB; ++pb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float* xp = xin + (16 * pb + 4 * g + i) * D;
+#pragma unroll
+              for (int q = 0; q < D; ++q) v[q] += acc[r][pb][i] * xp[q] + acc[r][(1 + q) * MP::NPB + pb][i];
             }
-          }
-          if (pde) act_adjoint<DIM, NCB, M_PDE, ACT, SV>(acc[r], zs);
-          else act_adjoint<DIM, NCB, M_VALUE, ACT, SV>(acc[r], zs);
-          v4f s = zero4();
+        } else {
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb)
-            if (cb < nvb) s += acc[r][cb];
-          s = row_sum4(s);
-          if (r + 1 < R && !decltype(last)::value) load_z(l, r + 1, zn);
-          if (j == 0) stg4(sb + 16 * r, old + s);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float* xp = xin + (16 * cb + 4 * g + i) * D;
+#pragma unroll
+              for (int q = 0; q < D; ++q) v[q] += acc[r][cb][i] * xp[q];
+            }
         }
-        if (l > 1) return;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          // dW1[n][q] += sum_pts zbar0 xi_q + zbar_q (first-derivative channel q)
-          float* s1 = slab + sh.s_w1 + (size_t)(16 * (rb0 + r) + 4 * g) * D;
-          v4f o1[D], v[D];
-#pragma unroll
-          for (int q = 0; q < D; ++q) {
-            o1[q] = (j == 0 && !first) ? ldg4(s1 + 4 * q) : zero4();
-            v[q] = zero4();
-          }
-          if (pde) {
-#pragma unroll
-            for (int pb = 0; pb < MP::NPB; ++pb)
-#pragma unroll
-              for (int q = 0; q < D; ++q)
-                v[q] += acc[r][pb] * xin[(16 * pb + j) * D + q] + acc[r][(1 + q) * MP::NPB + pb];
-          } else {
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-              for (int q = 0; q < D; ++q) v[q] += acc[r][cb] * xin[(16 * cb + j) * D + q];
-          }
-#pragma unroll
-          for (int q = 0; q < D; ++q) v[q] = row_sum4(v[q]);
-          if (j == 0) {
-            float t[4 * D];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-              for (int q = 0; q < D; ++q) t[i * D + q] = v[q][i];
-#pragma unroll
-            for (int q = 0; q < D; ++q) stg4(s1 + 4 * q, o1[q] + v4f{t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]});
-          }
+        for (int q = 0; q < D; ++q) {
+          const float t = group_sum(v[q]);
+          if (g == 0) stg(s1 + q, (first ? 0.f : ldg(s1 + q)) + t);
         }
       };
-      const float* wt = wf + sh.hid3_layer / 2;   // of W_2^T
-      if (H > 1) load_frags<R>(wt + (size_t)(H - 2) * sh.hid3_layer, KB, 0, lane16, f);
-      {
-        v4f none[NCB];
-        adjoint(H, none, std::true_type{});
-      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) adjoint(H, r, zl[r]);
 
       // ---- hidden layer adjoints
+      const float* wt = wf + sh.hid3_layer / 2;   // of W_2^T
       for (int l = H; l >= 2; --l) {
-        if (l < H) load_frags<R>(wt + (size_t)(l - 2) * sh.hid3_layer, KB, 0, lane16, f);
-        __syncthreads();   // every reader of the stack (dW_{l+1}; the output partials) is done
-        stack_store<R, NCB>(lds, rb0, NW, ls, acc);
+        // loads ahead of the barriers: z_{l-1} (of the first row block) and weights
+        auto load_z = [&](int r, v4f (&z)[NCB]) {
+          const float* st = stash + (size_t)(l - 2) * stash_l + (size_t)r * NCB * 256;
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) z[cb] = ldg4u(st + cb * 256, lane16);
+        };
+        v4f z[NCB];
+        load_z(0, z);
+        __syncthreads();   // every reader of the stack (layer l + 1; the output layer) is done
+        put_rows<R, NCB>(mine, ss, acc);
         __syncthreads();
-        v4f zn[NCB];   // z_{l-1} of the first row block
-        load_z(l - 1, 0, zn);
+        load_frags<R>(wt + (size_t)(l - 2) * sh.hid3_layer, KB, 0, lane16, f);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          v8h ha[NCB / 2][3];
+          if (pde) h_operand<DIM, NCB, M_PDE, ACT, SV>(z, swap, ha);
+          else h_operand<DIM, NCB, M_VALUE, ACT, SV>(z, swap, ha);
+          if (R > 1) load_z(r + 1 < R ? r + 1 : 0, z);   // for the next row block, at last again the first
+          if (prio) __builtin_amdgcn_s_setprio(1);
+          gemm_columns_t<NCB>(ha, lds, NW, ss, lane16,
+                              slab + sh.s_hid + (size_t)(l - 2) * Wp * Wp + (size_t)(rb0 + r) * NW * 256, first);
+          __builtin_amdgcn_s_setprio(0);
+        }
         if (prio) __builtin_amdgcn_s_setprio(1);
-        gemm_neurons<R, NCB, true>(wt + (size_t)(l - 2) * sh.hid3_layer, lds, NW, ls, lane16, f, acc);   // Hbar_{l-1}
+        gemm_neurons_t<R, NCB>(wt + (size_t)(l - 2) * sh.hid3_layer, lds, NW, ss, lane16, f, acc);   // Hbar_{l-1}
         __builtin_amdgcn_s_setprio(0);
-        v8h za[R][NCB / 2][3];
-        own_operands<R, NCB>(lds, rb0, NW, ls, za);
-        __syncthreads();
-        adjoint(l - 1, zn, std::false_type{});
-        __syncthreads();
-        if (prio) __builtin_amdgcn_s_setprio(1);
-        gemm_columns<R, NCB>(za, lds, NW, ls, lane16,
-                             slab + sh.s_hid + (size_t)(l - 2) * Wp * Wp + (size_t)rb0 * NW * 256, first);
-        __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          if (r > 0) load_z(r, z);
+          adjoint(l - 1, r, z);
+        }
       }
 
       // ---- end of segment: output bias gradient and loss sums
@@ -610,12 +734,20 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
 }
 
 // Two waves per SIMD (256 registers each); the 32-point tiles have twice the
-// columns and at most four waves, one per SIMD.
-template <int DIM, int PBP, int ACT>
+// columns and at most four waves, one per SIMD.  WIDE: above 128 neurons (eight
+// waves, the first NW - 8 of them with two row blocks).
+template <int DIM, int PBP, int ACT, int WIDE>
 __global__ __launch_bounds__(PBP == 1 ? 512 : 256, PBP == 1 ? 2 : 1) void split_step_kernel(const StepArgs args) {
   extern __shared__ __align__(16) char slds[];
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  step_tiles<DIM, PBP, ACT, 1>(args, slds, w, w);
+  if constexpr (WIDE) {
+    const int rb0 = split_rb0(w, args.sh.NW, args.sh.NWV);
+    // both branches meet the same barriers
+    if (w < args.sh.NW - args.sh.NWV) step_tiles<DIM, PBP, ACT, 2>(args, slds, rb0, w);
+    else step_tiles<DIM, PBP, ACT, 1>(args, slds, rb0, w);
+  } else {
+    step_tiles<DIM, PBP, ACT, 1>(args, slds, w, w);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -623,8 +755,8 @@ __global__ __launch_bounds__(PBP == 1 ? 512 : 256, PBP == 1 ? 2 : 1) void split_
 // ---------------------------------------------------------------------------
 template <int DIM, int ACT>
 const void* split_step_ptr(int tile_points, int NW) {
-  if (tile_points == 32) return NW <= 4 ? (const void*)split_step_kernel<DIM, 2, ACT> : nullptr;
-  return (const void*)split_step_kernel<DIM, 1, ACT>;
+  if (tile_points == 32) return NW <= 4 ? (const void*)split_step_kernel<DIM, 2, ACT, 0> : nullptr;
+  return NW > kMaxWaves ? (const void*)split_step_kernel<DIM, 1, ACT, 1> : (const void*)split_step_kernel<DIM, 1, ACT, 0>;
 }
 template const void* split_step_ptr<DDP_DIM, DDP_ACT>(int, int);
 
