@@ -496,8 +496,7 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   c->n_slabs = std::max(std::max(c->n_seg, c->ps_seg), 1);
   const int stash_wg = std::max(c->n_wg, 1);
   const int NCB = (2 * sh.dim + 2) * (c->tile_points / 16);
-  // t3: z_H stays in registers
-  c->stash_per_wg = (int64_t)sh.NW * (sh.t3 ? sh.H - 1 : sh.H) * NCB * 256;
+  c->stash_per_wg = (int64_t)sh.NW * sh.H * (NCB + (sh.t3 && sh.act == 1 ? c->tile_points / 16 : 0)) * 256;   // sin and t3: cos(z_0) too
 
   // exchange capacity: every ghost point in a half tile, plus one partial tile per face
   int64_t xcap = 0;

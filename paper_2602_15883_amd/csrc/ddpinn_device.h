@@ -35,8 +35,87 @@ __device__ __forceinline__ void stg4u(float* base, uint32_t off, v4f v) {
   *(GLOBAL_AS v4f*)((GLOBAL_AS char*)base + off) = v;
 }
 
-// sin and cos with full range reduction (device library)
-__device__ __forceinline__ void sincos_f32(float z, float& s, float& c) { sincosf(z, &s, &c); }
+__device__ __forceinline__ float ldgu(const float* base, uint32_t off) {
+  return *(const GLOBAL_AS float*)((const GLOBAL_AS char*)base + off);
+}
+__device__ __forceinline__ void stgu(float* base, uint32_t off, float v) {
+  *(GLOBAL_AS float*)((GLOBAL_AS char*)base + off) = v;
+}
+
+// sin and cos of four values.  The device library's sincosf carries its reduction
+// of large arguments inline: 0.5 KB of code and a branch per value, which, unrolled over a wave's fragments, made
+// the sin kernels up to 480 KB (the instruction cache holds 64) and spill.
+//   |z| <= 2^16 : r = z - k pi/2 in three fma steps (Cody and Waite; the first is
+//                 exact), then the Maclaurin series of sin and cos on |r| <= pi/4 (first
+//                 omitted terms 2e-9 and 1e-10)
+//   otherwise   : k and r from z * 2/pi modulo 4 in double, in pieces of 28 bits of 2/pi whose
+//                 products are exact (Payne and Hanek); one value after another in a
+//                 loop, which no ordinary network enters
+// Within 1.5 ulp of the exact values (the scheme is pinned on the CPU).
+__device__ __forceinline__ void sincos_reduce_large(float z, float& r, int& k) {
+  const double x = z;
+  double p = 0;
+  auto piece = [&](double c) {
+    const double t = x * c;
+    p += fma(-4.0, __builtin_rint(t * 0.25), t);
+  };
+  piece(0xa2f9836p-28);
+  piece(0xe4e4415p-56);
+  piece(0x29fc275p-84);
+  piece(0x7d1f534p-112);
+  piece(0xddc0db6p-140);
+  piece(0x295993cp-168);
+  piece(0x439041fp-196);
+  piece(0xe5163abp-224);
+  const double q = __builtin_rint(p);
+  k = (int)q;
+  r = (float)((p - q) * 1.5707963267948966);
+}
+__device__ __forceinline__ void sincos4(v4f z, v4f& s, v4f& c) {
+  v4f r;
+  int k[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float q = __builtin_rintf(z[i] * 0.63661977236758134f);
+    r[i] = fmaf(-q, -0x1.ee59dap-50f, fmaf(-q, -0x1.777a5cp-25f, fmaf(-q, 0x1.921fb6p+0f, z[i])));
+    k[i] = (int)q;
+  }
+  const float m = fmaxf(fmaxf(fabsf(z[0]), fabsf(z[1])), fmaxf(fabsf(z[2]), fabsf(z[3])));
+  if (__builtin_expect(m > 65536.f, 0)) {
+#pragma clang loop unroll(disable)
+    for (int t = 0; t < 4; ++t) {   // the four values rotate through the first place
+      float r0 = r[0];
+      if (fabsf(z[0]) > 65536.f) sincos_reduce_large(z[0], r0, k[0]);
+      r[0] = r0;
+      z = __builtin_shufflevector(z, z, 1, 2, 3, 0);
+      r = __builtin_shufflevector(r, r, 1, 2, 3, 0);
+      const int k0 = k[0];
+      k[0] = k[1];
+      k[1] = k[2];
+      k[2] = k[3];
+      k[3] = k0;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float x = r[i], u = x * x;
+    float p = 2.7557319223985893e-6f;       // 1/9!
+    p = fmaf(u, p, -1.9841269841269841e-4f);
+    p = fmaf(u, p, 8.3333333333333333e-3f);
+    p = fmaf(u, p, -1.6666666666666667e-1f);
+    const float sr = fmaf(x * u, p, x);
+    float q = -2.7557319223985888e-7f;      // -1/10!
+    q = fmaf(u, q, 2.4801587301587302e-5f);
+    q = fmaf(u, q, -1.3888888888888889e-3f);
+    q = fmaf(u, q, 4.1666666666666667e-2f);
+    q = fmaf(u, q, -0.5f);
+    const float cr = fmaf(u, q, 1.f);
+    // odd quarter turns exchange the two; the signs are bit 1 of k and of k + 1
+    const float a = (k[i] & 1) ? cr : sr, b = (k[i] & 1) ? sr : cr;
+    s[i] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, a) ^ ((uint32_t)(k[i] & 2) << 30));
+    c[i] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, b) ^ ((uint32_t)((k[i] + 1) & 2) << 30));
+  }
+}
 
 // tanh without branches, from two textbook forms:
 //   |x| < 0.4 : x * P(x^2), P = Maclaurin series of tanh(x)/x through the x^12
@@ -62,57 +141,32 @@ __device__ __forceinline__ float tanh_f32(float x) {
 
 enum : int { ACT_TANH = 0, ACT_SIN = 1 };
 
-// activation sigma(z) and its first derivatives: tanh (section 2.1 networks)
-// or sin (the paper's cylinder networks, section 3.2-3.3)
-template <int ACT>
-__device__ __forceinline__ void act_d2(float z, float& s, float& s1, float& s2) {
-  if constexpr (ACT == ACT_SIN) {
-    sincos_f32(z, s, s1);
-    s2 = -s;
-  } else {
-    s = tanh_f32(z);
-    s1 = 1.f - s * s;
-    s2 = -2.f * s * s1;
-  }
-}
-
+// activation sigma and its first derivatives: tanh (section 2.1 networks) or
+// sin (the paper's cylinder networks, section 3.2-3.3), four values at a time.
 // SV: the argument is tanh(z0) itself (kept in the stash in place of z0);
 // tanh's derivatives are polynomials in it, so tanh is not evaluated again
-template <int ACT, bool SV>
-__device__ __forceinline__ void act_d2s(float v, float& s, float& s1, float& s2) {
-  if constexpr (SV && ACT == ACT_TANH) {
-    s = v;
-    s1 = 1.f - s * s;
-    s2 = -2.f * s * s1;
-  } else {
-    act_d2<ACT>(v, s, s1, s2);
-  }
-}
-
-template <int ACT>
-__device__ __forceinline__ void act_d3(float z, float& s, float& s1, float& s2, float& s3) {
+template <int ACT, bool SV = false>
+__device__ __forceinline__ void act4(v4f z, v4f& s, v4f& s1, v4f& s2) {
   if constexpr (ACT == ACT_SIN) {
-    sincos_f32(z, s, s1);
+    sincos4(z, s, s1);
     s2 = -s;
-    s3 = -s1;
   } else {
-    s = tanh_f32(z);
+    if constexpr (SV) {
+      s = z;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[i] = tanh_f32(z[i]);
+    }
     s1 = 1.f - s * s;
     s2 = -2.f * s * s1;
-    s3 = 2.f * s1 * (3.f * s * s - 1.f);
   }
 }
 
-template <int ACT, bool SV>
-__device__ __forceinline__ void act_d3s(float v, float& s, float& s1, float& s2, float& s3) {
-  if constexpr (SV && ACT == ACT_TANH) {
-    s = v;
-    s1 = 1.f - s * s;
-    s2 = -2.f * s * s1;
-    s3 = 2.f * s1 * (3.f * s * s - 1.f);
-  } else {
-    act_d3<ACT>(v, s, s1, s2, s3);
-  }
+// the third derivative from the lower ones
+template <int ACT>
+__device__ __forceinline__ v4f act_third(v4f s, v4f s1) {
+  if constexpr (ACT == ACT_SIN) return -s1;
+  else return 2.f * s1 * (3.f * s * s - 1.f);
 }
 
 // Channel layout of a tile in a given mode.
@@ -140,24 +194,20 @@ __device__ __forceinline__ void act_forward(v4f (&a)[NCB]) {
   constexpr int NPB = M::NPB;
 #pragma unroll
   for (int pb = 0; pb < NPB; ++pb) {
+    v4f s, s1, s2;
+    act4<ACT>(a[pb], s, s1, s2);
+    a[pb] = s;
+    if constexpr (MODE == M_PDE) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float s, s1, s2;
-      act_d2<ACT>(a[pb][i], s, s1, s2);
-      if constexpr (MODE == M_PDE) {
-#pragma unroll
-        for (int jj = 0; jj < DIM; ++jj) {
-          const float z1 = a[(1 + jj) * NPB + pb][i];
-          const float z2 = a[(DIM + 2 + jj) * NPB + pb][i];
-          a[(DIM + 2 + jj) * NPB + pb][i] = s2 * z1 * z1 + s1 * z2;
-        }
-#pragma unroll
-        for (int jj = 0; jj <= DIM; ++jj) a[(1 + jj) * NPB + pb][i] *= s1;
-      } else if constexpr (MODE == M_GRAD) {
-#pragma unroll
-        for (int jj = 0; jj < DIM; ++jj) a[(1 + jj) * NPB + pb][i] *= s1;
+      for (int jj = 0; jj < DIM; ++jj) {
+        const v4f z1 = a[(1 + jj) * NPB + pb];
+        v4f& z2 = a[(DIM + 2 + jj) * NPB + pb];
+        z2 = s2 * z1 * z1 + s1 * z2;
       }
-      a[pb][i] = s;
+    }
+    if constexpr (MODE != M_VALUE) {
+#pragma unroll
+      for (int jj = 0; jj < M::CM - 1 && jj <= DIM; ++jj) a[(1 + jj) * NPB + pb] *= s1;
     }
   }
 }
@@ -173,35 +223,28 @@ __device__ __forceinline__ void act_adjoint(v4f (&hb)[NCB], const v4f (&zs)[NCB]
   constexpr int NPB = M::NPB;
 #pragma unroll
   for (int pb = 0; pb < NPB; ++pb) {
+    v4f s, s1, s2;
+    act4<ACT, SV>(zs[pb], s, s1, s2);
+    v4f z0b = s1 * hb[pb];
+    if constexpr (MODE == M_PDE) {
+      const v4f s3 = act_third<ACT>(s, s1);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if constexpr (MODE == M_PDE) {
-        float s, s1, s2, s3;
-        act_d3s<ACT, SV>(zs[pb][i], s, s1, s2, s3);
-        float z0b = s1 * hb[pb][i];
+      for (int jj = 0; jj <= DIM; ++jj) {
+        const int c = (1 + jj) * NPB + pb;
+        const v4f h1 = hb[c];
+        z0b += s2 * zs[c] * h1;
+        hb[c] = s1 * h1;
+      }
 #pragma unroll
-        for (int jj = 0; jj <= DIM; ++jj) {
-          const int c = (1 + jj) * NPB + pb;
-          const float h1 = hb[c][i];
-          z0b += s2 * zs[c][i] * h1;
-          hb[c][i] = s1 * h1;
-        }
-#pragma unroll
-        for (int jj = 0; jj < DIM; ++jj) {
-          const int c1 = (1 + jj) * NPB + pb, c2 = (DIM + 2 + jj) * NPB + pb;
-          const float h2 = hb[c2][i];
-          const float z1 = zs[c1][i], z2 = zs[c2][i];
-          hb[c2][i] = s1 * h2;
-          hb[c1][i] += 2.f * s2 * z1 * h2;
-          z0b += (s3 * z1 * z1 + s2 * z2) * h2;
-        }
-        hb[pb][i] = z0b;
-      } else {
-        float s, s1, s2;
-        act_d2s<ACT, SV>(zs[pb][i], s, s1, s2);
-        hb[pb][i] *= s1;
+      for (int jj = 0; jj < DIM; ++jj) {
+        const int c1 = (1 + jj) * NPB + pb, c2 = (DIM + 2 + jj) * NPB + pb;
+        const v4f h2 = hb[c2], z1 = zs[c1], z2 = zs[c2];
+        hb[c2] = s1 * h2;
+        hb[c1] += 2.f * s2 * z1 * h2;
+        z0b += (s3 * z1 * z1 + s2 * z2) * h2;
       }
     }
+    hb[pb] = z0b;
   }
 }
 

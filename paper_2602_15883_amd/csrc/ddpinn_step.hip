@@ -209,26 +209,105 @@ __device__ __forceinline__ void output_t(const float* wof, const char* st, int N
   }
 }
 
-// h of a pre-activation stack (SV: tanh(z0) in place of z0), split, as the
-// operand of a contraction over columns; a pair of column blocks at a time
-template <int DIM, int NCB, int MODE, int ACT, bool SV>
-__device__ __forceinline__ void h_operand(const v4f (&z)[NCB], bool swap, v8h (&ha)[NCB / 2][3]) {
+// What the stash keeps of a layer, per row block: the pre-activations z_c of the
+// derivative channels and, in place of z_0, what the derivatives of the activation at z_0
+// are polynomials in: tanh(z_0), or sin(z_0) and, in further blocks, cos(z_0), so that neither is
+// evaluated again in the backward.  Value tiles with sin keep z_0 itself (every
+// column block is a value there).
+template <int PBP, int ACT, int NCB>
+struct Keep {
+  static constexpr int kMore = ACT == ACT_SIN ? PBP : 0;
+  static constexpr int kBlocks = NCB + kMore;   // 1 KiB wave fragments per row block
+};
+
+// the first three derivatives of the activation at z_0 of point block pb
+template <int ACT, int NCB, int MODE, int NZ>
+__device__ __forceinline__ void derivs(const v4f (&z)[NZ], int pb, v4f& s, v4f& s1, v4f& s2, v4f& s3) {
+  if constexpr (ACT == ACT_SIN && MODE == M_PDE) {
+    s = z[pb];
+    s1 = z[NCB + pb];
+    s2 = -s;
+  } else {
+    act4<ACT, true>(z[pb], s, s1, s2);
+  }
+  s3 = act_third<ACT>(s, s1);
+}
+
+// z -> h in place; keep(block, fragment) takes what the backward needs
+template <int DIM, int NCB, int MODE, int ACT, typename F>
+__device__ __forceinline__ void activate_row(v4f (&a)[NCB], F keep) {
+  using M = ModeCfg<DIM, NCB, MODE>;
+  constexpr int NPB = M::NPB;
+#pragma unroll
+  for (int pb = 0; pb < NPB; ++pb) {
+    v4f s, s1, s2;
+    act4<ACT>(a[pb], s, s1, s2);
+    if constexpr (ACT == ACT_SIN && MODE == M_VALUE) keep(pb, a[pb]);
+    else keep(pb, s);
+    a[pb] = s;
+    if constexpr (MODE == M_PDE) {
+      if constexpr (ACT == ACT_SIN) keep(NCB + pb, s1);
+#pragma unroll
+      for (int jj = 0; jj <= DIM; ++jj) {
+        const int c1 = (1 + jj) * NPB + pb, c2 = (DIM + 2 + jj) * NPB + pb;
+        keep(c1, a[c1]);
+        if (jj < DIM) {
+          keep(c2, a[c2]);
+          a[c2] = s2 * a[c1] * a[c1] + s1 * a[c2];
+        }
+        a[c1] *= s1;
+      }
+    }
+  }
+}
+
+// Adjoint of activate_row: hb (dL/dh) -> dL/dz in place.
+//   zbar_jj = s1 hbar_jj
+//   zbar_j  = s1 hbar_j + 2 s2 z_j hbar_jj      (spatial j; time: s1 hbar_t)
+//   zbar_0  = s1 hbar_0 + s2 sum_j z_j hbar_j + sum_j (s3 z_j^2 + s2 z_jj) hbar_jj
+template <int DIM, int NCB, int MODE, int ACT, int NZ>
+__device__ __forceinline__ void adjoint_row(v4f (&hb)[NCB], const v4f (&z)[NZ]) {
+  using M = ModeCfg<DIM, NCB, MODE>;
+  constexpr int NPB = M::NPB;
+#pragma unroll
+  for (int pb = 0; pb < NPB; ++pb) {
+    v4f s, s1, s2, s3;
+    derivs<ACT, NCB, MODE>(z, pb, s, s1, s2, s3);
+    v4f z0 = s1 * hb[pb];
+    if constexpr (MODE == M_PDE) {
+#pragma unroll
+      for (int jj = 0; jj <= DIM; ++jj) {
+        const int c1 = (1 + jj) * NPB + pb, c2 = (DIM + 2 + jj) * NPB + pb;
+        const v4f h1 = hb[c1], z1 = z[c1];
+        z0 += s2 * z1 * h1;
+        hb[c1] = s1 * h1;
+        if (jj < DIM) {
+          const v4f h2 = hb[c2];
+          hb[c2] = s1 * h2;
+          hb[c1] += 2.f * s2 * z1 * h2;
+          z0 += (s3 * z1 * z1 + s2 * z[c2]) * h2;
+        }
+      }
+    }
+    hb[pb] = z0;
+  }
+}
+
+// h of the kept values, split, as the operand of a contraction over columns; a
+// pair of column blocks at a time
+template <int DIM, int NCB, int MODE, int ACT, int NZ>
+__device__ __forceinline__ void h_operand(const v4f (&z)[NZ], bool swap, v8h (&ha)[NCB / 2][3]) {
   using M = ModeCfg<DIM, NCB, MODE>;
   constexpr int NPB = M::NPB;
   v4f s1[NPB], s2[NPB];   // (value mode: unused)
   auto h_of = [&](int cb) -> v4f {
     const int c = cb / NPB, pb = cb - c * NPB;
     if (c == 0) {
-      v4f s;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float a0, a1, a2;
-        act_d2s<ACT, SV>(z[cb][i], a0, a1, a2);
-        s[i] = a0;
-        if constexpr (MODE == M_PDE) {
-          s1[pb][i] = a1;
-          s2[pb][i] = a2;
-        }
+      v4f s, a1, a2, a3;
+      derivs<ACT, NCB, MODE>(z, pb, s, a1, a2, a3);
+      if constexpr (MODE == M_PDE) {
+        s1[pb] = a1;
+        s2[pb] = a2;
       }
       return s;
     }
@@ -246,9 +325,9 @@ __device__ __forceinline__ void h_operand(const v4f (&z)[NCB], bool swap, v8h (&
     split4(h_of(2 * kc + 1), o);
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
-      const uint32_t u[4] = {swap ? o[p][0] : e[p][0], swap ? o[p][1] : e[p][1], swap ? e[p][0] : o[p][0], swap ? e[p][1] : o[p][1]};
       typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-      ha[kc][p] = __builtin_bit_cast(v8h, v4u{u[0], u[1], u[2], u[3]});
+      const v4u u = {swap ? o[p][0] : e[p][0], swap ? o[p][1] : e[p][1], swap ? e[p][0] : o[p][0], swap ? e[p][1] : o[p][1]};
+      ha[kc][p] = __builtin_bit_cast(v8h, u);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -331,22 +410,28 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
   constexpr int NCOL = 16 * NCB;
   using MP = ModeCfg<DIM, NCB, M_PDE>;
   using MV = ModeCfg<DIM, NCB, M_VALUE>;
-  constexpr bool SV = ACT == ACT_TANH;   // the stash keeps tanh(z0) in place of z0
+  constexpr int NZ = Keep<PBP, ACT, NCB>::kBlocks;
+  // one row block and tanh: layer H's values stay in registers, not in the stash
+  constexpr bool KEEP_H = R == 1 && ACT == ACT_TANH;
 
   const Shape& sh = args.sh;
   const int Wp = sh.Wp, NW = sh.NW, H = sh.H, KB = (NW + 1) >> 1;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int lane = tid & 63, g = lane >> 4, j = lane & 15;
-  const uint32_t lane16 = (uint32_t)lane * 16u;
+  // Byte offsets of the lane's memory accesses, on top of wave-uniform bases.
+  // fresh() hides their values from loop-invariant code motion, which would otherwise keep
+  // a 64-bit address per access in registers for the whole loop, and spill them.
+  uint32_t lane16 = (uint32_t)lane * 16u, j4 = (uint32_t)j * 4u;
+  auto fresh = [&] { asm volatile("" : "+v"(lane16), "+v"(j4)); };
   const StepSlots ss = step_slots<NCB>(lane);
   const bool swap = slot_half(g);
   const SplitStepLds L = split_step_lds(D, NW, NCB);
   float* ys = reinterpret_cast<float*>(lds + L.ys);
   float* xin = reinterpret_cast<float*>(lds + L.xin);
   char* mine = lds + rb0 * Stack<NCB>::kRow;   // the wave's row blocks in the stack
-  // stash: z of (layer, row block, column block), 1 KiB wave fragments
-  float* stash = args.stash + (size_t)blockIdx.x * args.stash_per_wg + (size_t)rb0 * NCB * 256;
-  const size_t stash_l = (size_t)NW * NCB * 256;
+  // stash: (layer, row block, block), 1 KiB wave fragments
+  float* stash = args.stash + (size_t)blockIdx.x * args.stash_per_wg + (size_t)rb0 * NZ * 256;
+  const size_t stash_l = (size_t)NW * NZ * 256;
   const float nu = args.nu;
   const bool prio = args.prio != 0;   // favour a wave in its matrix phases over one in its vector phases
 
@@ -410,41 +495,28 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
       }
       __syncthreads();
 
-      // ---- forward.  The stash keeps the pre-activations of layers 1..H-1 for
-      // the adjoint (z_H stays in registers); with tanh its value channel keeps tanh(z0), in which the
-      // derivatives of tanh are polynomials.
+      // ---- forward
+      fresh();
       v4f acc[R][NCB];
       const int nvb = pde ? MP::NPB : MV::NPB;   // value-channel column blocks
-      auto act = [&](int r) {
-        if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc[r]);
-        else act_forward<DIM, NCB, M_VALUE, ACT>(acc[r]);
-      };
-      // z_l in acc -> stash, then h_l in acc
+      // z_l in acc -> h_l, and what the backward needs of z_l into the stash
       auto activate = [&](int l) {
-        float* st = stash + (size_t)(l - 1) * stash_l;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb)
-            if (!SV || cb >= nvb) stg4u(st + (r * NCB + cb) * 256, lane16, acc[r][cb]);
-          act(r);
-          if (SV) {
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb)
-              if (cb < nvb) stg4u(st + (r * NCB + cb) * 256, lane16, acc[r][cb]);
-          }
+          float* st = stash + (size_t)(l - 1) * stash_l + (size_t)r * NZ * 256;
+          auto keep = [&](int b, v4f v) { stg4u(st + b * 256, lane16, v); };
+          if (pde) activate_row<DIM, NCB, M_PDE, ACT>(acc[r], keep);
+          else activate_row<DIM, NCB, M_VALUE, ACT>(acc[r], keep);
         }
       };
-      v4f zl[R][NCB];   // z_H
+      v4f zl[KEEP_H ? NZ : 1];   // of layer H
       auto activate_last = [&] {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) zl[r][cb] = acc[r][cb];
-          act(r);
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb)
-            if (SV && cb < nvb) zl[r][cb] = acc[r][cb];
+        if constexpr (KEEP_H) {
+          auto keep = [&](int b, v4f v) { zl[b] = v; };
+          if (pde) activate_row<DIM, NCB, M_PDE, ACT>(acc[0], keep);
+          else activate_row<DIM, NCB, M_VALUE, ACT>(acc[0], keep);
+        } else {
+          activate(H);
         }
       };
       const float* wf = fr + sh.f_hid3 + (size_t)rb0 * KB * 3 * kFragFloats;   // of W_2
@@ -452,7 +524,7 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
       float bias[R];
       auto load_bias = [&](int l) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) bias[r] = ldg(bp + (l - 1) * Wp + 16 * (rb0 + r) + j);
+        for (int r = 0; r < R; ++r) bias[r] = ldgu(bp + (l - 1) * Wp + 16 * (rb0 + r), j4);
       };
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -467,6 +539,7 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
         activate_last();
       }
       for (int l = 2; l <= H; ++l) {
+        fresh();
         put_rows<R, NCB>(mine, ss, acc);
         __syncthreads();
         if (prio) __builtin_amdgcn_s_setprio(1);
@@ -592,57 +665,58 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
       // The small gradients (dW_{H+1}, db_l, dW_1) are summed over the tile's
       // columns and added to the slab by the lanes g = 0.
       {
-        float* so = slab + sh.s_wo + 16 * rb0 + j;
-        v4f hb[R][NCB];
+        float* so = slab + sh.s_wo + 16 * rb0;
 #pragma unroll
-        for (int o = 0; o < D; ++o) {
-          float old[R], wo[R], s[R];
+        for (int r = 0; r < R; ++r) {
+          v4f hb[NCB];
 #pragma unroll
-          for (int r = 0; r < R; ++r) {
-            old[r] = (g == 0 && !first) ? ldg(so + o * Wp + 16 * r) : 0.f;
-            wo[r] = ldg(Wop + o * Wp + 16 * (rb0 + r) + j);
-            s[r] = 0.f;
-          }
-          float b = 0.f;
+          for (int o = 0; o < D; ++o) {
+            const float old = (g == 0 && !first) ? ldgu(so + o * Wp + 16 * r, j4) : 0.f;
+            const float wo = ldgu(Wop + o * Wp + 16 * (rb0 + r), j4);
+            float s = 0.f, b = 0.f;
 #pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) {
-            const v4f yv = *reinterpret_cast<const v4f*>(ys + o * NCOL + 16 * cb + 4 * g);
-            if (cb < nvb) b += (yv[0] + yv[1]) + (yv[2] + yv[3]);
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-              s[r] += (yv[0] * acc[r][cb][0] + yv[1] * acc[r][cb][1]) + (yv[2] * acc[r][cb][2] + yv[3] * acc[r][cb][3]);
-              hb[r][cb] = o == 0 ? wo[r] * yv : hb[r][cb] + wo[r] * yv;
+            for (int cb = 0; cb < NCB; ++cb) {
+              const v4f yv = *reinterpret_cast<const v4f*>(ys + o * NCOL + 16 * cb + 4 * g);
+              if (r == 0 && cb < nvb) b += (yv[0] + yv[1]) + (yv[2] + yv[3]);
+              s += (yv[0] * acc[r][cb][0] + yv[1] * acc[r][cb][1]) + (yv[2] * acc[r][cb][2] + yv[3] * acc[r][cb][3]);
+              hb[cb] = o == 0 ? wo * yv : hb[cb] + wo * yv;
+            }
+            if (R > 1) __builtin_amdgcn_sched_barrier(0);   // (ys would be read for all outputs at once)
+            s = group_sum(s);
+            if (g == 0) stgu(so + o * Wp + 16 * r, j4, old + s);
+            if (r == 0) {
+              b = group_sum(b);
+              if (tid == o) dbo += b;
+              asm volatile("" : "+v"(dbo));   // now: its terms would be kept until the tile's end
             }
           }
 #pragma unroll
-          for (int r = 0; r < R; ++r) {
-            s[r] = group_sum(s[r]);
-            if (g == 0) stg(so + o * Wp + 16 * r, old[r] + s[r]);
-          }
-          b = group_sum(b);
-          if (tid == o) dbo += b;
-          asm volatile("" : "+v"(dbo));   // now: its terms would be kept until the tile's end
+          for (int cb = 0; cb < NCB; ++cb) acc[r][cb] = hb[cb];
         }
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) acc[r][cb] = hb[r][cb];
       }
+      auto load_z = [&](int l, int r, v4f (&z)[NZ]) {   // of layer l, row block r
+        const float* st = stash + (size_t)(l - 1) * stash_l + (size_t)r * NZ * 256;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) z[cb] = ldg4u(st + cb * 256, lane16);
+#pragma unroll
+        for (int cb = NCB; cb < NZ; ++cb)
+          if (pde) z[cb] = ldg4u(st + cb * 256, lane16);
+      };
       // adjoint of layer l, row block r: acc[r] = hbar_l -> zbar_l; db_l and, at l = 1, dW_1
-      auto adjoint = [&](int l, int r, const v4f (&z)[NCB]) {
-        float* sb = slab + sh.s_b + (size_t)(l - 1) * Wp + 16 * (rb0 + r) + j;
-        const float old = (g == 0 && !first) ? ldg(sb) : 0.f;
-        if (pde) act_adjoint<DIM, NCB, M_PDE, ACT, SV>(acc[r], z);
-        else act_adjoint<DIM, NCB, M_VALUE, ACT, SV>(acc[r], z);
+      auto adjoint = [&](int l, int r, const v4f (&z)[NZ]) {
+        float* sb = slab + sh.s_b + (size_t)(l - 1) * Wp + 16 * (rb0 + r);
+        const float old = (g == 0 && !first) ? ldgu(sb, j4) : 0.f;
+        if (pde) adjoint_row<DIM, NCB, M_PDE, ACT>(acc[r], z);
+        else adjoint_row<DIM, NCB, M_VALUE, ACT>(acc[r], z);
         float s = 0.f;
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
           if (cb < nvb) s += (acc[r][cb][0] + acc[r][cb][1]) + (acc[r][cb][2] + acc[r][cb][3]);
         s = group_sum(s);
-        if (g == 0) stg(sb, old + s);
+        if (g == 0) stgu(sb, j4, old + s);
         if (l > 1) return;
         // dW1[n][q] += sum_pts zbar0 xi_q + zbar_q (first-derivative channel q)
-        float* s1 = slab + sh.s_w1 + (size_t)(16 * (rb0 + r) + j) * D;
+        float* s1 = slab + sh.s_w1 + (size_t)(16 * (rb0 + r)) * D;
         float v[D];
 #pragma unroll
         for (int q = 0; q < D; ++q) v[q] = 0.f;
@@ -668,23 +742,27 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
 #pragma unroll
         for (int q = 0; q < D; ++q) {
           const float t = group_sum(v[q]);
-          if (g == 0) stg(s1 + q, (first ? 0.f : ldg(s1 + q)) + t);
+          if (g == 0) stgu(s1 + q, j4 * D, (first ? 0.f : ldgu(s1 + q, j4 * D)) + t);
         }
       };
+      if constexpr (KEEP_H) {
+        adjoint(H, 0, zl);
+      } else {
 #pragma unroll
-      for (int r = 0; r < R; ++r) adjoint(H, r, zl[r]);
+        for (int r = 0; r < R; ++r) {
+          v4f z[NZ];
+          load_z(H, r, z);
+          adjoint(H, r, z);
+        }
+      }
 
       // ---- hidden layer adjoints
       const float* wt = wf + sh.hid3_layer / 2;   // of W_2^T
       for (int l = H; l >= 2; --l) {
+        fresh();
         // loads ahead of the barriers: z_{l-1} (of the first row block) and weights
-        auto load_z = [&](int r, v4f (&z)[NCB]) {
-          const float* st = stash + (size_t)(l - 2) * stash_l + (size_t)r * NCB * 256;
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) z[cb] = ldg4u(st + cb * 256, lane16);
-        };
-        v4f z[NCB];
-        load_z(0, z);
+        v4f z[NZ];
+        load_z(l - 1, 0, z);
         __syncthreads();   // every reader of the stack (layer l + 1; the output layer) is done
         put_rows<R, NCB>(mine, ss, acc);
         __syncthreads();
@@ -692,9 +770,9 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           v8h ha[NCB / 2][3];
-          if (pde) h_operand<DIM, NCB, M_PDE, ACT, SV>(z, swap, ha);
-          else h_operand<DIM, NCB, M_VALUE, ACT, SV>(z, swap, ha);
-          if (R > 1) load_z(r + 1 < R ? r + 1 : 0, z);   // for the next row block, at last again the first
+          if (pde) h_operand<DIM, NCB, M_PDE, ACT>(z, swap, ha);
+          else h_operand<DIM, NCB, M_VALUE, ACT>(z, swap, ha);
+          if (R > 1) load_z(l - 1, r + 1 < R ? r + 1 : 0, z);   // for the next row block, at last again the first
           if (prio) __builtin_amdgcn_s_setprio(1);
           gemm_columns_t<NCB>(ha, lds, NW, ss, lane16,
                               slab + sh.s_hid + (size_t)(l - 2) * Wp * Wp + (size_t)(rb0 + r) * NW * 256, first);
@@ -705,7 +783,7 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
         __builtin_amdgcn_s_setprio(0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          if (r > 0) load_z(r, z);
+          if (r > 0) load_z(l - 1, r, z);
           adjoint(l - 1, r, z);
         }
       }

@@ -27,26 +27,25 @@ __device__ __forceinline__ void act_store_bwd(float* buf, int S2, const v4f (&z)
   using M = ModeCfg<DIM, NCB, MODE>;
   constexpr int NPB = M::NPB;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float* row = buf + (16 * w + 4 * g + i) * S2 + j;
+  for (int pb = 0; pb < NPB; ++pb) {
+    v4f s, s1, s2;
+    act4<ACT>(z[pb], s, s1, s2);
 #pragma unroll
-    for (int pb = 0; pb < NPB; ++pb) {
-      float s, s1, s2;
-      act_d2<ACT>(z[pb][i], s, s1, s2);
-      row[16 * pb] = s;
+    for (int i = 0; i < 4; ++i) {
+      float* row = buf + (16 * w + 4 * g + i) * S2 + j;
+      row[16 * pb] = s[i];
       if constexpr (MODE == M_PDE) {
 #pragma unroll
-        for (int jj = 0; jj <= DIM; ++jj) row[16 * ((1 + jj) * NPB + pb)] = s1 * z[(1 + jj) * NPB + pb][i];
+        for (int jj = 0; jj <= DIM; ++jj) row[16 * ((1 + jj) * NPB + pb)] = s1[i] * z[(1 + jj) * NPB + pb][i];
 #pragma unroll
         for (int jj = 0; jj < DIM; ++jj) {
           const float z1 = z[(1 + jj) * NPB + pb][i];
-          row[16 * ((DIM + 2 + jj) * NPB + pb)] = s2 * z1 * z1 + s1 * z[(DIM + 2 + jj) * NPB + pb][i];
+          row[16 * ((DIM + 2 + jj) * NPB + pb)] = s2[i] * z1 * z1 + s1[i] * z[(DIM + 2 + jj) * NPB + pb][i];
         }
       }
     }
   }
 }
-
 
 // ---------------------------------------------------------------------------
 // GEMMs on FP32 MFMA 16x16x4
@@ -358,23 +357,23 @@ __device__ __forceinline__ void act_store_bwd_cols(float* buf, int S2, const v4f
     if (cb >= CB0 && cb < CB0 + NCBH) row[16 * (cb - CB0)] = v;
   };
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float* row = buf + (16 * rb + 4 * g + i) * S2 + j;
+  for (int pb = 0; pb < NPB; ++pb) {
+    if constexpr (MODE != M_PDE) {
+      if (pb < CB0 || pb >= CB0 + NCBH) continue;
+    }
+    v4f s, s1, s2;
+    act4<ACT>(z[pb], s, s1, s2);
 #pragma unroll
-    for (int pb = 0; pb < NPB; ++pb) {
-      if constexpr (MODE != M_PDE) {
-        if (pb < CB0 || pb >= CB0 + NCBH) continue;
-      }
-      float s, s1, s2;
-      act_d2<ACT>(z[pb][i], s, s1, s2);
-      put(row, pb, s);
+    for (int i = 0; i < 4; ++i) {
+      float* row = buf + (16 * rb + 4 * g + i) * S2 + j;
+      put(row, pb, s[i]);
       if constexpr (MODE == M_PDE) {
 #pragma unroll
-        for (int jj = 0; jj <= DIM; ++jj) put(row, (1 + jj) * NPB + pb, s1 * z[(1 + jj) * NPB + pb][i]);
+        for (int jj = 0; jj <= DIM; ++jj) put(row, (1 + jj) * NPB + pb, s1[i] * z[(1 + jj) * NPB + pb][i]);
 #pragma unroll
         for (int jj = 0; jj < DIM; ++jj) {
           const float z1 = z[(1 + jj) * NPB + pb][i];
-          put(row, (DIM + 2 + jj) * NPB + pb, s2 * z1 * z1 + s1 * z[(DIM + 2 + jj) * NPB + pb][i]);
+          put(row, (DIM + 2 + jj) * NPB + pb, s2[i] * z1 * z1 + s1[i] * z[(DIM + 2 + jj) * NPB + pb][i]);
         }
       }
     }
