@@ -78,9 +78,8 @@ Shape make_shape(int dim, int W, int H) {
   sh.Wp = (W + 15) / 16 * 16;
   sh.NW = sh.Wp / 16;
   sh.s3 = split_fits(dim, sh.NW) ? 1 : 0;
-  sh.t3 = sh.s3;
   sh.NWV = std::min(sh.NW, kMaxWaves);
-  sh.Kq = sh.t3 ? sh.Wp / 4 : (W + 3) / 4;   // t3: neurons at their own positions
+  sh.Kq = sh.s3 ? sh.Wp / 4 : (W + 3) / 4;   // triples: neurons at their own positions
   sh.P = (int32_t)nparams(dim, W, H);
   const int64_t Wp = sh.Wp, D = sh.D;
   // packed offsets
@@ -94,16 +93,16 @@ Shape make_shape(int dim, int W, int H) {
   }
   // fragment buffer
   o = 0;
-  sh.f_hid = o; o += sh.t3 ? 0 : 2 * (int64_t)(H - 1) * Wp * Wp;
+  sh.f_hid = o; o += sh.s3 ? 0 : 2 * (int64_t)(H - 1) * Wp * Wp;
   sh.f_w1 = o;  o += Wp * D;
   sh.f_b = o;   o += (int64_t)H * Wp;
   sh.f_wo = o;  o += D * Wp;
   sh.f_bo = o;  o += 4;
   sh.f_hid3 = o = (o + 63) / 64 * 64;
-  sh.hid3_layer = (sh.t3 ? 2LL : 1LL) * sh.NW * ((sh.NW + 1) / 2) * 768;
+  sh.hid3_layer = 2LL * sh.NW * ((sh.NW + 1) / 2) * 768;
   o += sh.s3 ? (H - 1) * sh.hid3_layer : 0;
   sh.f_wo3 = o;
-  o += sh.t3 ? ((sh.NW + 1) / 2) * 768 : 0;
+  o += sh.s3 ? ((sh.NW + 1) / 2) * 768 : 0;
   sh.frag_floats = (o + 63) / 64 * 64;
   // slab
   o = 0;
@@ -384,10 +383,6 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
     max_lds = std::max(max_lds, optin);
   HIPCHECK(ddp::set_lds_limits(max_lds));
 
-  // two row blocks per wave: the column-split LDS plan when the plain one
-  // does not fit
-  if (!sh.t3 && sh.NW > sh.NWV && (int64_t)step_lds_floats(sh, 16) * 4 > max_lds) c->sh.split = 1;
-
   // tile shape: 32-point collocation tiles when they fit in LDS with at
   // least the occupancy of 16-point tiles, unless fixed by the caller
   c->threads = sh.NWV * 64;
@@ -496,7 +491,7 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   c->n_slabs = std::max(std::max(c->n_seg, c->ps_seg), 1);
   const int stash_wg = std::max(c->n_wg, 1);
   const int NCB = (2 * sh.dim + 2) * (c->tile_points / 16);
-  c->stash_per_wg = (int64_t)sh.NW * sh.H * (NCB + (sh.t3 && sh.act == 1 ? c->tile_points / 16 : 0)) * 256;   // sin and t3: cos(z_0) too
+  c->stash_per_wg = (int64_t)sh.NW * sh.H * (NCB + (sh.s3 && sh.act == 1 ? c->tile_points / 16 : 0)) * 256;   // sin, triples: cos(z_0) too
 
   // exchange capacity: every ghost point in a half tile, plus one partial tile per face
   int64_t xcap = 0;

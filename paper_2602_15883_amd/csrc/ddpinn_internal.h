@@ -56,10 +56,7 @@ struct Shape {
   int32_t P;                      // packed parameter count
   int32_t act;                    // activation: 0 tanh, 1 sin
   int32_t NWV;                    // waves per workgroup, min(NW, kMaxWaves)
-  int32_t s3;                     // queries and exchange on bf16 triples (ddpinn_split.h)
-  int32_t t3;                     // the training step on bf16 triples (implies s3)
-  int32_t split;                  // two row blocks per wave and the step's LDS plan does not
-                                  // fit: one forward activation stack, backward by column halves
+  int32_t s3;                     // the kernels on bf16 triples (ddpinn_split.h), else ddpinn_wide.hip
   int32_t Kq;                     // ceil(W/4): K-steps of the hidden-layer GEMMs (hidden neurons
                                   // are stored at permuted positions, see hid_pos)
   int32_t pad_;
@@ -72,9 +69,9 @@ struct Shape {
   int64_t f_bo;    // b_{H+1} [4]
   int64_t f_hid3;  // hidden layers as bf16 triples (ddpinn_split.h): layer l (2..H) at f_hid3 +
                    // (l-2)*hid3_layer: fragments [row block][K block][part][64 lanes][8 bf16] of
-                   // W_l, then (t3; hid3_layer/2 further) of its transpose
+                   // W_l, then (hid3_layer/2 further) of its transpose
   int64_t hid3_layer;
-  int64_t f_wo3;   // W_{H+1} as bf16 triples (t3): [K block][part][64 lanes][8 bf16], rows padded to 16
+  int64_t f_wo3;   // W_{H+1} as bf16 triples: [K block][part][64 lanes][8 bf16], rows padded to 16
   int64_t frag_floats;
   // gradient slab (per segment)
   int64_t s_hid;   // dW_l (l = 2..H) in accumulator order at s_hid + (l-2)*Wp*Wp
@@ -231,7 +228,7 @@ template <int DIM> const void* split_query_ptr(int mode, int act, int small, int
 template <int DIM> const void* split_exchange_ptr(int act, int NW);
 // Kernels on FP32 MFMA (ddpinn_wide.hip): the step above 128 neurons, queries of
 // 3D networks above 208
-const void* wide_step_ptr(int dim, int act, int split, int Wp);
+const void* wide_step_ptr(int act);
 const void* wide_query_ptr(int mode, int act, int small);
 const void* wide_exchange_ptr(int act);
 int wide_step_lds_floats(const Shape& sh);

@@ -24,7 +24,7 @@ namespace ddp {
 // threads: one per float ahead of f_hid3, then one per pair of bf16 triples
 __host__ __device__ inline int64_t prep_threads(const Shape& sh) {
   const int64_t KB = (sh.NW + 1) / 2;
-  return sh.f_hid3 + (sh.s3 ? (sh.t3 ? 2 : 1) * (sh.H - 1) * sh.NW * KB * 256 : 0) + (sh.t3 ? KB * 256 : 0);
+  return sh.f_hid3 + (sh.s3 ? (2 * (sh.H - 1) * sh.NW + 1) * KB * 256 : 0);
 }
 
 __global__ void prep_kernel(const PrepArgs a) {
@@ -43,8 +43,8 @@ __global__ void prep_kernel(const PrepArgs a) {
     int e = (int)(idx - sh.f_hid3);
     const int m = e / per;
     e -= m * per;
-    const bool out = m == (sh.t3 ? 2 : 1) * (H - 1);   // W_{H+1}: its D rows
-    const int l = out ? H + 1 : 2 + (sh.t3 ? m >> 1 : m), trans = sh.t3 && !out ? m & 1 : 0;
+    const bool out = m == 2 * (H - 1);   // W_{H+1}: its D rows
+    const int l = out ? H + 1 : 2 + (m >> 1), trans = out ? 0 : m & 1;
     const int e2 = e & 3, lane = (e >> 2) & 63, t = e >> 8, kb = t % KB, rb = t / KB;
     const int r = out ? ((lane & 15) < D ? lane & 15 : -1) : hid_neuron(sh, 16 * rb + (lane & 15));
     float x[2];
@@ -104,12 +104,12 @@ __global__ void prep_kernel(const PrepArgs a) {
 
 // row and column positions of element e of a layer's dW in the slab: tiles [row
 // block][column block][64 lanes][4], lane (g, j): row 4g + i, column j; the
-// kernels on triples (t3) keep the transpose so
+// kernels on triples keep the transpose so
 __device__ __forceinline__ void slab_tile_rc(const Shape& sh, int e, int& r, int& c) {
   const int lane = (e >> 2) & 63, t = e >> 8, w = t / sh.NW, nb = t - w * sh.NW;
   const int a = 16 * w + 4 * (lane >> 4) + (e & 3), b = 16 * nb + (lane & 15);
-  r = sh.t3 ? b : a;
-  c = sh.t3 ? a : b;
+  r = sh.s3 ? b : a;
+  c = sh.s3 ? a : b;
 }
 
 // packed parameter at a slab position (-1: padding or a loss sum)
@@ -580,7 +580,7 @@ static const void* split_exchange_any(int dim, int act, int NW) {
 }
 
 int step_lds_floats(const Shape& sh, int tile_points) {
-  if (sh.t3) return split_step_lds(sh.D, sh.NW, (2 * sh.dim + 2) * (tile_points / 16)).total / 4;
+  if (sh.s3) return split_step_lds(sh.D, sh.NW, (2 * sh.dim + 2) * (tile_points / 16)).total / 4;
   return wide_step_lds_floats(sh);
 }
 
@@ -590,8 +590,8 @@ int query_lds_floats(const Shape& sh, int small) {
 }
 
 const void* step_kernel_ptr(const Shape& sh, int tile_points) {
-  if (sh.t3) return split_step_any(sh.dim, tile_points, sh.act, sh.NW);
-  return tile_points == 16 ? wide_step_ptr(sh.dim, sh.act, sh.split, sh.Wp) : nullptr;
+  if (sh.s3) return split_step_any(sh.dim, tile_points, sh.act, sh.NW);
+  return tile_points == 16 ? wide_step_ptr(sh.act) : nullptr;
 }
 const void* prep_kernel_ptr() { return (const void*)prep_kernel; }
 const void* reduce_kernel_ptr() { return (const void*)reduce_kernel; }
@@ -713,10 +713,7 @@ hipError_t set_lds_limits(int bytes) {
         }
         allow(split_exchange_any(dim, act, nw));
       }
-      for (int wp : {144, 160, 208}) {   // the constant strides and the argument
-        allow(wide_step_ptr(dim, act, 0, wp));
-        allow(wide_step_ptr(dim, act, 1, wp));
-      }
+      allow(wide_step_ptr(act));
       for (int small = 0; small <= 1; ++small) {
         allow(wide_query_ptr(M_VALUE, act, small));
         allow(wide_query_ptr(M_PDE, act, small));

@@ -1,7 +1,7 @@
-// Kernels on FP32 MFMA 16x16x4 for the widths whose activation stacks of bf16
-// triples (ddpinn_split.h) do not pay or do not fit: the training step above 128
-// neurons (a wave owns two row blocks, w and w + 8, and runs them one after the
-// other) and the query and exchange of 3D networks above 208 neurons.
+// Kernels on FP32 MFMA 16x16x4 for the networks whose activation stack of bf16
+// triples (ddpinn_split.h) does not fit in the LDS: 3D above 208 neurons.  A wave
+// owns two row blocks, w and w + 8, and runs them one after the other; the step
+// holds its backward operands for half of a tile's columns at a time.
 //
 //   Each hidden layer is Z = W_l H (all channels at once, N = 16*NCB columns).
 //   The A operand (weights) streams from a fragment-ordered copy in global
@@ -17,34 +17,6 @@ namespace ddp {
 
 __device__ __forceinline__ v4f mfma4(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-
-// h = act(z) of a stashed pre-activation stack, written straight into the
-// neuron-major LDS layout [neuron][column] (stride S2) used by the dW GEMM.
-template <int DIM, int NCB, int MODE, int ACT>
-__device__ __forceinline__ void act_store_bwd(float* buf, int S2, const v4f (&z)[NCB], int w, int g, int j) {
-  using M = ModeCfg<DIM, NCB, MODE>;
-  constexpr int NPB = M::NPB;
-#pragma unroll
-  for (int pb = 0; pb < NPB; ++pb) {
-    v4f s, s1, s2;
-    act4<ACT>(z[pb], s, s1, s2);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float* row = buf + (16 * w + 4 * g + i) * S2 + j;
-      row[16 * pb] = s[i];
-      if constexpr (MODE == M_PDE) {
-#pragma unroll
-        for (int jj = 0; jj <= DIM; ++jj) row[16 * ((1 + jj) * NPB + pb)] = s1[i] * z[(1 + jj) * NPB + pb][i];
-#pragma unroll
-        for (int jj = 0; jj < DIM; ++jj) {
-          const float z1 = z[(1 + jj) * NPB + pb][i];
-          row[16 * ((DIM + 2 + jj) * NPB + pb)] = s2[i] * z1 * z1 + s1[i] * z[(DIM + 2 + jj) * NPB + pb][i];
-        }
-      }
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -115,25 +87,6 @@ __device__ __forceinline__ void gemm_rows(const float* __restrict__ afrag, const
   if (KT) mfma_tail<NCB>(a0, bb, S, s4, KT, acc);
 }
 
-// acc = the rows of one row block over the K chunks [c0, c1) of the KC
-// chunks of a lane group's segment (the last chunk holds KT steps if KT > 0):
-// one part of a GEMM whose K range is split between waves
-template <int NCB>
-__device__ __forceinline__ void gemm_rows_part(const float* __restrict__ afrag, const float* bufB, int S, int KC,
-                                               int KT, int c0, int c1, int g, int j, int lane, v4f (&acc)[NCB]) {
-  const float* bb = bufB + j * S + g * (4 * KC);
-  const uint32_t lo = (uint32_t)lane * 16u;
-#pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) acc[cb] = zero4();
-  v4f a = ldg4u(afrag + c0 * 256, lo);
-  for (int c = c0; c < c1; ++c) {
-    const v4f an = (c + 1 < c1) ? ldg4u(afrag + (c + 1) * 256, lo) : a;
-    if (c == KC - 1 && KT) mfma_tail<NCB>(a, bb, S, c, KT, acc);
-    else mfma_step<NCB>(a, bb, S, c, acc);
-    a = an;
-  }
-}
-
 // dw[t] += sum_col Zbar[16w + m][col] * Hprev[16(nb0+t) + n][col], t < NNB
 //   Zbar from bufG ([col][neuron], stride S); Hprev from bufHb ([neuron][col], stride S2)
 //   Column of step (s4, q) in lane group g: 16*s4 + 4*g + q.  The four groups
@@ -194,65 +147,22 @@ __device__ __forceinline__ void output_layer(const float* bufH, int S, int Wp,
   }
 }
 
-
 // ---------------------------------------------------------------------------
 // LDS plan of the step kernel (floats)
 // ---------------------------------------------------------------------------
 struct StepLds {
   int S, S2, NCOL;
-  int bufH, bufG, ys, yb, xin, acc1, dbacc, red, sched, part, nparts, total;
+  int bufH, bufG, ys, yb, xin, acc1, dbacc, red, sched, total;
 };
 
-// Row blocks beyond the eight waves.  With exactly two of them (Wp = 160, the
-// paper's 6x150 network) the plan with two stacks per tile splits their
-// GEMMs' K range in halves between four waves, one per SIMD, so no wave
-// carries more than 1.5 row blocks (instead of 2, 2, 1, ...) and every SIMD
-// 2.5 (instead of 3, 3, 2, 2).  The parts meet in four LDS tiles; only where
-// those fit in the 160 KB of LDS as well.
-constexpr int kLdsBytes = 160 * 1024;
-__host__ __device__ inline int step_ksplit_parts(int Wp, int split, int floats_before, int NCB) {
-  const int nw = Wp / 16, ne = nw - (nw < 8 ? nw : 8);
-  const bool want = !split && ne == 2;
-  return (want && (floats_before + 4 * NCB * 256) * 4 <= kLdsBytes) ? 4 : 0;
-}
-
-// Row stride of the [col][neuron] stacks: Wp + 4, a compile-time constant for the
-// paper's cylinder widths (Wp = 160 and 208) and a kernel argument for the
-// others.  A constant stride makes every LDS address of a tile one lane base
-// plus an immediate offset.  With each stride the rows that one operand read
-// or store touches fall in distinct banks.
-
-__host__ __device__ inline StepLds step_lds(int D, int Wp, int H, int NCB, int S = 0) {
+// The forward keeps one activation stack [NCOL][S] at bufG (row stride S = Wp + 4:
+// the rows that one operand read or store touches fall in distinct banks); the
+// backward holds Zbar [NCOL/2][S] at bufG and H_{l-1} [Wp][NCOL/2 + 4] at bufH for
+// one half of the tile's columns at a time.
+__host__ __device__ inline StepLds step_lds(int D, int Wp, int H, int NCB) {
   StepLds L;
   L.NCOL = 16 * NCB;
-  L.S = S ? S : Wp + 4;
-  L.S2 = L.NCOL + 4;
-  const int hsz = (L.NCOL * L.S > Wp * L.S2) ? L.NCOL * L.S : Wp * L.S2;
-  int o = 0;
-  L.bufH = o; o += (hsz + 3) & ~3;
-  L.bufG = o; o += (L.NCOL * L.S + 3) & ~3;
-  L.ys = o;   o += (D * L.NCOL + 3) & ~3;
-  L.yb = o;   o += (D * L.NCOL + 3) & ~3;
-  L.xin = o;  o += (L.NCOL * D + 3) & ~3;
-  L.acc1 = o; o += (Wp * D + 3) & ~3;
-  L.dbacc = o; o += (H * Wp + 3) & ~3;
-  L.red = o;  o += 64;
-  L.sched = o; o += 4;   // the item range taken by the workgroup
-  L.part = o;
-  L.nparts = step_ksplit_parts(Wp, 0, o, NCB);
-  o += L.nparts * NCB * 256;
-  L.total = o;
-  return L;
-}
-
-// LDS plan of the column-split variant (two row blocks per wave, when the
-// plan above does not fit): the forward keeps one activation stack [NCOL][S]
-// at bufG; the backward holds Zbar [NCOL/2][S] at bufG and H_{l-1}
-// [Wp][NCOL/2 + 4] at bufH for one half of the tile's columns at a time.
-__host__ __device__ inline StepLds step_lds_split(int D, int Wp, int H, int NCB, int S = 0) {
-  StepLds L;
-  L.NCOL = 16 * NCB;
-  L.S = S ? S : Wp + 4;
+  L.S = Wp + 4;
   L.S2 = L.NCOL / 2 + 4;
   const int zh = ((L.NCOL / 2) * L.S + 3) & ~3;
   const int bwd = zh + Wp * L.S2;
@@ -268,9 +178,6 @@ __host__ __device__ inline StepLds step_lds_split(int D, int Wp, int H, int NCB,
   L.dbacc = o; o += (H * Wp + 3) & ~3;
   L.red = o;  o += 64;
   L.sched = o; o += 4;
-  L.part = o;
-  L.nparts = step_ksplit_parts(Wp, 1, o, NCB);
-  o += L.nparts * NCB * 256;
   L.total = o;
   return L;
 }
@@ -339,12 +246,6 @@ __device__ __forceinline__ void adjoint_rows(v4f (&acc)[NCB], const v4f (&zs)[NC
       if (j == 0) acc1[r * D + q] += s;
     }
   }
-}
-
-template <int SPLIT>
-__host__ __device__ inline StepLds step_plan(int D, int Wp, int H, int NCB, int S = 0) {
-  if constexpr (SPLIT) return step_lds_split(D, Wp, H, NCB, S);
-  else return step_lds(D, Wp, H, NCB, S);
 }
 
 // h = act(z) of a stashed pre-activation stack, only the column blocks
@@ -436,8 +337,7 @@ __device__ __forceinline__ void dw_tiles(float* sw, bool first, const float* buf
 // ---------------------------------------------------------------------------
 // Fused step kernel: persistent over this workgroup's item range.
 // ---------------------------------------------------------------------------
-// SS: the row stride of the [col][neuron] stacks (step_row_stride)
-template <int DIM, int ACT, int SPLIT, int SS>
+template <int DIM, int ACT>
 __global__ __launch_bounds__(512) void step_kernel(const StepArgs args) {
   constexpr int D = DIM + 1;
   constexpr int CF = 2 * DIM + 2;
@@ -456,7 +356,7 @@ __global__ __launch_bounds__(512) void step_kernel(const StepArgs args) {
   // lets every per-wave address (weights, stash, slab) be a scalar base plus
   // the lane offset instead of a 64-bit vector address per use
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, j = lane & 15;
-  const StepLds L = step_plan<SPLIT>(D, Wp, H, NCB, SS);
+  const StepLds L = step_lds(D, Wp, H, NCB);
   float* bufH = lds + L.bufH;
   float* bufG = lds + L.bufG;
   float* ys = lds + L.ys;
@@ -465,13 +365,7 @@ __global__ __launch_bounds__(512) void step_kernel(const StepArgs args) {
   float* acc1 = lds + L.acc1;
   float* dbacc = lds + L.dbacc;
   float* red = lds + L.red;
-  float* part = lds + L.part;
-  const int S = SS ? SS : L.S, S2 = L.S2;
-  // two row blocks beyond the eight waves (the plan with two stacks per tile): their GEMMs are
-  // split over K between waves w and w + 2 (w < 2, the blocks' owners), and
-  // summed by the owner from four LDS tiles
-  const bool ks = !SPLIT && L.nparts == 4;
-  const int KCh = ((sh.Kq + 3) >> 2);   // K chunks of a lane group's segment
+  const int S = L.S, S2 = L.S2;
   // dW tiles of this wave (two-row-block kernels): the layer's NW*NW tiles in
   // contiguous runs whose lengths even out each wave's work between two
   // barriers.  A row block of Hbar costs NW dW tiles in multiply-adds (both
@@ -479,11 +373,10 @@ __global__ __launch_bounds__(512) void step_kernel(const StepArgs args) {
   // around the GEMMs (recomputing h, the adjoint) adds about a quarter of
   // that; so a wave with fewer Hbar row blocks takes more dW tiles: wave v's
   // share is (9/4 NW^2 - 5/4 NWV * NW * rows(v)) / NWV, rows(v) its row
-  // blocks (1.5 for waves 0..3 with the K-split above).  cut(v) is the sum
-  // of the shares of waves < v, with rows counted in halves.
+  // blocks.  cut(v) is the sum of the shares of waves < v, with rows counted in halves.
   auto dw_cut = [&](int v) {
     const int ne = NW - NWV;
-    const int hb = ks ? 3 * (v < 4 ? v : 4) + 2 * (v > 4 ? v - 4 : 0) : 2 * v + 2 * (v < ne ? v : ne);
+    const int hb = 2 * v + 2 * (v < ne ? v : ne);
     return (18 * NW * NW * v - 5 * NW * NWV * hb) / (8 * NWV);
   };
   const int dw_t0 = dw_cut(w), dw_t1 = dw_cut(w + 1);
@@ -569,121 +462,51 @@ __global__ __launch_bounds__(512) void step_kernel(const StepArgs args) {
     __syncthreads();
 
     v4f acc[NCB];
-    // ---- forward: input layer.  Activations ping-pong between the two LDS
-    // stacks, so one barrier per layer suffices and each wave's activation
-    // work overlaps the other waves' GEMMs.
-    float* hin = bufH;
-    float* hout = bufG;
-    if constexpr (SPLIT) {
-      // two row blocks per wave, one activation stack: every wave's GEMMs read
-      // the stack before any wave overwrites it; the first block's
-      // pre-activations wait in the stash meanwhile
-      hin = bufG;
-      for (int r = 0; r < nrb; ++r) {
-        const int rb = w + r * NWV;
-        float* st = stash_w + r * stash_rb;
-        if (pde) input_layer<DIM, NCB, M_PDE>(acc, W1p, bp, xin, rb, g, j);
-        else input_layer<DIM, NCB, M_VALUE>(acc, W1p, bp, xin, rb, g, j);
+    // ---- forward: input layer.
+    // two row blocks per wave, one activation stack: every wave's GEMMs read
+    // the stack before any wave overwrites it; the first block's
+    // pre-activations wait in the stash meanwhile
+    float* hin = bufG;
+    for (int r = 0; r < nrb; ++r) {
+      const int rb = w + r * NWV;
+      float* st = stash_w + r * stash_rb;
+      if (pde) input_layer<DIM, NCB, M_PDE>(acc, W1p, bp, xin, rb, g, j);
+      else input_layer<DIM, NCB, M_VALUE>(acc, W1p, bp, xin, rb, g, j);
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) stg4u(st + (0 * NCB + cb) * 256, lo16, acc[cb]);
-        if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc);
-        else act_forward<DIM, NCB, M_VALUE, ACT>(acc);
-        store_fwd<NCB>(hin, S, acc, rb, g, j);
-      }
-      __syncthreads();
-      for (int l = 2; l <= H; ++l) {
-        const float* Wl = fr + sh.f_hid + (size_t)(l - 2) * 2 * Wp * Wp;
-        for (int r = 0; r < nrb; ++r) {
-          const int rb = w + r * NWV;
-          float* st = stash_w + r * stash_rb;
-          const float* Wf = Wl + (size_t)rb * 16 * Wp;
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) acc[cb] = zero4();
-          if (prio && w >= (NWV >> 1)) __builtin_amdgcn_s_setprio(2);
-          gemm_rows<NCB>(Wf, hin, S, K4, g, j, lane, acc, KT);
-          __builtin_amdgcn_s_setprio(0);
-          if (pde) add_bias<NCB, MP::NPB>(acc, bp + (l - 1) * Wp, rb, g);
-          else add_bias<NCB, MV::NPB>(acc, bp + (l - 1) * Wp, rb, g);
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) stg4u(st + ((l - 1) * NCB + cb) * 256, lo16, acc[cb]);
-        }
-        __syncthreads();
-        for (int r = nrb - 1; r >= 0; --r) {
-          if (r != nrb - 1) {
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) acc[cb] = ldg4u(stash_w + r * stash_rb + ((l - 1) * NCB + cb) * 256, lo16);
-          }
-          if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc);
-          else act_forward<DIM, NCB, M_VALUE, ACT>(acc);
-          store_fwd<NCB>(hin, S, acc, w + r * NWV, g, j);
-        }
-        __syncthreads();
-      }
-    } else {
-      // two row blocks per wave: the same steps per row block
-      for (int r = 0; r < nrb; ++r) {
-        const int rb = w + r * NWV;
-        float* st = stash_w + r * stash_rb;
-        if (pde) input_layer<DIM, NCB, M_PDE>(acc, W1p, bp, xin, rb, g, j);
-        else input_layer<DIM, NCB, M_VALUE>(acc, W1p, bp, xin, rb, g, j);
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) stg4u(st + (0 * NCB + cb) * 256, lo16, acc[cb]);
-        if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc);
-        else act_forward<DIM, NCB, M_VALUE, ACT>(acc);
-        store_fwd<NCB>(hin, S, acc, rb, g, j);
-      }
-      __syncthreads();
-      for (int l = 2; l <= H; ++l) {
-        const float* Wl = fr + sh.f_hid + (size_t)(l - 2) * 2 * Wp * Wp;
-        for (int r = 0; r < (ks ? 1 : nrb); ++r) {
-          const int rb = w + r * NWV;
-          float* st = stash_w + r * stash_rb;
-          const float* Wf = Wl + (size_t)rb * 16 * Wp;
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) acc[cb] = zero4();
-          if (prio && w >= (NWV >> 1)) __builtin_amdgcn_s_setprio(2);
-          gemm_rows<NCB>(Wf, hin, S, K4, g, j, lane, acc, KT);
-          __builtin_amdgcn_s_setprio(0);
-          if (pde) add_bias<NCB, MP::NPB>(acc, bp + (l - 1) * Wp, rb, g);
-          else add_bias<NCB, MV::NPB>(acc, bp + (l - 1) * Wp, rb, g);
-#pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) stg4u(st + ((l - 1) * NCB + cb) * 256, lo16, acc[cb]);
-          if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc);
-          else act_forward<DIM, NCB, M_VALUE, ACT>(acc);
-          store_fwd<NCB>(hout, S, acc, rb, g, j);
-        }
-        if (ks) {
-          // the two extra row blocks: half of the K range each for waves
-          // 0..3 (block NWV + (w & 1), half w >> 1), summed by the owner
-          if (w < 4) {
-            const int e = NWV + (w & 1), c0 = (w >> 1) ? KCh / 2 : 0, c1 = (w >> 1) ? KCh : KCh / 2;
-            gemm_rows_part<NCB>(Wl + (size_t)e * 16 * Wp, hin, S, KCh, KT, c0, c1, g, j, lane, acc);
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) *reinterpret_cast<v4f*>(part + (w * NCB + cb) * 256 + lane * 4) = acc[cb];
-          }
-          __syncthreads();
-          if (nrb == 2) {
-            const int e = w + NWV;
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb)
-              acc[cb] = *reinterpret_cast<const v4f*>(part + (w * NCB + cb) * 256 + lane * 4) +
-                        *reinterpret_cast<const v4f*>(part + ((w + 2) * NCB + cb) * 256 + lane * 4);
-            if (pde) add_bias<NCB, MP::NPB>(acc, bp + (l - 1) * Wp, e, g);
-            else add_bias<NCB, MV::NPB>(acc, bp + (l - 1) * Wp, e, g);
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) stg4u(stash_w + stash_rb + ((l - 1) * NCB + cb) * 256, lo16, acc[cb]);
-            if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc);
-            else act_forward<DIM, NCB, M_VALUE, ACT>(acc);
-            store_fwd<NCB>(hout, S, acc, e, g, j);
-          }
-        }
-        __syncthreads();
-        float* t = hin;
-        hin = hout;
-        hout = t;
-      }
+      for (int cb = 0; cb < NCB; ++cb) stg4u(st + (0 * NCB + cb) * 256, lo16, acc[cb]);
+      if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc);
+      else act_forward<DIM, NCB, M_VALUE, ACT>(acc);
+      store_fwd<NCB>(hin, S, acc, rb, g, j);
     }
-
+    __syncthreads();
+    for (int l = 2; l <= H; ++l) {
+      const float* Wl = fr + sh.f_hid + (size_t)(l - 2) * 2 * Wp * Wp;
+      for (int r = 0; r < nrb; ++r) {
+        const int rb = w + r * NWV;
+        float* st = stash_w + r * stash_rb;
+        const float* Wf = Wl + (size_t)rb * 16 * Wp;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) acc[cb] = zero4();
+        if (prio && w >= (NWV >> 1)) __builtin_amdgcn_s_setprio(2);
+        gemm_rows<NCB>(Wf, hin, S, K4, g, j, lane, acc, KT);
+        __builtin_amdgcn_s_setprio(0);
+        if (pde) add_bias<NCB, MP::NPB>(acc, bp + (l - 1) * Wp, rb, g);
+        else add_bias<NCB, MV::NPB>(acc, bp + (l - 1) * Wp, rb, g);
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) stg4u(st + ((l - 1) * NCB + cb) * 256, lo16, acc[cb]);
+      }
+      __syncthreads();
+      for (int r = nrb - 1; r >= 0; --r) {
+        if (r != nrb - 1) {
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) acc[cb] = ldg4u(stash_w + r * stash_rb + ((l - 1) * NCB + cb) * 256, lo16);
+        }
+        if (pde) act_forward<DIM, NCB, M_PDE, ACT>(acc);
+        else act_forward<DIM, NCB, M_VALUE, ACT>(acc);
+        store_fwd<NCB>(hin, S, acc, w + r * NWV, g, j);
+      }
+      __syncthreads();
+    }
     // ---- output layer (h_H is in hin)
     if (pde) output_layer<DIM, NCB, M_PDE>(hin, S, Wp, Wop, bop, ys, tid, nthr);
     else output_layer<DIM, NCB, M_VALUE>(hin, S, Wp, Wop, bop, ys, tid, nthr);
@@ -818,170 +641,80 @@ __global__ __launch_bounds__(512) void step_kernel(const StepArgs args) {
         out_adjoint_rows<D, NCB>(acc, Wop, yb, Wp, rb, g, j);
         if (pde) adjoint_rows<DIM, NCB, M_PDE, ACT>(acc, zs, dbacc, acc1, xin, Wp, rb, H, g, j);
         else adjoint_rows<DIM, NCB, M_VALUE, ACT>(acc, zs, dbacc, acc1, xin, Wp, rb, H, g, j);
-        if (H > 1 && (SPLIT || r + 1 < nrb)) {
+        if (H > 1) {
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb) stg4u(st + ((H - 1) * NCB + cb) * 256, lo16, acc[cb]);
         }
       }
-      if constexpr (SPLIT) {
-        // The tile's columns in two halves (Zbar and H_{l-1} of one half fit
-        // in LDS at a time; the GEMMs are separable over columns).  Every
-        // block's zbar and hbar wait in its own stash slot between barriers.
-        constexpr int NCBH = NCB / 2;
-        for (int l = H; l >= 2; --l) {
-          float* sw = args.slabs + (size_t)item.slab * sh.slab_floats + sh.s_hid + (size_t)(l - 2) * Wp * Wp;
-          const size_t zl = (size_t)(l - 1) * NCB * 256, zp = (size_t)(l - 2) * NCB * 256;
+      // The tile's columns in two halves (Zbar and H_{l-1} of one half fit
+      // in LDS at a time; the GEMMs are separable over columns).  Every
+      // block's zbar and hbar wait in its own stash slot between barriers.
+      constexpr int NCBH = NCB / 2;
+      for (int l = H; l >= 2; --l) {
+        float* sw = args.slabs + (size_t)item.slab * sh.slab_floats + sh.s_hid + (size_t)(l - 2) * Wp * Wp;
+        const size_t zl = (size_t)(l - 1) * NCB * 256, zp = (size_t)(l - 2) * NCB * 256;
 #pragma unroll
-          for (int hh = 0; hh < 2; ++hh) {
-            // this half's Zbar_l of both row blocks: the wave's own stash
-            // slots, so they are requested before the barrier (which only
-            // guards the LDS stacks)
-            v4f t[NCBH];
-            v4f tz[2][NCBH];
+        for (int hh = 0; hh < 2; ++hh) {
+          // this half's Zbar_l of both row blocks: the wave's own stash
+          // slots, so they are requested before the barrier (which only
+          // guards the LDS stacks)
+          v4f t[NCBH];
+          v4f tz[2][NCBH];
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-              if (r < nrb) {
+          for (int r = 0; r < 2; ++r) {
+            if (r < nrb) {
 #pragma unroll
-                for (int c = 0; c < NCBH; ++c)
-                  tz[r][c] = ldg4u(stash_w + r * stash_rb + zl + ((size_t)hh * NCBH + c) * 256, lo16);
-              }
+              for (int c = 0; c < NCBH; ++c)
+                tz[r][c] = ldg4u(stash_w + r * stash_rb + zl + ((size_t)hh * NCBH + c) * 256, lo16);
             }
-            __syncthreads();
-#pragma unroll
-            for (int r = 0; r < 2; ++r)
-              if (r < nrb) store_fwd<NCBH>(bufG, S, tz[r], w + r * NWV, g, j);
-            // H_{l-1} of this half, recomputed from z_{l-1}
-            for (int r = 0; r < nrb; ++r) {
-#pragma unroll
-              for (int cb = 0; cb < NCB; ++cb) zs[cb] = ldg4u(stash_w + r * stash_rb + zp + cb * 256, lo16);
-              if (hh == 0) {
-                if (pde) act_store_bwd_cols<DIM, NCB, M_PDE, ACT, 0, NCBH>(bufH, S2, zs, w + r * NWV, g, j);
-                else act_store_bwd_cols<DIM, NCB, M_VALUE, ACT, 0, NCBH>(bufH, S2, zs, w + r * NWV, g, j);
-              } else {
-                if (pde) act_store_bwd_cols<DIM, NCB, M_PDE, ACT, NCBH, NCBH>(bufH, S2, zs, w + r * NWV, g, j);
-                else act_store_bwd_cols<DIM, NCB, M_VALUE, ACT, NCBH, NCBH>(bufH, S2, zs, w + r * NWV, g, j);
-              }
-            }
-            __syncthreads();
-            if (raise) __builtin_amdgcn_s_setprio(2);
-            dw_tiles<NCBH>(sw, (item.flags & ITEM_FIRST) && hh == 0, bufG, S, bufH, S2, NW, dw_t0, dw_t1, g, j,
-                           lo16);
-            // Hbar_{l-1} of this half into the stash slot of Zbar_l (consumed)
-            const float* WTl = fr + sh.f_hid + (size_t)(l - 2) * 2 * Wp * Wp + (size_t)Wp * Wp;
-            for (int r = 0; r < nrb; ++r) {
-              const int rb = w + r * NWV;
-#pragma unroll
-              for (int c = 0; c < NCBH; ++c) t[c] = zero4();
-              const float* WT = WTl + (size_t)rb * 16 * Wp;
-              gemm_rows<NCBH>(WT, bufG, S, K4, g, j, lane, t, KT);
-              float* st = stash_w + r * stash_rb + zl + (size_t)hh * NCBH * 256;
-#pragma unroll
-              for (int c = 0; c < NCBH; ++c) stg4u(st + c * 256, lo16, t[c]);
-            }
-            __builtin_amdgcn_s_setprio(0);
-          }
-          // adjoint of layer l-1 per block; zbar_{l-1} replaces z_{l-1}
-          for (int r = 0; r < nrb; ++r) {
-            const int rb = w + r * NWV;
-            float* st = stash_w + r * stash_rb;
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) acc[cb] = ldg4u(st + zl + cb * 256, lo16);
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) zs[cb] = ldg4u(st + zp + cb * 256, lo16);
-            if (pde) adjoint_rows<DIM, NCB, M_PDE, ACT>(acc, zs, dbacc, acc1, xin, Wp, rb, l - 1, g, j);
-            else adjoint_rows<DIM, NCB, M_VALUE, ACT>(acc, zs, dbacc, acc1, xin, Wp, rb, l - 1, g, j);
-            if (l > 2) {
-#pragma unroll
-              for (int cb = 0; cb < NCB; ++cb) stg4u(st + zp + cb * 256, lo16, acc[cb]);
-            }
-          }
-        }
-      } else {
-        // every block's Zbar_l and H_{l-1} fit in LDS together
-        for (int l = H; l >= 2; --l) {
-          // the first block's Zbar_l and z_{l-1} come from the wave's own
-          // stash slots: in 2D they are requested before the barrier (which
-          // only guards the LDS stacks), so their latency overlaps the wait
-          // (the 3D kernels have no registers to hold them across it)
-          constexpr bool early = DIM == 2;
-          v4f zb[NCB];
-          if (early) {
-            if (nrb == 2) {
-#pragma unroll
-              for (int cb = 0; cb < NCB; ++cb) zb[cb] = ldg4u(stash_w + ((l - 1) * NCB + cb) * 256, lo16);
-            }
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) zs[cb] = ldg4u(stash_w + ((l - 2) * NCB + cb) * 256, lo16);
           }
           __syncthreads();
-          // Zbar_l into LDS: the last block's from registers, the first's from the stash
-          store_fwd<NCB>(bufG, S, acc, w + (nrb - 1) * NWV, g, j);
-          if (nrb == 2) {
-            if (!early) {
 #pragma unroll
-              for (int cb = 0; cb < NCB; ++cb) zb[cb] = ldg4u(stash_w + ((l - 1) * NCB + cb) * 256, lo16);
-            }
-            store_fwd<NCB>(bufG, S, zb, w, g, j);
-          }
-          // h_{l-1} recomputed from z_{l-1}
+          for (int r = 0; r < 2; ++r)
+            if (r < nrb) store_fwd<NCBH>(bufG, S, tz[r], w + r * NWV, g, j);
+          // H_{l-1} of this half, recomputed from z_{l-1}
           for (int r = 0; r < nrb; ++r) {
-            if (r > 0 || !early) {
 #pragma unroll
-              for (int cb = 0; cb < NCB; ++cb)
-                zs[cb] = ldg4u(stash_w + r * stash_rb + ((l - 2) * NCB + cb) * 256, lo16);
+            for (int cb = 0; cb < NCB; ++cb) zs[cb] = ldg4u(stash_w + r * stash_rb + zp + cb * 256, lo16);
+            if (hh == 0) {
+              if (pde) act_store_bwd_cols<DIM, NCB, M_PDE, ACT, 0, NCBH>(bufH, S2, zs, w + r * NWV, g, j);
+              else act_store_bwd_cols<DIM, NCB, M_VALUE, ACT, 0, NCBH>(bufH, S2, zs, w + r * NWV, g, j);
+            } else {
+              if (pde) act_store_bwd_cols<DIM, NCB, M_PDE, ACT, NCBH, NCBH>(bufH, S2, zs, w + r * NWV, g, j);
+              else act_store_bwd_cols<DIM, NCB, M_VALUE, ACT, NCBH, NCBH>(bufH, S2, zs, w + r * NWV, g, j);
             }
-            if (pde) act_store_bwd<DIM, NCB, M_PDE, ACT>(bufH, S2, zs, w + r * NWV, g, j);
-            else act_store_bwd<DIM, NCB, M_VALUE, ACT>(bufH, S2, zs, w + r * NWV, g, j);
           }
           __syncthreads();
-          float* sw = args.slabs + (size_t)item.slab * sh.slab_floats + sh.s_hid + (size_t)(l - 2) * Wp * Wp;
           if (raise) __builtin_amdgcn_s_setprio(2);
-          dw_tiles<NCB>(sw, item.flags & ITEM_FIRST, bufG, S, bufH, S2, NW, dw_t0, dw_t1, g, j, lo16);
-          __builtin_amdgcn_s_setprio(0);
-          // Hbar_{l-1} = W_l^T Zbar_l, then the adjoint of layer l-1, per block
+          dw_tiles<NCBH>(sw, (item.flags & ITEM_FIRST) && hh == 0, bufG, S, bufH, S2, NW, dw_t0, dw_t1, g, j,
+                         lo16);
+          // Hbar_{l-1} of this half into the stash slot of Zbar_l (consumed)
           const float* WTl = fr + sh.f_hid + (size_t)(l - 2) * 2 * Wp * Wp + (size_t)Wp * Wp;
-          if (ks && w < 4) {
-            // the extra row blocks' Hbar over half of the K range (as in the forward)
-            const int e = NWV + (w & 1), c0 = (w >> 1) ? KCh / 2 : 0, c1 = (w >> 1) ? KCh : KCh / 2;
-            if (raise) __builtin_amdgcn_s_setprio(2);
-            gemm_rows_part<NCB>(WTl + (size_t)e * 16 * Wp, bufG, S, KCh, KT, c0, c1, g, j, lane, acc);
-            __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) *reinterpret_cast<v4f*>(part + (w * NCB + cb) * 256 + lane * 4) = acc[cb];
-          }
-          for (int r = 0; r < (ks ? 1 : nrb); ++r) {
+          for (int r = 0; r < nrb; ++r) {
             const int rb = w + r * NWV;
-            float* st = stash_w + r * stash_rb;
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) zs[cb] = ldg4u(st + ((l - 2) * NCB + cb) * 256, lo16);
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) acc[cb] = zero4();
+            for (int c = 0; c < NCBH; ++c) t[c] = zero4();
             const float* WT = WTl + (size_t)rb * 16 * Wp;
-            if (raise) __builtin_amdgcn_s_setprio(2);
-            gemm_rows<NCB>(WT, bufG, S, K4, g, j, lane, acc, KT);
-            __builtin_amdgcn_s_setprio(0);
-            if (pde) adjoint_rows<DIM, NCB, M_PDE, ACT>(acc, zs, dbacc, acc1, xin, Wp, rb, l - 1, g, j);
-            else adjoint_rows<DIM, NCB, M_VALUE, ACT>(acc, zs, dbacc, acc1, xin, Wp, rb, l - 1, g, j);
-            if (l > 2 && r + 1 < nrb) {
+            gemm_rows<NCBH>(WT, bufG, S, K4, g, j, lane, t, KT);
+            float* st = stash_w + r * stash_rb + zl + (size_t)hh * NCBH * 256;
 #pragma unroll
-              for (int cb = 0; cb < NCB; ++cb) stg4u(st + ((l - 2) * NCB + cb) * 256, lo16, acc[cb]);
-            }
+            for (int c = 0; c < NCBH; ++c) stg4u(st + c * 256, lo16, t[c]);
           }
-          if (ks) {
-            if (nrb == 2) {
+          __builtin_amdgcn_s_setprio(0);
+        }
+        // adjoint of layer l-1 per block; zbar_{l-1} replaces z_{l-1}
+        for (int r = 0; r < nrb; ++r) {
+          const int rb = w + r * NWV;
+          float* st = stash_w + r * stash_rb;
 #pragma unroll
-              for (int cb = 0; cb < NCB; ++cb) zs[cb] = ldg4u(stash_w + stash_rb + ((l - 2) * NCB + cb) * 256, lo16);
-            }
-            __syncthreads();   // the halves are in LDS
-            if (nrb == 2) {
-              const int e = w + NWV;
+          for (int cb = 0; cb < NCB; ++cb) acc[cb] = ldg4u(st + zl + cb * 256, lo16);
 #pragma unroll
-              for (int cb = 0; cb < NCB; ++cb)
-                acc[cb] = *reinterpret_cast<const v4f*>(part + (w * NCB + cb) * 256 + lane * 4) +
-                          *reinterpret_cast<const v4f*>(part + ((w + 2) * NCB + cb) * 256 + lane * 4);
-              if (pde) adjoint_rows<DIM, NCB, M_PDE, ACT>(acc, zs, dbacc, acc1, xin, Wp, e, l - 1, g, j);
-              else adjoint_rows<DIM, NCB, M_VALUE, ACT>(acc, zs, dbacc, acc1, xin, Wp, e, l - 1, g, j);
-            }
+          for (int cb = 0; cb < NCB; ++cb) zs[cb] = ldg4u(st + zp + cb * 256, lo16);
+          if (pde) adjoint_rows<DIM, NCB, M_PDE, ACT>(acc, zs, dbacc, acc1, xin, Wp, rb, l - 1, g, j);
+          else adjoint_rows<DIM, NCB, M_VALUE, ACT>(acc, zs, dbacc, acc1, xin, Wp, rb, l - 1, g, j);
+          if (l > 2) {
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) stg4u(st + zp + cb * 256, lo16, acc[cb]);
           }
         }
       }
@@ -1219,27 +952,14 @@ __global__ __launch_bounds__(512) void exchange_kernel(const ExchangeArgs a) {
 // ---------------------------------------------------------------------------
 int wide_step_lds_floats(const Shape& sh) {
   const int NCB = 2 * sh.dim + 2;
-  return sh.split ? step_lds_split(sh.D, sh.Wp, sh.H, NCB).total : step_lds(sh.D, sh.Wp, sh.H, NCB).total;
+  return step_lds(sh.D, sh.Wp, sh.H, NCB).total;
 }
 int wide_query_lds_floats(const Shape& sh, int small) {
   return query_lds(sh.D, sh.Wp, small ? sh.dim + 1 : 2 * sh.dim + 2).total;
 }
 
-// step: the column-split LDS plan or not; constant row strides for the
-// paper's cylinder widths
-template <int DIM, int SPLIT, int SS>
-static const void* step_act(int act) {
-  return act == ACT_SIN ? (const void*)step_kernel<DIM, ACT_SIN, SPLIT, SS> : (const void*)step_kernel<DIM, ACT_TANH, SPLIT, SS>;
-}
-const void* wide_step_ptr(int dim, int act, int split, int Wp) {
-  if (dim == 2) {
-    if (Wp == 160 && !split) return step_act<2, 0, 164>(act);
-    if (Wp == 208 && split) return step_act<2, 1, 212>(act);
-    return split ? step_act<2, 1, 0>(act) : step_act<2, 0, 0>(act);
-  }
-  if (Wp == 160 && split) return step_act<3, 1, 164>(act);
-  if (Wp == 208 && split) return step_act<3, 1, 212>(act);
-  return split ? step_act<3, 1, 0>(act) : step_act<3, 0, 0>(act);
+const void* wide_step_ptr(int act) {
+  return act == ACT_SIN ? (const void*)step_kernel<3, ACT_SIN> : (const void*)step_kernel<3, ACT_TANH>;
 }
 const void* wide_query_ptr(int mode, int act, int small) {
   if (mode == M_VALUE) {

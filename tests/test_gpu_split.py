@@ -1,5 +1,5 @@
-"""Contractions on bf16 triples: the step (up to 128 neurons), the queries and the
-exchange (up to 256 in 2D, 208 in 3D) against the FP64 oracle at the edges of
+"""Contractions on bf16 triples: the step, the queries and the exchange (up to 256
+neurons in 2D, 208 in 3D) against the FP64 oracle at the edges of
 their tiles: one and two row blocks, an even and an odd number of them (the last K block
 holds 16 neurons), the last and the first width of a range, ragged point tiles, both activations."""
 import numpy as np
@@ -13,7 +13,7 @@ torch = pytest.importorskip("torch")
 CASES = [(2, 1, 2, "tanh", 1), (2, 16, 3, "sin", 16), (3, 17, 3, "tanh", 17), (2, 32, 2, "sin", 33),
          (3, 33, 4, "sin", 40), (2, 48, 3, "tanh", 97), (3, 80, 2, "tanh", 15), (2, 112, 3, "tanh", 100),
          (3, 112, 3, "sin", 50), (2, 127, 2, "sin", 64), (3, 128, 3, "tanh", 65), (2, 128, 16, "tanh", 31)]
-QUERY_ONLY = [(2, 129, 2, "tanh", 100), (2, 256, 3, "sin", 97), (3, 144, 2, "tanh", 129), (3, 208, 3, "sin", 130)]
+WIDE = [(2, 129, 2, "tanh", 100), (2, 256, 3, "sin", 97), (3, 144, 2, "tanh", 129), (3, 208, 3, "sin", 130)]
 
 
 def test_triples_hold_every_fp32():
@@ -35,7 +35,7 @@ def test_triples_hold_every_fp32():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dim,W,H,act,npde", CASES + QUERY_ONLY)
+@pytest.mark.parametrize("dim,W,H,act,npde", CASES + WIDE)
 def test_split_kernels_against_oracle(orc, dim, W, H, act, npde):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -4,6 +4,7 @@ exact values over the whole float range."""
 from fractions import Fraction as F
 
 import numpy as np
+import pytest
 
 f32, f64 = np.float32, np.float64
 PIECES = [0xa2f9836, 0xe4e4415, 0x29fc275, 0x7d1f534, 0xddc0db6, 0x295993c, 0x439041f, 0xe5163ab]
@@ -94,3 +95,31 @@ def test_large_arguments():
     red = np.array([float(v) for v in red])
     assert ulps(s, np.sin(red)).max() < 1.5
     assert ulps(c, np.cos(red)).max() < 1.5
+
+
+@pytest.mark.gpu
+def test_kernels_follow_the_scheme_over_the_float_range():
+    """One hidden layer of two neurons that pass x and y on: the query returns
+    sin of the coordinates themselves."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2602_15883_amd as P
+    import workloads as wl
+    print("sin over the float range", flush=True)
+    pb = wl.tiny(dim=2, width=2, depth=1, n_pde=16, n_obs=4, n_gh=0, n_anc=1, seed=1)
+    pb.activation = "sin"
+    pb.subs[0].theta[:] = np.array([1, 0, 0, 0, 1, 0, 0, 0, 1, 0, 0, 1, 0, 0, 0, 0, 0], f32)
+    rng = np.random.default_rng(6)
+    x = np.zeros((2000, 3), f32)
+    x[:, 0] = rng.uniform(-100, 100, 2000)
+    x[:, 1] = 10.0 ** rng.uniform(-6, 38, 2000)
+    pi = pi_fraction()
+    red = np.array([float(F(float(v)) - 2 * pi * round(F(float(v)) / (2 * pi))) for v in x[:, 1]])
+    ctx = P.context_from_problem(pb, device="cuda")
+    try:
+        got = ctx.query(torch.from_numpy(x).cuda(), sub=0, what="value").cpu().numpy()
+    finally:
+        ctx.close()
+    assert ulps(got[:, 0], np.sin(x[:, 0].astype(f64))).max() < 1.5
+    assert ulps(got[:, 1], np.sin(red)).max() < 1.5
