@@ -88,23 +88,14 @@ __device__ __forceinline__ void put_rows(char* st, const StepSlots& ss, const v4
     for (int cb = 0; cb < NCB; ++cb) put_cb<NCB>(st + r * Stack<NCB>::kRow, ss, cb, a[r][cb]);
 }
 
-// operand of a contraction over neurons: column blocks 2 kc, 2 kc + 1 of the K
-// block whose row blocks start at st
-template <int NCB>
-__device__ __forceinline__ void neuron_operand(const char* st, const StepSlots& ss, int kc, v8h (&a)[2][3]) {
-#pragma unroll
-  for (int o = 0; o < 2; ++o)
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      const v4s lo = lds_read_tr(st + ss.tr[o][0] + unit_at<NCB>(kc, p)), hi = lds_read_tr(st + ss.tr[o][1] + unit_at<NCB>(kc, p));
-      a[o][p] = __builtin_bit_cast(v8h, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    }
-}
-
 // acc[r][cb] = (weights of the wave's row blocks) x (stack), transposed tile.  f: the weight
 // fragments of the first K block; the next block's are requested before the
-// products of the current one, and so are the stack operands of the next two column
-// blocks (12 R matrix instructions of 16 cycles ahead).
+// products of the current one, into the other of two sets (copies between them would
+// take issue slots from the products).
+// One LDS read is issued behind each matrix instruction: a burst of the twelve of a
+// pair of column blocks, which all waves issue at the same time, holds up the products behind it.
+// 192 products per wave, two waves per SIMD (6,220 cycles of the matrix unit): bursts 8,170
+// cycles, two reads every two products 7,500, one read behind each 7,020.
 template <int R, int NCB>
 __device__ __forceinline__ void gemm_neurons_t(const float* wf, const char* st, int NW, const StepSlots& ss,
                                                uint32_t lane16, Frags<R>& f, v4f (&acc)[R][NCB]) {
@@ -114,34 +105,60 @@ __device__ __forceinline__ void gemm_neurons_t(const float* wf, const char* st, 
   for (int r = 0; r < R; ++r)
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) acc[r][cb] = zero4();
-  v8h a[2][3], an[2][3];
-  if (KF > 0) neuron_operand<NCB>(st, ss, 0, an);
-  for (int kb = 0; kb < KF; ++kb, st += 2 * Stack<NCB>::kRow) {
-    v4f w[R][3];
+  const char* at[2][2];
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+  for (int o = 0; o < 2; ++o)
 #pragma unroll
-      for (int p = 0; p < 3; ++p) w[r][p] = f.a[r][p];
-    load_frags<R>(wf, KB, kb + 1 < KB ? kb + 1 : kb, lane16, f);   // (the last one again at the end)
+    for (int h = 0; h < 2; ++h) at[o][h] = st + ss.tr[o][h];
+  auto join = [](v4s lo, v4s hi) { return __builtin_bit_cast(v8h, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)); };
+  v8h a[2][2][3];
+  if (KF > 0) {
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) a[0][o][p] = join(lds_read_tr(at[o][0] + unit_at<NCB>(0, p)), lds_read_tr(at[o][1] + unit_at<NCB>(0, p)));
+  }
+  Frags<R> f2;
+  auto block = [&](Frags<R>& cur, Frags<R>& nxt, int kb, auto par) {
+    constexpr int P = NC & 1 ? decltype(par)::value : 0;
+    uint32_t lo = lane16;
+    asm volatile("" : "+v"(lo));   // (scalar bases)
+    load_frags<R>(wf, KB, kb + 1 < KB ? kb + 1 : kb, lo, nxt);   // (the last one again at the end)
 #pragma unroll
     for (int kc = 0; kc < NC; ++kc) {
-#pragma unroll
-      for (int o = 0; o < 2; ++o)
-#pragma unroll
-        for (int p = 0; p < 3; ++p) a[o][p] = an[o][p];
-      if (kc + 1 < NC) neuron_operand<NCB>(st, ss, kc + 1, an);
-      else neuron_operand<NCB>(kb + 1 < KF ? st + 2 * Stack<NCB>::kRow : st, ss, 0, an);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
+      if (kc + 1 == NC) {
+        // the next K block; from the last one back to the first
+        const int step = kb + 1 < KF ? 2 * Stack<NCB>::kRow : -(KF - 1) * 2 * Stack<NCB>::kRow;
 #pragma unroll
         for (int o = 0; o < 2; ++o)
 #pragma unroll
+          for (int h = 0; h < 2; ++h) at[o][h] += step;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        v4s lo, hi;
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+#pragma unroll
           for (int r = 0; r < R; ++r)
-            acc[r][2 * kc + o] = mfma32(a[o][kPartB[q]], __builtin_bit_cast(v8h, w[r][kPartA[q]]), acc[r][2 * kc + o]);
+            acc[r][2 * kc + o] = mfma32(a[(kc + P) & 1][o][kPartB[q]], __builtin_bit_cast(v8h, cur.a[r][kPartA[q]]), acc[r][2 * kc + o]);
+          (o ? hi : lo) = lds_read_tr(at[q & 1][o] + unit_at<NCB>(kc + 1 < NC ? kc + 1 : 0, kPartB[q >> 1]));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        a[(kc + 1 + P) & 1][q & 1][kPartB[q >> 1]] = join(lo, hi);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
+  };
+  int kb = 0;
+  for (; kb + 2 <= KF; kb += 2) {
+    block(f, f2, kb, std::integral_constant<int, 0>{});
+    block(f2, f, kb + 1, std::integral_constant<int, 1>{});
+  }
+  if (kb < KF) {
+    block(f, f2, kb, std::integral_constant<int, 0>{});
+    f = f2;
   }
   if (NW & 1) {   // a last K block of 16 neurons
 #pragma unroll
@@ -150,7 +167,7 @@ __device__ __forceinline__ void gemm_neurons_t(const float* wf, const char* st, 
 #pragma unroll
       for (int o = 0; o < 2; ++o)
 #pragma unroll
-        for (int p = 0; p < 3; ++p) a4[o][p] = lds_read_tr(st + ss.tr1[o] + unit_at<NCB>(kc, p));
+        for (int p = 0; p < 3; ++p) a4[o][p] = lds_read_tr(st + KF * 2 * Stack<NCB>::kRow + ss.tr1[o] + unit_at<NCB>(kc, p));
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int q = 0; q < 6; ++q) {
@@ -335,40 +352,70 @@ __device__ __forceinline__ void h_operand(const v4f (&z)[NZ], bool swap, v8h (&h
 
 // dW of one row block n of H (ha) against two row blocks m of Zbar at a time, added to the slab (sw:
 // tiles [NW][64 lanes][4] of row block n; lane (g, j): neuron 4g + i of n, neuron
-// j of m).  The old slab values are requested before the products they are added to.
+// j of m).  The old slab values are requested before the products they are added to; one LDS
+// read behind every two products (192 of them, two waves per SIMD: 8,120 cycles with
+// the reads of a column pair in a burst, 7,610 so).
 template <int NCB>
 __device__ __forceinline__ void gemm_columns_t(const v8h (&ha)[NCB / 2][3], const char* st, int NW, const StepSlots& ss,
                                                uint32_t lane16, float* sw, bool first) {
+  constexpr int NC = NCB / 2;
   const char* base = st + ss.slot;
-  auto add = [&](int mb, auto nt) {
-    constexpr int NT = decltype(nt)::value;
-    v4f old[NT], dw[NT];
+  v8h b[2][2][3];
+  auto read = [&](const char* row, int kc, int t, int p) {
+    return *reinterpret_cast<const v8h*>(row + t * Stack<NCB>::kRow + unit_at<NCB>(kc, p));
+  };
 #pragma unroll
-    for (int t = 0; t < NT; ++t) old[t] = first ? zero4() : ldg4u(sw + (size_t)(mb + t) * 256, lane16);
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int kc = 0; kc < NCB / 2; ++kc) {
-      v8h b[NT][3];
+    for (int p = 0; p < 3; ++p) b[0][t][p] = read(NW > 1 ? base : base - t * Stack<NCB>::kRow, 0, t, p);
+  auto pair = [&](int mb, auto par) {
+    constexpr int P = NC & 1 ? decltype(par)::value : 0;
+    uint32_t lo = lane16;
+    asm volatile("" : "+v"(lo));   // (scalar bases)
+    v4f old[2], dw[2];
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+    for (int t = 0; t < 2; ++t) old[t] = first ? zero4() : ldg4u(sw + (size_t)(mb + t) * 256, lo);
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
-          b[t][p] = *reinterpret_cast<const v8h*>(base + t * Stack<NCB>::kRow + unit_at<NCB>(kc, p));
+    for (int kc = 0; kc < NC; ++kc) {
+      // the next pair; past the last one the last two row blocks (an odd last one is done from them)
+      const char* nx = kc + 1 < NC ? base : base + (mb + 4 <= NW ? 2 : NW - 2 - mb) * Stack<NCB>::kRow;
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int q = 0; q < 6; ++q) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
-          dw[t] = mfma32(ha[kc][kPartA[q]], b[t][kPartB[q]], (kc == 0 && q == 0) ? zero4() : dw[t]);
+        for (int t = 0; t < 2; ++t)
+          dw[t] = mfma32(ha[kc][kPartA[q]], b[(kc + P) & 1][t][kPartB[q]], (kc == 0 && q == 0) ? zero4() : dw[t]);
+        b[(kc + 1 + P) & 1][q & 1][kPartB[q >> 1]] = read(nx, kc + 1 < NC ? kc + 1 : 0, q & 1, kPartB[q >> 1]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
-    for (int t = 0; t < NT; ++t) stg4u(sw + (size_t)(mb + t) * 256, lane16, old[t] + dw[t]);
-    base += NT * Stack<NCB>::kRow;
+    for (int t = 0; t < 2; ++t) stg4u(sw + (size_t)(mb + t) * 256, lo, old[t] + dw[t]);
+    base += (mb + 4 <= NW ? 2 : NW - 2 - mb) * Stack<NCB>::kRow;
   };
   int mb = 0;
-  for (; mb + 2 <= NW; mb += 2) add(mb, std::integral_constant<int, 2>{});
-  if (mb < NW) add(mb, std::integral_constant<int, 1>{});
+  for (; mb + 4 <= NW; mb += 4) {
+    pair(mb, std::integral_constant<int, 0>{});
+    pair(mb + 2, std::integral_constant<int, 1>{});
+  }
+  if (mb + 2 <= NW) {
+    pair(mb, std::integral_constant<int, 0>{});
+    mb += 2;
+  }
+  if (mb < NW) {   // an odd last row block
+    const char* row = st + ss.slot + mb * Stack<NCB>::kRow;
+    const v4f old = first ? zero4() : ldg4u(sw + (size_t)mb * 256, lane16);
+    v4f dw = zero4();
+#pragma unroll
+    for (int kc = 0; kc < NC; ++kc) {
+      v8h c[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) c[p] = read(row, kc, 0, p);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) dw = mfma32(ha[kc][kPartA[q]], c[kPartB[q]], dw);
+    }
+    stg4u(sw + (size_t)mb * 256, lane16, old + dw);
+  }
 }
 
 // input layer: z0 = W1 xi + b1 and the seeded channels, transposed tile
