@@ -6,7 +6,7 @@ namespace ddp {
 
 // forward of one staged tile (points in xin) through all layers; outputs in ys.
 // One LDS stack: every wave's products read it before any wave overwrites it.
-template <int DIM, int NCB, int MODE, int ACT, int R, bool DB>
+template <int DIM, int NCB, int MODE, int ACT, int R>
 __device__ __forceinline__ void split_forward(const Shape& sh, const float* fr, char* lds, const SplitQueryLds& L,
                                               int rb0, int w, int lane, int tid, int nthr) {
   using M = ModeCfg<DIM, NCB, MODE>;
@@ -30,7 +30,7 @@ __device__ __forceinline__ void split_forward(const Shape& sh, const float* fr, 
     for (int r = 0; r < R; ++r) bias[r] = ldg4(fr + sh.f_b + (l - 1) * Wp + 16 * (rb0 + r) + 4 * g);
     stack_store<R, NCB>(lds, rb0, NW, ls, acc);
     __syncthreads();
-    gemm_neurons<R, NCB, DB>(wf, lds, NW, ls, lane16, f, acc);
+    gemm_neurons<R, NCB>(wf, lds, NW, ls, lane16, f, acc);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
 #pragma unroll
@@ -97,12 +97,12 @@ __device__ __forceinline__ void split_forward_any(const Shape& sh, const float* 
   if constexpr (WIDE) {
     const int rb0 = split_rb0(w, sh.NW, sh.NWV);
     if (split_rb0(w + 1, sh.NW, sh.NWV) - rb0 == 2)
-      split_forward<DIM, NCB, MODE, ACT, 2, true>(sh, fr, lds, L, rb0, w, lane, tid, nthr);
-    else split_forward<DIM, NCB, MODE, ACT, 1, true>(sh, fr, lds, L, rb0, w, lane, tid, nthr);
+      split_forward<DIM, NCB, MODE, ACT, 2>(sh, fr, lds, L, rb0, w, lane, tid, nthr);
+    else split_forward<DIM, NCB, MODE, ACT, 1>(sh, fr, lds, L, rb0, w, lane, tid, nthr);
   } else if constexpr (NCB <= 3) {
     split_forward_small<DIM, NCB, MODE, ACT>(sh, fr, lds, L, w, lane, tid, nthr);
   } else {
-    split_forward<DIM, NCB, MODE, ACT, 1, false>(sh, fr, lds, L, w, w, lane, tid, nthr);
+    split_forward<DIM, NCB, MODE, ACT, 1>(sh, fr, lds, L, w, w, lane, tid, nthr);
   }
 }
 

@@ -42,6 +42,8 @@
 // 263 bytes/clock for the 16-byte reads and 248 for the transposing ones, against 138
 // for pairs of 8-byte reads from a layout of 512-byte units.
 #pragma once
+#include <type_traits>
+
 #include "ddpinn_device.h"
 
 namespace ddp {
@@ -223,10 +225,12 @@ __device__ __forceinline__ void products16(const v4f (&a)[R][3], const char* sp,
 
 // acc[r][cb] = rows of the wave's row blocks of (weights x stack), K = all NW
 // row blocks of the stack.  f: the weight fragments of the first K block; the next
-// block's are requested before the products of the current one.  DB (where
-// registers allow): so are the stack operands of the next CG column
-// blocks (6 CG R matrix instructions of 16 cycles ahead).
-template <int R, int NCB, bool DB>
+// block's are requested before the products of the current one, and so are the
+// stack operands of the next CG column blocks, one LDS read at a time between the products (a
+// burst of them, which all waves issue at the same time, holds up the products
+// behind it); nothing is copied between the two sets.  Residuals of 30,000 3D points,
+// 8x128: 300 us with bursts, 289 so.
+template <int R, int NCB>
 __device__ __forceinline__ void gemm_neurons(const float* wf, const char* st, int NW, const LaneSlots& ls,
                                              uint32_t lane16, Frags<R>& f, v4f (&acc)[R][NCB]) {
   constexpr int CG = NCB % 2 == 0 ? 2 : 1;   // column blocks in flight
@@ -238,30 +242,44 @@ __device__ __forceinline__ void gemm_neurons(const float* wf, const char* st, in
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) acc[r][cb] = zero4();
   const char* sp = st + ls.pair;
-  v8h b[CG][3], bn[CG][3];
-  if (DB && KF > 0) stack_operand<CG>(sp, 0, bn);
-  for (int kb = 0; kb < KF; ++kb, sp += kNext) {
-    v4f a[R][3];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int p = 0; p < 3; ++p) a[r][p] = f.a[r][p];
-    load_frags<R>(wf, KB, kb + 1 < KB ? kb + 1 : kb, lane16, f);   // (the last one again at the end)
+  v8h b[2][CG][3];
+  if (KF > 0) stack_operand<CG>(sp, 0, b[0]);
+  Frags<R> f2;
+  auto block = [&](Frags<R>& cur, Frags<R>& nxt, int kb, auto par) {
+    constexpr int P = NG & 1 ? decltype(par)::value : 0;
+    uint32_t lo = lane16;
+    asm volatile("" : "+v"(lo));   // (scalar bases)
+    load_frags<R>(wf, KB, kb + 1 < KB ? kb + 1 : kb, lo, nxt);   // (the last one again at the end)
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) {
-      if constexpr (DB) {
+      const int c0 = gi + 1 < NG ? (gi + 1) * CG : 0;
+      if (gi + 1 == NG) sp += kb + 1 < KF ? kNext : 0;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
 #pragma unroll
         for (int c = 0; c < CG; ++c)
 #pragma unroll
-          for (int p = 0; p < 3; ++p) b[c][p] = bn[c][p];
-        if (gi + 1 < NG) stack_operand<CG>(sp, (gi + 1) * CG, bn);
-        else stack_operand<CG>(kb + 1 < KF ? sp + kNext : sp, 0, bn);
-      } else {
-        stack_operand<CG>(sp, gi * CG, b);
+          for (int r = 0; r < R; ++r)
+            acc[r][gi * CG + c] = mfma32(__builtin_bit_cast(v8h, cur.a[r][kPartA[q]]), b[(gi + P) & 1][c][kPartB[q]], acc[r][gi * CG + c]);
+        if (q < 3 * CG) {
+          const int c = q % CG, p = kPartB[q / CG];
+          b[(gi + 1 + P) & 1][c][p] = *reinterpret_cast<const v8h*>(sp + ((c0 + c) * 3 + p) * 2 * kUnit);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      products32<R, NCB, CG>(a, b, gi * CG, acc);
     }
+  };
+  int kb = 0;
+  for (; kb + 2 <= KF; kb += 2) {
+    block(f, f2, kb, std::integral_constant<int, 0>{});
+    block(f2, f, kb + 1, std::integral_constant<int, 1>{});
   }
+  if (kb < KF) {
+    block(f, f2, kb, std::integral_constant<int, 0>{});
+    f = f2;
+  }
+  if (KF > 0) sp += kNext;
   if (NW & 1) products16<R, NCB, CG>(f.a, sp + ls.alone - ls.pair, acc);
 }
 
