@@ -449,7 +449,7 @@ __device__ __forceinline__ void input_layer_t(v4f (&a)[NCB], const float* __rest
 }
 
 // one tile after another of this workgroup's item ranges, for a wave of R row blocks
-template <int DIM, int PBP, int ACT, int R>
+template <int DIM, int PBP, int ACT, int R, int WIDE>
 __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int rb0, int w) {
   constexpr int D = DIM + 1;
   constexpr int CF = 2 * DIM + 2;
@@ -476,6 +476,18 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
   float* ys = reinterpret_cast<float*>(lds + L.ys);
   float* xin = reinterpret_cast<float*>(lds + L.xin);
   char* mine = lds + rb0 * Stack<NCB>::kRow;   // the wave's row blocks in the stack
+  // dW row blocks of the wave: its own, but some of the second ones above eight row blocks go
+  // to a wave with one, on another SIMD (wave v is on SIMD v mod 4).  Of the NW - 8 second blocks a SIMD
+  // whose waves hold more blocks than another's has, between two barriers of the backward, that much more
+  // Hbar; n mod 4 = 1, 2, 3 of them are uneven, and the first 1, 2, 1 of
+  // those uneven ones move by as many waves (dW of 10 blocks: 5 row block products per
+  // SIMD instead of 6, 6, 4, 4).
+  int dw2 = R > 1 ? rb0 + 1 : -1;   // the second dW row block, or none
+  if constexpr (WIDE) {
+    const int ne = NW - sh.NWV, m = ne & 3, n_move = m == 2 ? 2 : m ? 1 : 0;
+    const int v = R > 1 ? w : w - m;   // the wave whose second block it is about
+    if (v >= ne - m && v < ne - m + n_move) dw2 = R > 1 ? -1 : split_rb0(v, NW, sh.NWV) + 1;
+  }
   // stash: (layer, row block, block), 1 KiB wave fragments
   float* stash = args.stash + (size_t)blockIdx.x * args.stash_per_wg + (size_t)rb0 * NZ * 256;
   const size_t stash_l = (size_t)NW * NZ * 256;
@@ -741,8 +753,8 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
           for (int cb = 0; cb < NCB; ++cb) acc[r][cb] = hb[cb];
         }
       }
-      auto load_z = [&](int l, int r, v4f (&z)[NZ]) {   // of layer l, row block r
-        const float* st = stash + (size_t)(l - 1) * stash_l + (size_t)r * NZ * 256;
+      auto load_z = [&](int l, int r, v4f (&z)[NZ]) {   // of layer l, row block rb0 + r
+        const float* st = stash + (ptrdiff_t)(l - 1) * (ptrdiff_t)stash_l + (ptrdiff_t)r * NZ * 256;
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) z[cb] = ldg4u(st + cb * 256, lane16);
 #pragma unroll
@@ -814,16 +826,18 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
         put_rows<R, NCB>(mine, ss, acc);
         __syncthreads();
         load_frags<R>(wt + (size_t)(l - 2) * sh.hid3_layer, KB, 0, lane16, f);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
+        for (int n = rb0; n >= 0;) {
           v8h ha[NCB / 2][3];
           if (pde) h_operand<DIM, NCB, M_PDE, ACT>(z, swap, ha);
           else h_operand<DIM, NCB, M_VALUE, ACT>(z, swap, ha);
-          if (R > 1) load_z(l - 1, r + 1 < R ? r + 1 : 0, z);   // for the next row block, at last again the first
+          const int next = WIDE && n == rb0 ? dw2 : -1;
+          if (WIDE && dw2 >= 0) load_z(l - 1, next >= 0 ? next - rb0 : 0, z);   // of the next one, at last again of the first
           if (prio) __builtin_amdgcn_s_setprio(1);
           gemm_columns_t<NCB>(ha, lds, NW, ss, lane16,
-                              slab + sh.s_hid + (size_t)(l - 2) * Wp * Wp + (size_t)(rb0 + r) * NW * 256, first);
+                              slab + sh.s_hid + (size_t)(l - 2) * Wp * Wp + (size_t)n * NW * 256, first);
           __builtin_amdgcn_s_setprio(0);
+          if (!WIDE) break;
+          n = next;
         }
         if (prio) __builtin_amdgcn_s_setprio(1);
         gemm_neurons_t<R, NCB>(wt + (size_t)(l - 2) * sh.hid3_layer, lds, NW, ss, lane16, f, acc);   // Hbar_{l-1}
@@ -868,10 +882,10 @@ __global__ __launch_bounds__(PBP == 1 ? 512 : 256, PBP == 1 ? 2 : 1) void split_
   if constexpr (WIDE) {
     const int rb0 = split_rb0(w, args.sh.NW, args.sh.NWV);
     // both branches meet the same barriers
-    if (w < args.sh.NW - args.sh.NWV) step_tiles<DIM, PBP, ACT, 2>(args, slds, rb0, w);
-    else step_tiles<DIM, PBP, ACT, 1>(args, slds, rb0, w);
+    if (w < args.sh.NW - args.sh.NWV) step_tiles<DIM, PBP, ACT, 2, 1>(args, slds, rb0, w);
+    else step_tiles<DIM, PBP, ACT, 1, 1>(args, slds, rb0, w);
   } else {
-    step_tiles<DIM, PBP, ACT, 1>(args, slds, w, w);
+    step_tiles<DIM, PBP, ACT, 1, 0>(args, slds, w, w);
   }
 }
 
