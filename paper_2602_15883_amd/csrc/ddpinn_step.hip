@@ -729,6 +729,8 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
         for (int r = 0; r < R; ++r) {
           v4f hb[NCB];
 #pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) hb[cb] = zero4();
+#pragma unroll(WIDE ? 1 : D)   // (unrolled, ys is read for all outputs at once: with two row blocks, registers spill)
           for (int o = 0; o < D; ++o) {
             const float old = (g == 0 && !first) ? ldgu(so + o * Wp + 16 * r, j4) : 0.f;
             const float wo = ldgu(Wop + o * Wp + 16 * (rb0 + r), j4);
@@ -738,9 +740,8 @@ __device__ __forceinline__ void step_tiles(const StepArgs& args, char* lds, int 
               const v4f yv = *reinterpret_cast<const v4f*>(ys + o * NCOL + 16 * cb + 4 * g);
               if (r == 0 && cb < nvb) b += (yv[0] + yv[1]) + (yv[2] + yv[3]);
               s += (yv[0] * acc[r][cb][0] + yv[1] * acc[r][cb][1]) + (yv[2] * acc[r][cb][2] + yv[3] * acc[r][cb][3]);
-              hb[cb] = o == 0 ? wo * yv : hb[cb] + wo * yv;
+              hb[cb] += wo * yv;
             }
-            if (R > 1) __builtin_amdgcn_sched_barrier(0);   // (ys would be read for all outputs at once)
             s = group_sum(s);
             if (g == 0) stgu(so + o * Wp + 16 * r, j4, old + s);
             if (r == 0) {
