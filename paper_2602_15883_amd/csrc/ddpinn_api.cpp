@@ -79,6 +79,7 @@ Shape make_shape(int dim, int W, int H) {
   sh.NW = sh.Wp / 16;
   sh.s3 = split_fits(dim, sh.NW) ? 1 : 0;
   sh.NWV = std::min(sh.NW, kMaxWaves);
+  sh.NWS = sh.NWV;
   sh.Kq = sh.s3 ? sh.Wp / 4 : (W + 3) / 4;   // triples: neurons at their own positions
   sh.P = (int32_t)nparams(dim, W, H);
   const int64_t Wp = sh.Wp, D = sh.D;
@@ -146,6 +147,14 @@ void tiles_of(const pinn_subdomain& s, int sub, int tp, int tv, std::vector<Item
 // the extra activation work of a value tile is per wave (independent of the
 // width) while the GEMM work per wave grows with it.
 double value_tile_cost(const Shape& sh) { return 1.0 + 21.0 / sh.Wp; }
+
+constexpr int64_t kLastLevelCache = 256 << 20;   // bytes
+
+// stash of a workgroup of the step
+int64_t stash_floats(const Shape& sh, int tile_points) {
+  const int pb = tile_points / 16, more = sh.s3 && sh.act == 1 ? pb : 0;   // sin, triples: cos(z_0) too
+  return (int64_t)sh.NW * sh.H * ((2 * sh.dim + 2) * pb + more) * 256;
+}
 
 // Split a sorted item list into n_wg contiguous ranges of equal estimated
 // cost and mark segments (maximal runs of one subdomain inside one
@@ -385,7 +394,22 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
 
   // tile shape: 32-point collocation tiles when they fit in LDS with at
   // least the occupancy of 16-point tiles, unless fixed by the caller
-  c->threads = sh.NWV * 64;
+  //
+  // Two workgroups of four waves per compute unit in place of one of up to
+  // eight, where both fit (step_halves) and there are tiles for them: a wave then owns two row
+  // blocks, reads the LDS stack half as often, and one workgroup's vector phases overlap the
+  // other's products.  Each holds a stash and a slab, and above the 256 MB of the last-level cache
+  // for all of them the step slows down: gradient of 3D 5x96, 20,000 points (200 MB)
+  // 0.36 -> 0.31 ms, 2D 8x80, 100,000 points (230 MB) 1.65 -> 1.47 ms; 2D 8x100 (380 MB) 2.34
+  // -> 2.59 ms.  A caller's blocks_per_cu = 1 keeps the one workgroup.
+  if (step_halves(sh) && cfg->tile_points != 32 && cfg->blocks_per_cu != 1) {
+    std::vector<Item> tiles;
+    for (int s = 0; s < c->n_sub; ++s) tiles_of(c->subs[s], s, 16, step_value_points(sh.dim, 16), tiles);
+    const int64_t n = (int64_t)tiles.size(), wg = std::min<int64_t>(n, 2 * c->num_cu);
+    if (n > c->num_cu && wg * (sh.slab_floats + stash_floats(sh, 16)) * 4 <= kLastLevelCache) c->sh.NWS = 4;
+  }
+  c->threads = sh.NWS * 64;
+  const int qthreads = sh.NWV * 64;
   auto occ_of = [&](int tp, int* occ) -> pinn_status {
     const int lf = step_lds_floats(sh, tp);
     const void* k = step_kernel_ptr(sh, tp);
@@ -403,7 +427,7 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   if (tp == 0) tp = 16;
   const int occ = (tp == 32) ? occ32 : occ16;
   if (occ < 1) {
-    if (!step_kernel_ptr(sh, tp))
+    if (tp == 32 && sh.NW > kMaxWaves)
       return fail(PINN_E_UNSUPPORTED, "width %d: only 16-point tiles above %d neurons", cfg->width, 16 * kMaxWaves);
     return fail(PINN_E_UNSUPPORTED, "tile of %d points needs %d B of LDS per workgroup (device limit %d B)", tp,
                 step_lds_floats(sh, tp) * 4, max_lds);
@@ -418,20 +442,20 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   // would leave its last workgroups to start after the others finish
   for (int q = 0; q < 4; ++q) {
     int nb = 0;
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, query_kernel_ptr(sh, q), c->threads,
+    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, query_kernel_ptr(sh, q), qthreads,
                                                           (size_t)c->qlds_floats * 4));
     c->query_occ[q] = std::max(1, nb);
   }
   c->qlds_small_floats = query_lds_floats(sh, 1);
   for (int q = 0; q < 2; ++q) {
     int nb = 0;
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, query_kernel_ptr(sh, q, 1), c->threads,
+    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, query_kernel_ptr(sh, q, 1), qthreads,
                                                           (size_t)c->qlds_small_floats * 4));
     c->query_occ_small[q] = std::max(1, nb);
   }
   {
     int nb = 0;
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, exchange_kernel_ptr(sh), c->threads,
+    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, exchange_kernel_ptr(sh), qthreads,
                                                           (size_t)c->qlds_floats * 4));
     c->exch_occ = std::max(1, nb);
   }
@@ -446,7 +470,8 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   // different rates; ranges handed out in turn (four per workgroup unless the
   // caller's tuning says otherwise) even it out.
   c->dynamic = c->step_occ > 1;
-  const int rpw = cfg->ranges_per_wg > 0 ? cfg->ranges_per_wg : 4;
+  // (one for the halves: a range has its own slab to be summed, 2D 8x80 1.41 against 1.58 ms per step with four)
+  const int rpw = cfg->ranges_per_wg > 0 ? cfg->ranges_per_wg : (sh.NWS < sh.NWV ? 1 : 4);
   auto ranges_for = [&](int n_items, int n_wg) {
     return c->dynamic ? std::max(1, std::min(n_items, rpw * n_wg)) : n_wg;
   };
@@ -490,8 +515,7 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   }
   c->n_slabs = std::max(std::max(c->n_seg, c->ps_seg), 1);
   const int stash_wg = std::max(c->n_wg, 1);
-  const int NCB = (2 * sh.dim + 2) * (c->tile_points / 16);
-  c->stash_per_wg = (int64_t)sh.NW * sh.H * (NCB + (sh.s3 && sh.act == 1 ? c->tile_points / 16 : 0)) * 256;   // sin, triples: cos(z_0) too
+  c->stash_per_wg = stash_floats(sh, c->tile_points);
 
   // exchange capacity: every ghost point in a half tile, plus one partial tile per face
   int64_t xcap = 0;

@@ -55,7 +55,8 @@ struct Shape {
   int32_t dim, D, W, H, Wp, NW;   // D = dim+1 inputs/outputs; Wp = W padded to 16; NW = Wp/16 row blocks
   int32_t P;                      // packed parameter count
   int32_t act;                    // activation: 0 tanh, 1 sin
-  int32_t NWV;                    // waves per workgroup, min(NW, kMaxWaves)
+  int32_t NWV;                    // waves per workgroup of the queries and the exchange, min(NW, kMaxWaves)
+  int32_t NWS;                    // waves per workgroup of the step: NWV, or 4 (step_halves)
   int32_t s3;                     // the kernels on bf16 triples (ddpinn_split.h), else ddpinn_wide.hip
   int32_t Kq;                     // ceil(W/4): K-steps of the hidden-layer GEMMs (hidden neurons
                                   // are stored at permuted positions, see hid_pos)
@@ -223,7 +224,7 @@ hipError_t launch_evaluate(const EvalArgs& a, hipStream_t s);
 // eight waves; above 128 neurons (queries and exchange) eight waves, the first NW - 8 of them
 // with two row blocks (waves w and w + 4 share a SIMD, which so holds at most
 // one row block more than another).
-template <int DIM, int ACT> const void* split_step_ptr(int tile_points, int NW);
+template <int DIM, int ACT> const void* split_step_ptr(int tile_points, int NW, int NWS);
 template <int DIM> const void* split_query_ptr(int mode, int act, int small, int NW);
 template <int DIM> const void* split_exchange_ptr(int act, int NW);
 // Kernels on FP32 MFMA (ddpinn_wide.hip): the step above 128 neurons, queries of
@@ -235,6 +236,7 @@ int wide_step_lds_floats(const Shape& sh);
 int wide_query_lds_floats(const Shape& sh, int small);
 // whether a query tile's activation stack of triples fits in LDS (all 2D networks, 3D up to 208 neurons)
 bool split_fits(int dim, int NW);
+bool step_halves(const Shape& sh);
 
 // Kernel entry points and their LDS needs (for graph nodes and occupancy).
 const void* step_kernel_ptr(const Shape& sh, int tile_points);

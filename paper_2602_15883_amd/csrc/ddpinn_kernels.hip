@@ -568,15 +568,21 @@ bool split_fits(int dim, int NW) {
   return std::max(split_query_lds(dim + 1, NW, std::min(NW, 8), NCB).total, split_step_lds(dim + 1, NW, NCB).total) <= kLdsBytes;
 }
 
-static const void* split_step_any(int dim, int tile_points, int act, int NW) {
-  if (dim == 2) return act == ACT_SIN ? split_step_ptr<2, ACT_SIN>(tile_points, NW) : split_step_ptr<2, ACT_TANH>(tile_points, NW);
-  return act == ACT_SIN ? split_step_ptr<3, ACT_SIN>(tile_points, NW) : split_step_ptr<3, ACT_TANH>(tile_points, NW);
+static const void* split_step_any(int dim, int tile_points, int act, int NW, int NWS) {
+  if (dim == 2) return act == ACT_SIN ? split_step_ptr<2, ACT_SIN>(tile_points, NW, NWS) : split_step_ptr<2, ACT_TANH>(tile_points, NW, NWS);
+  return act == ACT_SIN ? split_step_ptr<3, ACT_SIN>(tile_points, NW, NWS) : split_step_ptr<3, ACT_TANH>(tile_points, NW, NWS);
 }
 static const void* split_query_any(int dim, int mode, int act, int small, int NW) {
   return dim == 2 ? split_query_ptr<2>(mode, act, small, NW) : split_query_ptr<3>(mode, act, small, NW);
 }
 static const void* split_exchange_any(int dim, int act, int NW) {
   return dim == 2 ? split_exchange_ptr<2>(act, NW) : split_exchange_ptr<3>(act, NW);
+}
+
+// Five to eight row blocks whose stack fits in the LDS twice: the step can run two
+// workgroups of four waves per compute unit in place of one of eight.
+bool step_halves(const Shape& sh) {
+  return sh.s3 && sh.NW > 4 && sh.NW <= kMaxWaves && 2 * split_step_lds(sh.D, sh.NW, 2 * sh.dim + 2).total <= kLdsBytes;
 }
 
 int step_lds_floats(const Shape& sh, int tile_points) {
@@ -590,7 +596,7 @@ int query_lds_floats(const Shape& sh, int small) {
 }
 
 const void* step_kernel_ptr(const Shape& sh, int tile_points) {
-  if (sh.s3) return split_step_any(sh.dim, tile_points, sh.act, sh.NW);
+  if (sh.s3) return split_step_any(sh.dim, tile_points, sh.act, sh.NW, sh.NWS);
   return tile_points == 16 ? wide_step_ptr(sh.act) : nullptr;
 }
 const void* prep_kernel_ptr() { return (const void*)prep_kernel; }
@@ -622,7 +628,7 @@ hipError_t launch_step(const StepArgs& a, int tile_points, int n_wg, hipStream_t
   const size_t lds = (size_t)a.lds_floats * sizeof(float);
   const void* k = step_kernel_ptr(a.sh, tile_points);
   if (!k) return hipErrorInvalidValue;
-  const dim3 block(a.sh.NWV * 64);
+  const dim3 block(a.sh.NWS * 64);
   void* args[] = {const_cast<StepArgs*>(&a)};
   return hipLaunchKernel(k, dim3(n_wg), block, args, lds, s);
 }
@@ -643,7 +649,7 @@ hipError_t launch_step_timed(const StepArgs& a, int tile_points, int n_wg, hipSt
   const size_t lds = (size_t)a.lds_floats * sizeof(float);
   const void* k = step_kernel_ptr(a.sh, tile_points);
   if (!k) return hipErrorInvalidValue;
-  const dim3 block(a.sh.NWV * 64);
+  const dim3 block(a.sh.NWS * 64);
   void* args[] = {const_cast<StepArgs*>(&a)};
   return hipExtLaunchKernel(k, dim3(n_wg), block, args, lds, s, e0, e1, 0);
 }
@@ -704,8 +710,8 @@ hipError_t set_lds_limits(int bytes) {
   };
   for (int dim = 2; dim <= 3; ++dim)
     for (int act = ACT_TANH; act <= ACT_SIN; ++act) {
-      allow(split_step_any(dim, 32, act, 4));
-      for (int nw : {8, 13}) allow(split_step_any(dim, 16, act, nw));
+      allow(split_step_any(dim, 32, act, 4, 4));
+      for (int nw : {8, 13}) allow(split_step_any(dim, 16, act, nw, 8));
       for (int nw : {8, 16}) {
         for (int mode : {M_PDE, M_VALUE, M_GRAD}) {
           allow(split_query_any(dim, mode, act, 0, nw));

@@ -68,6 +68,34 @@ def test_split_kernels_against_oracle(orc, dim, W, H, act, npde):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dim,W,H,act", [(3, 96, 3, "tanh"), (2, 80, 2, "sin"), (2, 112, 2, "tanh"), (2, 128, 2, "sin")])
+def test_two_workgroups_per_compute_unit(orc, dim, W, H, act):
+    """Five to eight row blocks and more tiles than compute units: workgroups of four
+    waves, one to four of which own two row blocks (and hand on the dW of some)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2602_15883_amd as P
+    print(f"halves dim={dim} W={W} H={H} act={act}", flush=True)
+    orc.set_activation(act)
+    try:
+        pb = wl.tiny(dim=dim, width=W, depth=H, n_pde=16 * 300 + 3, n_obs=70, n_gh=7, n_anc=1, seed=W)
+        pb.activation = act
+        tol = 16 * H * np.sqrt(W + 16) * 2.0 ** -24 * 4
+        Lr, gr = oracle_loss_grad(orc, pb)
+        for per_cu, threads in ((0, 256), (1, 64 * ((W + 15) // 16))):
+            ctx = P.context_from_problem(pb, device="cuda", blocks_per_cu=per_cu)
+            try:
+                assert ctx.launch_info()["threads"] == threads
+                loss, g = ctx.step(1, update=False, want_grad=True)
+                for name, a, b in (("loss", loss.cpu().numpy()[0], Lr), ("grad", g.cpu().numpy()[0], gr)):
+                    assert rel_report(a, b)[1] <= tol, (name, per_cu, rel_report(a, b), tol)
+            finally:
+                ctx.close()
+    finally:
+        orc.set_activation("tanh")
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("dim,W,H,act,clip", [(2, 50, 3, "tanh", 0.0), (3, 17, 2, "sin", 1e-3), (2, 112, 1, "tanh", 0.0),
                                               (2, 150, 2, "sin", 0.5), (3, 200, 2, "tanh", 0.0), (3, 240, 2, "tanh", 1.0)])
 def test_adam_leaves_the_weight_copies_current(dim, W, H, act, clip):
