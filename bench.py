@@ -12,7 +12,8 @@ also carries:
   roofline          the fused step kernel's algorithmic FP32 FLOPs per launch
                     divided by its average duration (HIP events tied to the
                     kernel's dispatch: its start and end time stamps), against
-                    the FP32 MFMA peak, plus HBM traffic from rocprofv3
+                    the matrix peak for FP32 operands (six bf16 products per
+                    multiply-add), plus HBM traffic from rocprofv3
                     counters when a matching profile is committed under
                     profiles/
   config2           the same figures for the 2D 3->8x100->3 network at 100,000
@@ -44,7 +45,8 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_FP32_MFMA_TFLOPS = 157.3     # MI355X dense FP32 matrix
+# FP32 multiply-adds on the bf16 matrix units (2.5166 PFLOP/s dense), six products each
+PEAK_FP32_MFMA_TFLOPS = 2516.6 / 6
 PEAK_HBM_GBS = 8000.0
 COPY_BYTES = 256 << 20            # size of the counter-calibration copy (each way)
 

@@ -24,8 +24,6 @@ __device__ __forceinline__ v4f zero4() { return v4f{0.f, 0.f, 0.f, 0.f}; }
 #define CONST_AS __attribute__((address_space(4)))
 __device__ __forceinline__ v4f ldg4(const float* p) { return *(const GLOBAL_AS v4f*)p; }
 __device__ __forceinline__ float ldg(const float* p) { return *(const GLOBAL_AS float*)p; }
-__device__ __forceinline__ void stg4(float* p, v4f v) { *(GLOBAL_AS v4f*)p = v; }
-__device__ __forceinline__ void stg(float* p, float v) { *(GLOBAL_AS float*)p = v; }
 // wave-uniform base + 32-bit per-lane byte offset: selects the scalar-base
 // addressing form (one lane-offset register instead of a 64-bit address per lane)
 __device__ __forceinline__ v4f ldg4u(const float* base, uint32_t off) {
@@ -218,14 +216,14 @@ __device__ __forceinline__ void act_forward(v4f (&a)[NCB]) {
 //   zbar_j  = s1 hbar_j + 2 s2 z_j hbar_jj      (spatial j; time: s1 hbar_t)
 //   zbar_0  = s1 hbar_0 + s2 sum_j z_j hbar_j + sum_j (s3 z_j^2 + s2 z_jj) hbar_jj
 //   with s1, s2, s3 the first three derivatives of the activation at z_0
-template <int DIM, int NCB, int MODE, int ACT, bool SV = false>
+template <int DIM, int NCB, int MODE, int ACT>
 __device__ __forceinline__ void act_adjoint(v4f (&hb)[NCB], const v4f (&zs)[NCB]) {
   using M = ModeCfg<DIM, NCB, MODE>;
   constexpr int NPB = M::NPB;
 #pragma unroll
   for (int pb = 0; pb < NPB; ++pb) {
     v4f s, s1, s2;
-    act4<ACT, SV>(zs[pb], s, s1, s2);
+    act4<ACT>(zs[pb], s, s1, s2);
     v4f z0b = s1 * hb[pb];
     if constexpr (MODE == M_PDE) {
       const v4f s3 = act_third<ACT>(s, s1);
@@ -255,13 +253,6 @@ __device__ __forceinline__ float sum16(float v) {
   v += __shfl_xor(v, 4, 16);
   v += __shfl_xor(v, 2, 16);
   v += __shfl_xor(v, 1, 16);
-  return v;
-}
-
-// sum over the four lane groups (same j)
-__device__ __forceinline__ float sum_groups(float v) {
-  v += __shfl_xor(v, 16, 64);
-  v += __shfl_xor(v, 32, 64);
   return v;
 }
 

@@ -221,20 +221,19 @@ hipError_t launch_evaluate(const EvalArgs& a, hipStream_t s);
 
 // Kernels on bf16 triples (ddpinn_step.hip, ddpinn_query.hip): one instance
 // file per dimension (and activation).  One row block of 16 neurons per wave up to
-// eight waves; above 128 neurons (queries and exchange) eight waves, the first NW - 8 of them
-// with two row blocks (waves w and w + 4 share a SIMD, which so holds at most
+// eight waves; with fewer waves than row blocks (above 128 neurons, and step_halves) the first
+// ones have two (waves w and w + 4 share a SIMD, which so holds at most
 // one row block more than another).
 template <int DIM, int ACT> const void* split_step_ptr(int tile_points, int NW, int NWS);
 template <int DIM> const void* split_query_ptr(int mode, int act, int small, int NW);
 template <int DIM> const void* split_exchange_ptr(int act, int NW);
-// Kernels on FP32 MFMA (ddpinn_wide.hip): the step above 128 neurons, queries of
-// 3D networks above 208
+// Kernels on FP32 MFMA (ddpinn_wide.hip): 3D networks above 208 neurons
 const void* wide_step_ptr(int act);
 const void* wide_query_ptr(int mode, int act, int small);
 const void* wide_exchange_ptr(int act);
 int wide_step_lds_floats(const Shape& sh);
 int wide_query_lds_floats(const Shape& sh, int small);
-// whether a query tile's activation stack of triples fits in LDS (all 2D networks, 3D up to 208 neurons)
+// whether a tile's activation stack of triples fits in LDS (all 2D networks, 3D up to 208 neurons)
 bool split_fits(int dim, int NW);
 bool step_halves(const Shape& sh);
 

@@ -1,8 +1,8 @@
 // Kernels around the networks, and the launchers: weight copies, gradient
 // reduction and Adam, query routing, evaluation metrics (arXiv 2602.15883,
 // sections 2.1, 2.2 and 3).  The network kernels are in ddpinn_step.hip (the fused
-// training step up to 128 neurons), ddpinn_query.hip (query and exchange) and ddpinn_wide.hip
-// (the step above 128 neurons; query and exchange of 3D networks above 208).
+// training step), ddpinn_query.hip (query and exchange) and ddpinn_wide.hip (all three for
+// 3D networks above 208 neurons).
 //
 // Gradients: each workgroup of the step accumulates its contribution in a
 // private slab (one per (workgroup, subdomain) segment); the slabs are summed in
@@ -563,6 +563,10 @@ int step_value_points(int dim, int tile_points) {
 
 // LDS of a compute unit
 constexpr int kLdsBytes = 160 * 1024;
+
+// The kernels on triples serve every network whose stack fits: where both kinds ran, the fp32 ones
+// were slower at every width (3D 8x200, 600,000 points: 104 against 55 ms per step; 2D 4x50,
+// 2,000 points: 69 against 47 us).
 bool split_fits(int dim, int NW) {
   const int NCB = 2 * dim + 2;
   return std::max(split_query_lds(dim + 1, NW, std::min(NW, 8), NCB).total, split_step_lds(dim + 1, NW, NCB).total) <= kLdsBytes;

@@ -20,27 +20,25 @@
 // scaled.  An infinite operand gives NaN (inf - inf in the split) where fp32
 // arithmetic might give an infinity.
 //
-// Tile layout.  A wave owns R row blocks of 16 neurons.  Its accumulator
-// fragment acc[r][cb] holds, in lane (g, j) (g = lane / 16, j = lane % 16),
-// neurons 4g + i (i = 0..3) of the row block and column 16 cb + j: four bf16
-// per part, 8 bytes.  The LDS stack of a layer holds exactly those fragments, so
-// a layer's result goes to LDS without any exchange between lanes:
-//   * two row blocks 2 kb, 2 kb + 1 (K block kb) share units of 1 KiB, one per
-//     (kb, column block, part): 64 slots of 16 bytes, slot (g, j) at 16 g + (j ^ c(g)),
-//     c = 0, 12, 4, 8; the even row block's 8 bytes come first for g = 0, 3 and
-//     second for g = 1, 2.  As the operand of a contraction over neurons a slot
-//     (one ds_read_b128) is a lane's 8 K values; the weight fragments use the same
-//     order of neurons (k_neuron).
-//   * the last row block of an odd number has units of 512 bytes, slot
-//     (g, j) of 8 bytes at 16 g + (j ^ 4 g).
-//   * as the operand of the weight gradient (a contraction over columns) the
-//     transposing LDS read (ds_read_b64_tr_b16) gives each lane one neuron
-//     and four columns.
-// LDS serves 16-byte reads 16 lanes at a time (of two lane groups g = 2k, 2k + 1: j in
-// 0..3, 12..15 of one and 4..11 of the other) and 8-byte ones 32 at a time; with this
-// placement both kinds touch every bank once.  Measured on one compute unit:
-// 263 bytes/clock for the 16-byte reads and 248 for the transposing ones, against 138
-// for pairs of 8-byte reads from a layout of 512-byte units.
+// The kernels keep the operands of one side, the activations (or Zbar), in an LDS
+// stack of parts, 6 bytes per value, and stream the weights as fragments.  A stack
+// unit holds, for two blocks of 16, 64 slots of 16 bytes in lane order: slot (g, j) (g = lane / 16,
+// j = lane % 16) at 16 g + (j ^ c(g)), c = 0, 12, 4, 8; the even block's 8 bytes (four bf16 of
+// an accumulator fragment) come first for g = 0, 3 and second for g = 1, 2, so
+// a result goes to LDS without any exchange between lanes.  LDS serves 16-byte reads
+// 16 lanes at a time (of two lane groups g = 2k, 2k + 1: j in 0..3, 12..15 of one and 4..11
+// of the other) and 8-byte ones 32 at a time; with this placement a read of a slot
+// (ds_read_b128) and a transposing read (ds_read_b64_tr_b16) both touch every bank
+// once.  Measured on one compute unit: 263 bytes/clock for the 16-byte reads and 248 for the
+// transposing ones, against 138 for pairs of 8-byte reads from units of 512 bytes.
+//
+// Here: the queries and the exchange.  A wave owns R row blocks of 16 neurons; its
+// accumulator fragment acc[r][cb] holds, in lane (g, j), neurons 4g + i (i = 0..3) of
+// the row block and column 16 cb + j.  Two row blocks 2 kb, 2 kb + 1 (K block kb) share
+// units, one per (kb, column block, part); a slot is then a lane's 8 K values of a contraction
+// over neurons, and the weight fragments use the same order of neurons (k_neuron).
+// The last row block of an odd number has units of 512 bytes, slot (g, j) of 8
+// bytes at 16 g + (j ^ 4 g).  The training step has its tiles transposed (ddpinn_step.hip).
 #pragma once
 #include <type_traits>
 
@@ -68,19 +66,18 @@ __host__ __device__ __forceinline__ int k_neuron(int g, int e) { return 16 * ((e
 
 // a lane's byte offsets within the units: 16-byte slots of a pair of row
 // blocks, 8-byte slots of a row block that stands alone; plain and transposing
-struct LaneSlots { uint32_t pair, half, alone, pair_tr, half_tr, alone_tr; };
+struct LaneSlots { uint32_t pair, half, alone, pair_tr, half_tr; };
 __device__ __forceinline__ LaneSlots lane_slots(int lane) {
   const int g = lane >> 4, j = lane & 15;
   LaneSlots s;
   s.pair = (uint32_t)(16 * g + (j ^ slot_xor(g))) * 16u;
   s.half = (uint32_t)slot_half(g) * 8u;            // of the even row block; the odd one's is 8 - half
   s.alone = (uint32_t)(16 * g + (j ^ (4 * g))) * 8u;
-  // transposing read: lane i of group gp fetches four neurons (4 gq ..) of column
-  // 4 gp + i / 4, gq = i % 4, and receives neuron i, columns 4 gp .. 4 gp + 3
+  // transposing read: lane i of group gp fetches four values of the slot (i % 4, 4 gp +
+  // i / 4) and receives value i of the slots' sixteen, for 4 gp .. 4 gp + 3
   const int col = 4 * g + ((lane >> 2) & 3), gq = lane & 3;
   s.pair_tr = (uint32_t)(16 * gq + (col ^ slot_xor(gq))) * 16u;
   s.half_tr = (uint32_t)slot_half(gq) * 8u;
-  s.alone_tr = (uint32_t)(16 * gq + (col ^ (4 * gq))) * 8u;
   return s;
 }
 
@@ -376,7 +373,7 @@ __host__ __device__ inline SplitQueryLds split_query_lds(int D, int NW, int NWV,
 
 // LDS of a step workgroup, in bytes.  ys holds the outputs, then (in place) the
 // loss seeds ybar; it also takes the loss sums at the end of a segment and the
-// index of the item range.  The stack takes the output layer's partial sums.
+// index of the item range.
 struct SplitStepLds { int ys, xin, total; };
 __host__ __device__ inline SplitStepLds split_step_lds(int D, int NW, int NCB) {
   SplitStepLds L;
