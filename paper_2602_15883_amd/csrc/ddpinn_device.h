@@ -324,7 +324,8 @@ __device__ __forceinline__ void residuals(F Y, float nu, float (&r)[DIM + 1]) {
 }
 
 // ---------------------------------------------------------------------------
-// Hidden-neuron positions.  A hidden layer's Wp positions are read by the four
+// Hidden-neuron positions (fp32 kernels; on triples Kq = Wp/4 and every neuron is at
+// its own position).  A hidden layer's Wp positions are read by the four
 // lane groups of a GEMM's K dimension in segments of Wp/4.  Neuron n sits at
 // position (n / Kq) * (Wp/4) + n % Kq with Kq = ceil(W/4): the padding fills
 // the tail of every segment, so the GEMMs stop after Kq K-steps instead of

@@ -58,11 +58,11 @@ struct Shape {
   int32_t NWV;                    // waves per workgroup of the queries and the exchange, min(NW, kMaxWaves)
   int32_t NWS;                    // waves per workgroup of the step: NWV, or 4 (step_halves)
   int32_t s3;                     // the kernels on bf16 triples (ddpinn_split.h), else ddpinn_wide.hip
-  int32_t Kq;                     // ceil(W/4): K-steps of the hidden-layer GEMMs (hidden neurons
-                                  // are stored at permuted positions, see hid_pos)
+  int32_t Kq;                     // fp32 kernels: ceil(W/4), K-steps of the hidden-layer GEMMs (hidden
+                                  // neurons are stored at permuted positions, see hid_pos); else Wp/4
   int32_t pad_;
   // fragment buffer (per subdomain)
-  int64_t f_hid;   // hidden layer l (2..H): forward A-fragments at f_hid + (l-2)*2*Wp*Wp,
+  int64_t f_hid;   // fp32 kernels: hidden layer l (2..H), forward A-fragments at f_hid + (l-2)*2*Wp*Wp,
                    // transposed (backward) A-fragments Wp*Wp further
   int64_t f_w1;    // W1 padded [Wp][D]
   int64_t f_b;     // b_1..b_H padded [H][Wp]
@@ -99,7 +99,7 @@ struct StepArgs {
   int64_t stash_per_wg;     // floats
   float nu;
   int32_t lds_floats;
-  int32_t prio;             // the younger half of the waves raises its priority for its GEMMs
+  int32_t prio;             // waves raise their priority for their matrix phases
   int32_t pad_;
 };
 

@@ -1,8 +1,8 @@
 """Autotuner for the fused step's launch shape.
 
 Knobs: collocation points per tile (16, or 32 when the workgroup has at most
-four waves), persistent workgroups per compute unit, whether the younger half
-of a workgroup's waves raises its priority for its GEMMs, and how many item
+four waves), persistent workgroups per compute unit, whether waves
+raise their priority for their matrix phases, and how many item
 ranges each workgroup takes in turn when several share a compute unit.  Each
 candidate is a fresh context over the same device tensors; its fused-kernel
 time is measured with HIP events tied to the kernel's dispatch
