@@ -395,13 +395,13 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   // tile shape: 32-point collocation tiles when they fit in LDS with at
   // least the occupancy of 16-point tiles, unless fixed by the caller
   //
-  // Two workgroups of four waves per compute unit in place of one of up to
-  // eight, where both fit (step_halves) and there are tiles for them: a wave then owns two row
-  // blocks, reads the LDS stack half as often, and one workgroup's vector phases overlap the
-  // other's products.  Each holds a stash and a slab, and above the 256 MB of the last-level cache
-  // for all of them the step slows down: gradient of 3D 5x96, 20,000 points (200 MB)
-  // 0.36 -> 0.31 ms, 2D 8x80, 100,000 points (230 MB) 1.65 -> 1.47 ms; 2D 8x100 (380 MB) 2.34
-  // -> 2.59 ms.  A caller's blocks_per_cu = 1 keeps the one workgroup.
+  // Two workgroups of four waves per compute unit in place of one (step_halves)
+  // where there are tiles for both: a wave then owns up to two row blocks, reads the
+  // LDS stack half as often, and one workgroup's vector phases overlap the other's products.
+  // Steps: 2D 6x72 sin, 100,000 points 1.29 -> 1.07 ms, 2D 8x80, 6,000 points 0.216 -> 0.145, 3D 5x96,
+  // 20,000 points 0.36 -> 0.31, 2D 5x96, 100,000 points 1.10 -> 1.04.  Each workgroup holds a stash and a
+  // slab; where all of them exceed the 256 MB of the last-level cache the gain is lost (2D 8x96,
+  // 283 MB: 1.90 -> 1.94 ms).  A caller's blocks_per_cu = 1 keeps the one workgroup.
   if (step_halves(sh) && cfg->tile_points != 32 && cfg->blocks_per_cu != 1) {
     std::vector<Item> tiles;
     for (int s = 0; s < c->n_sub; ++s) tiles_of(c->subs[s], s, 16, step_value_points(sh.dim, 16), tiles);

@@ -586,10 +586,13 @@ static const void* split_exchange_any(int dim, int act, int NW) {
   return dim == 2 ? split_exchange_ptr<2>(act, NW) : split_exchange_ptr<3>(act, NW);
 }
 
-// Five to eight row blocks whose stack fits in the LDS twice: the step can run two
-// workgroups of four waves per compute unit in place of one of eight.
+// Five or six row blocks, whose stack fits in the LDS twice: the step can run two
+// workgroups of four waves per compute unit in place of one of five or six waves,
+// which leaves SIMDs with a single wave.  With seven or eight (2D; 3D does not fit) the two ways are
+// within 1 % (2D 8x128 at 4 layers, 100,000 points: 1.20 and 1.21 ms per step) or the one is faster
+// (2D 2x112, 50,000 points: 0.25 against 0.26 ms).
 bool step_halves(const Shape& sh) {
-  return sh.s3 && sh.NW > 4 && sh.NW <= kMaxWaves && 2 * split_step_lds(sh.D, sh.NW, 2 * sh.dim + 2).total <= kLdsBytes;
+  return sh.s3 && sh.NW > 4 && sh.NW <= 6 && 2 * split_step_lds(sh.D, sh.NW, 2 * sh.dim + 2).total <= kLdsBytes;
 }
 
 int step_lds_floats(const Shape& sh, int tile_points) {

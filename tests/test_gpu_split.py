@@ -68,10 +68,12 @@ def test_split_kernels_against_oracle(orc, dim, W, H, act, npde):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dim,W,H,act", [(3, 96, 3, "tanh"), (2, 80, 2, "sin"), (2, 112, 2, "tanh"), (2, 128, 2, "sin")])
-def test_two_workgroups_per_compute_unit(orc, dim, W, H, act):
-    """Five to eight row blocks and more tiles than compute units: workgroups of four
-    waves, one to four of which own two row blocks (and hand on the dW of some)."""
+@pytest.mark.parametrize("dim,W,H,act,waves", [(3, 96, 3, "tanh", 4), (2, 80, 2, "sin", 4), (3, 65, 2, "sin", 4),
+                                               (2, 96, 2, "tanh", 4), (2, 97, 2, "tanh", 7)])
+def test_two_workgroups_per_compute_unit(orc, dim, W, H, act, waves):
+    """Five or six row blocks and more tiles than compute units: workgroups of four
+    waves, one or two of which own two row blocks and hand on the dW of the second;
+    seven row blocks: one workgroup of seven waves."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2602_15883_amd as P
@@ -82,7 +84,7 @@ def test_two_workgroups_per_compute_unit(orc, dim, W, H, act):
         pb.activation = act
         tol = 16 * H * np.sqrt(W + 16) * 2.0 ** -24 * 4
         Lr, gr = oracle_loss_grad(orc, pb)
-        for per_cu, threads in ((0, 256), (1, 64 * ((W + 15) // 16))):
+        for per_cu, threads in ((0, 64 * waves), (1, 64 * ((W + 15) // 16))):
             ctx = P.context_from_problem(pb, device="cuda", blocks_per_cu=per_cu)
             try:
                 assert ctx.launch_info()["threads"] == threads
