@@ -111,7 +111,8 @@ typedef struct {
                              1 = all at one priority throughout */
   int32_t ranges_per_wg;  /* launch knob: item ranges per persistent
                              workgroup when several workgroups share a
-                             compute unit (taken in turn); 0 = 4, 1..64     */
+                             compute unit (taken in turn), 1..64; 0 = the
+                             library's choice (one)                         */
   int32_t guard_bytes;    /* memory-check mode: 0 = off; else a multiple of
                              256 up to 1 MiB left after every region of the
                              workspace and filled with a pattern at create;

@@ -467,11 +467,13 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   const int max_wg = c->num_cu * c->step_occ;
   c->n_wg = std::max(1, std::min(c->n_items, max_wg));
   // With several workgroups per compute unit the co-resident ones advance at
-  // different rates; ranges handed out in turn (four per workgroup unless the
-  // caller's tuning says otherwise) even it out.
+  // different rates; ranges handed out in turn can even it out (a caller's tuning).  The default is one
+  // per workgroup: each range has its own slab to be written and summed, and
+  // the two workgroups of a compute unit end within a tile of each other.  Steps with four
+  // ranges and with one: 2D 4x32, 200,000 points 0.386 and 0.337 ms, 2D 8x64 sin, 20,000 points 0.255 and 0.240,
+  // 3D 6x64, 50,000 points 0.447 and 0.435, 16 x 2D 6x64 6.00 and 5.97.
   c->dynamic = c->step_occ > 1;
-  // (one for the halves: a range has its own slab to be summed, 2D 8x80 1.41 against 1.58 ms per step with four)
-  const int rpw = cfg->ranges_per_wg > 0 ? cfg->ranges_per_wg : (sh.NWS < sh.NWV ? 1 : 4);
+  const int rpw = cfg->ranges_per_wg > 0 ? cfg->ranges_per_wg : 1;
   auto ranges_for = [&](int n_items, int n_wg) {
     return c->dynamic ? std::max(1, std::min(n_items, rpw * n_wg)) : n_wg;
   };
@@ -848,8 +850,13 @@ pinn_status pinn_query(pinn_ctx* c, const float* x, int64_t n, int32_t sub, uint
   qa.lds_floats = c->qlds_floats;
   const int CF = 2 * sh.dim + 2;
   // requests too small to fill the chip take 16-point tiles: a tile's chain of
-  // layers is the latency, and smaller tiles shorten it
-  const bool small = what <= PINN_Q_UVPW && n <= 16LL * c->num_cu * c->query_occ_small[what];
+  // layers is the latency, and smaller tiles shorten it.  They stay ahead for a few rounds of
+  // the compute units: values (one column block instead of 2 dim + 2) for five (3D 3x116, 16,000
+  // points 12.2 us against 17.4 us with full tiles, 32,000 22.0 against 18.2; 2D 8x100 25.6 and 34.2 us,
+  // 24,000 points 37 and 35), uvpw (three column blocks instead of six) for three (2D 8x100, 12,000 points
+  // 29.8 and 32.0 us, 16,000 38.7 and 33.4)
+  const int64_t rounds = what == PINN_Q_VALUE ? 5 : 3;
+  const bool small = what <= PINN_Q_UVPW && n <= 16 * std::max<int64_t>(rounds, c->query_occ_small[what]) * c->num_cu;
   qa.small = small ? 1 : 0;
   if (small) qa.lds_floats = c->qlds_small_floats;
   const int npts = small ? 16 : (what == PINN_Q_VALUE) ? 16 * CF : (what == PINN_Q_UVPW ? 16 * CF / (sh.dim + 1) : 16);
