@@ -202,6 +202,7 @@ struct pinn_ctx {
   int step_occ = 1;
   int query_occ[4] = {1, 1, 1, 1};   // resident query workgroups per compute unit, by query kind
   int qlds_small_floats = 0;         // LDS of the small-tile query (value and gradient modes)
+  int query_occ_small2 = 0;          // of the small-tile value query with fewer registers (0: not used)
   int query_occ_small[2] = {1, 1};   // its resident workgroups per compute unit (value, gradient)
   int exch_occ = 1;
   // grouped launch: n_wg workgroups over n_ranges item ranges (taken in
@@ -453,6 +454,9 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
                                                           (size_t)c->qlds_small_floats * 4));
     c->query_occ_small[q] = std::max(1, nb);
   }
+  if (sh.s3 && sh.NW <= kMaxWaves)
+    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->query_occ_small2, query_kernel_ptr(sh, PINN_Q_VALUE, 2), qthreads,
+                                                          (size_t)c->qlds_small_floats * 4));
   {
     int nb = 0;
     HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, exchange_kernel_ptr(sh), qthreads,
@@ -851,16 +855,19 @@ pinn_status pinn_query(pinn_ctx* c, const float* x, int64_t n, int32_t sub, uint
   const int CF = 2 * sh.dim + 2;
   // requests too small to fill the chip take 16-point tiles: a tile's chain of
   // layers is the latency, and smaller tiles shorten it.  They stay ahead for a few rounds of
-  // the compute units: values (one column block instead of 2 dim + 2) for five (3D 3x116, 16,000
-  // points 12.2 us against 17.4 us with full tiles, 32,000 22.0 against 18.2; 2D 8x100 25.6 and 34.2 us,
-  // 24,000 points 37 and 35), uvpw (three column blocks instead of six) for three (2D 8x100, 12,000 points
-  // 29.8 and 32.0 us, 16,000 38.7 and 33.4)
-  const int64_t rounds = what == PINN_Q_VALUE ? 5 : 3;
+  // the compute units: values (one column block instead of 2 dim + 2) for eight (2D 8x100, 20,000
+  // points 19 us against 34 with full tiles; 3D 6x200 sin, 32,000 points 60 and 83), uvpw (three
+  // column blocks instead of six) for three (2D 8x100, 12,000 points 29.8 and 32.0 us, 16,000 38.7 and 33.4)
+  const int64_t rounds = what == PINN_Q_VALUE ? 8 : 3;
   const bool small = what <= PINN_Q_UVPW && n <= 16 * std::max<int64_t>(rounds, c->query_occ_small[what]) * c->num_cu;
-  qa.small = small ? 1 : 0;
+  // values with more tiles than compute units: the kernel of half the registers, of which
+  // more workgroups are resident (2D 8x100, 16,000 points 15.3 us, 25.6 with the other; 2D 5x80 8.4 and
+  // 17.6 at 20,000; at one tile per compute unit the other is ahead, 34.4 against 37.3 us for 450 routed points)
+  const bool lean = small && what == PINN_Q_VALUE && c->query_occ_small2 > c->query_occ_small[0] && n > 16LL * c->num_cu;
+  qa.small = lean ? 2 : small ? 1 : 0;
   if (small) qa.lds_floats = c->qlds_small_floats;
   const int npts = small ? 16 : (what == PINN_Q_VALUE) ? 16 * CF : (what == PINN_Q_UVPW ? 16 * CF / (sh.dim + 1) : 16);
-  const int max_wg = c->num_cu * (small ? c->query_occ_small[what] : c->query_occ[what]);
+  const int max_wg = c->num_cu * (lean ? c->query_occ_small2 : small ? c->query_occ_small[what] : c->query_occ[what]);
   if (sub >= 0) {
     const int64_t tiles = (n + npts - 1) / npts;
     HIPCHECK(launch_query(qa, (int)std::min<int64_t>(tiles, max_wg), s));

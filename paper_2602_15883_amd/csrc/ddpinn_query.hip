@@ -91,7 +91,7 @@ __device__ __forceinline__ void split_forward_small(const Shape& sh, const float
 }
 
 // WIDE: above 128 neurons (eight waves, some with two row blocks)
-template <int DIM, int NCB, int MODE, int ACT, int WIDE>
+template <int DIM, int NCB, int MODE, int ACT, int WIDE, bool AHEAD = true>
 __device__ __forceinline__ void split_forward_any(const Shape& sh, const float* fr, char* lds, const SplitQueryLds& L,
                                                   int w, int lane, int tid, int nthr) {
   if constexpr (WIDE) {
@@ -99,7 +99,7 @@ __device__ __forceinline__ void split_forward_any(const Shape& sh, const float* 
     if (split_rb0(w + 1, sh.NW, sh.NWV) - rb0 == 2)
       split_forward<DIM, NCB, MODE, ACT, 2>(sh, fr, lds, L, rb0, w, lane, tid, nthr);
     else split_forward<DIM, NCB, MODE, ACT, 1>(sh, fr, lds, L, rb0, w, lane, tid, nthr);
-  } else if constexpr (NCB <= 3) {
+  } else if constexpr (NCB <= 3 && AHEAD) {
     split_forward_small<DIM, NCB, MODE, ACT>(sh, fr, lds, L, w, lane, tid, nthr);
   } else {
     split_forward<DIM, NCB, MODE, ACT, 1>(sh, fr, lds, L, w, w, lane, tid, nthr);
@@ -113,8 +113,10 @@ __device__ __forceinline__ void split_forward_any(const Shape& sh, const float* 
 // The others run four waves per SIMD and are bound by the matrix units, whose products the other
 // waves' activations and splits overlap: uvpw at 200,000 points, 16 networks 2D 8x100, 606 us with routing
 // (products 229 at the rate of a large bf16 product); fp32 matrix instructions 1,026.
+// SMALL = 2 (values): the same tiles with the weights fetched as they are needed, in half the
+// registers, for requests that fill more of the chip.
 template <int DIM, int MODE, int ACT, int SMALL, int WIDE>
-__global__ __launch_bounds__(512, WIDE || SMALL ? 2 : 4) void split_query_kernel(const QueryArgs a) {
+__global__ __launch_bounds__(512, WIDE || SMALL == 1 ? 2 : 4) void split_query_kernel(const QueryArgs a) {
   constexpr int D = DIM + 1, CF = 2 * DIM + 2;
   constexpr int CMODE = MODE == M_VALUE ? 1 : (MODE == M_GRAD ? DIM + 1 : CF);
   constexpr int NCB = SMALL ? CMODE : CF;
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(512, WIDE || SMALL ? 2 : 4) void split_query_kernel
       xin[k] = pidx[pt] >= 0 ? a.x[(size_t)pidx[pt] * D + (k - pt * D)] : 0.f;
     }
     __syncthreads();
-    split_forward_any<DIM, NCB, MODE, ACT, WIDE>(sh, a.subs[sub].frag, qlds, L, w, lane, tid, nthr);
+    split_forward_any<DIM, NCB, MODE, ACT, WIDE, SMALL != 2>(sh, a.subs[sub].frag, qlds, L, w, lane, tid, nthr);
     for (int k = tid; k < NPTS; k += nthr) {
       if (pidx[k] < 0) continue;
       const int64_t q = pidx[k];
@@ -255,6 +257,9 @@ static const void* ptr_act(int act) {
 }
 template <int DIM, int WIDE>
 static const void* ptr_mode(int mode, int act, int small) {
+  if constexpr (!WIDE) {
+    if (mode == M_VALUE && small == 2) return ptr_act<DIM, M_VALUE, 2, WIDE>(act);
+  }
   if (mode == M_VALUE) return small ? ptr_act<DIM, M_VALUE, 1, WIDE>(act) : ptr_act<DIM, M_VALUE, 0, WIDE>(act);
   if (mode == M_GRAD) {
     // only 2D has a gradient-mode query (u, v, p, omega)

@@ -98,6 +98,32 @@ def test_two_workgroups_per_compute_unit(orc, dim, W, H, act, waves):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dim,W,H,act", [(2, 16, 2, "tanh"), (2, 80, 3, "sin"), (3, 112, 3, "tanh"), (2, 128, 2, "sin"),
+                                         (3, 144, 2, "tanh")])
+@pytest.mark.parametrize("n", [4097, 8191, 16401, 32769])
+def test_value_queries_by_size(orc, dim, W, H, act, n):
+    """One tile per compute unit and more: the value kernels of small tiles, of half
+    the registers, and of full tiles."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2602_15883_amd as P
+    print(f"values dim={dim} W={W} n={n}", flush=True)
+    orc.set_activation(act)
+    try:
+        pb = wl.tiny(dim=dim, width=W, depth=H, n_pde=n, n_obs=5, n_gh=0, n_anc=1, seed=W)
+        pb.activation = act
+        x = np.ascontiguousarray(pb.subs[0].pde_x)
+        ctx = P.context_from_problem(pb, device="cuda")
+        try:
+            got = ctx.query(torch.from_numpy(x).cuda(), sub=0, what="value").cpu().numpy()
+        finally:
+            ctx.close()
+        assert_close(got, orc.channels(dim, W, H, pb.subs[0].theta, x)[:, 0], 1e-5, "value")
+    finally:
+        orc.set_activation("tanh")
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("dim,W,H,act,clip", [(2, 50, 3, "tanh", 0.0), (3, 17, 2, "sin", 1e-3), (2, 112, 1, "tanh", 0.0),
                                               (2, 150, 2, "sin", 0.5), (3, 200, 2, "tanh", 0.0), (3, 240, 2, "tanh", 1.0)])
 def test_adam_leaves_the_weight_copies_current(dim, W, H, act, clip):
