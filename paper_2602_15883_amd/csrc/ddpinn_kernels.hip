@@ -31,7 +31,9 @@ __global__ void prep_kernel(const PrepArgs a) {
   const Shape& sh = a.sh;
   const int s = blockIdx.y;
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s == 0 && idx < a.n_counters) a.counters[idx] = 0;
+  // (strided: one counter per subdomain can be more than the threads of a small network's copies)
+  if (s == 0)
+    for (int64_t k = idx; k < a.n_counters; k += (int64_t)gridDim.x * blockDim.x) a.counters[k] = 0;
   const float* th = a.subs[s].theta;
   float* fr = a.subs[s].frag;
   const int W = sh.W, Wp = sh.Wp, D = sh.D, H = sh.H;
