@@ -203,6 +203,8 @@ struct pinn_ctx {
   int query_occ[4] = {1, 1, 1, 1};   // resident query workgroups per compute unit, by query kind
   int qlds_small_floats = 0;         // LDS of the small-tile query (value and gradient modes)
   int query_occ_small2 = 0;          // of the small-tile value query with fewer registers (0: not used)
+  int qlds_one_floats = 0;           // LDS and resident workgroups of full tiles in one wave (two row blocks)
+  int query_occ_one[4] = {0, 0, 0, 0};
   int query_occ_small[2] = {1, 1};   // its resident workgroups per compute unit (value, gradient)
   int exch_occ = 1;
   // grouped launch: n_wg workgroups over n_ranges item ranges (taken in
@@ -454,9 +456,15 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
                                                           (size_t)c->qlds_small_floats * 4));
     c->query_occ_small[q] = std::max(1, nb);
   }
-  if (sh.s3 && sh.NW <= kMaxWaves)
+  if (sh.s3 && sh.NW > 1 && sh.NW <= kMaxWaves)
     HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->query_occ_small2, query_kernel_ptr(sh, PINN_Q_VALUE, 2), qthreads,
                                                           (size_t)c->qlds_small_floats * 4));
+  if (sh.NW == 2) {
+    c->qlds_one_floats = query_lds_floats(sh, 3);
+    for (int q = 0; q < 4; ++q)
+      HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->query_occ_one[q], query_kernel_ptr(sh, q, 3), 64,
+                                                            (size_t)c->qlds_one_floats * 4));
+  }
   {
     int nb = 0;
     HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, exchange_kernel_ptr(sh), qthreads,
@@ -854,20 +862,29 @@ pinn_status pinn_query(pinn_ctx* c, const float* x, int64_t n, int32_t sub, uint
   qa.lds_floats = c->qlds_floats;
   const int CF = 2 * sh.dim + 2;
   // requests too small to fill the chip take 16-point tiles: a tile's chain of
-  // layers is the latency, and smaller tiles shorten it.  They stay ahead for a few rounds of
-  // the compute units: values (one column block instead of 2 dim + 2) for eight (2D 8x100, 20,000
-  // points 19 us against 34 with full tiles; 3D 6x200 sin, 32,000 points 60 and 83), uvpw (three
-  // column blocks instead of six) for three (2D 8x100, 12,000 points 29.8 and 32.0 us, 16,000 38.7 and 33.4)
-  const int64_t rounds = what == PINN_Q_VALUE ? 8 : 3;
-  const bool small = what <= PINN_Q_UVPW && n <= 16 * std::max<int64_t>(rounds, c->query_occ_small[what]) * c->num_cu;
-  // values with more tiles than compute units: the kernel of half the registers, of which
-  // more workgroups are resident (2D 8x100, 16,000 points 15.3 us, 25.6 with the other; 2D 5x80 8.4 and
-  // 17.6 at 20,000; at one tile per compute unit the other is ahead, 34.4 against 37.3 us for 450 routed points)
-  const bool lean = small && what == PINN_Q_VALUE && c->query_occ_small2 > c->query_occ_small[0] && n > 16LL * c->num_cu;
-  qa.small = lean ? 2 : small ? 1 : 0;
-  if (small) qa.lds_floats = c->qlds_small_floats;
+  // layers is the latency, and smaller tiles shorten it.  They stay ahead for a few times what the
+  // compute units hold.  Values (one column block instead of 2 dim + 2): up to 64 waves per
+  // compute unit (2D 6x128: 34,000 points 60 us against 61 with full tiles, 50,000 points 83 and 66; 2D 6x32:
+  // 125,000 points 28 and 39, 200,000 43 and 39); uvpw (three column blocks instead of six): up to
+  // two and a half times the resident workgroups, at least three per compute unit (2D 6x32: 34,000 points
+  // 18.4 and 21.0, 60,000 29.3 and 25.0; 2D 6x128: 12,000 points 44 and 50, 16,000 58 and 54).  One row block: see split_forward_alone
+  // (2D 6x16: 300,000 values 25 and 35)
+  const int64_t rounds = what == PINN_Q_VALUE ? (sh.NW == 1 ? 128 : 64 / sh.NWV)
+                       : what == PINN_Q_UVPW ? std::max(3, 5 * c->query_occ_small[1] / 2) : 0;
+  const bool small = n <= 16 * rounds * c->num_cu;
+  // values beyond two waves per SIMD: the kernel of half the registers, of which more workgroups are
+  // resident (2D 6x48, 16,000 points 9.0 us, 9.8 with the other, 4,500 points 11.6 and 10.9; 2D 6x80, 4,500 points
+  // 15.0 and 17.7; 450 routed points of 2D 8x100 37.3 and 34.4)
+  const bool lean = small && what == PINN_Q_VALUE && c->query_occ_small2 > c->query_occ_small[0] &&
+                    n > 16LL * std::max(1, kMaxWaves / sh.NWV) * c->num_cu;
   const int npts = small ? 16 : (what == PINN_Q_VALUE) ? 16 * CF : (what == PINN_Q_UVPW ? 16 * CF / (sh.dim + 1) : 16);
-  const int max_wg = c->num_cu * (lean ? c->query_occ_small2 : small ? c->query_occ_small[what] : c->query_occ[what]);
+  // full tiles of two row blocks: one wave each, with a longer chain and less LDS, once there are
+  // one and a half times the tiles that two-wave workgroups hold (2D 6x24 uvpw: 70,000 points 25.3 us with two
+  // waves, 35 with one, 125,000 points 42 and 36)
+  const bool one = !small && c->query_occ_one[what] > 0 && 2 * ((n + npts - 1) / npts) > 3LL * c->query_occ[what] * c->num_cu;
+  qa.small = lean ? 2 : small ? 1 : one ? 3 : 0;
+  if (small || one) qa.lds_floats = small ? c->qlds_small_floats : c->qlds_one_floats;
+  const int max_wg = c->num_cu * (lean ? c->query_occ_small2 : small ? c->query_occ_small[what] : one ? c->query_occ_one[what] : c->query_occ[what]);
   if (sub >= 0) {
     const int64_t tiles = (n + npts - 1) / npts;
     HIPCHECK(launch_query(qa, (int)std::min<int64_t>(tiles, max_wg), s));

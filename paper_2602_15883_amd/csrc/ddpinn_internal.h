@@ -146,7 +146,8 @@ struct QueryArgs {
   int32_t what;
   float nu;
   int32_t lds_floats;
-  int32_t small;            // one 16-point block per channel (value and gradient modes)
+  int32_t small;            // tile: 0 full, 1 one 16-point block per channel (value and gradient modes),
+                            // 2 the same in half the registers (values), 3 full in one wave (two row blocks)
 };
 
 struct RouteArgs {
@@ -239,7 +240,7 @@ bool step_halves(const Shape& sh);
 
 // Kernel entry points and their LDS needs (for graph nodes and occupancy).
 const void* step_kernel_ptr(const Shape& sh, int tile_points);
-const void* query_kernel_ptr(const Shape& sh, int what, int small = 0);   // what: Q_VALUE, Q_UVPW, Q_CHANNELS/Q_RESIDUAL
+const void* query_kernel_ptr(const Shape& sh, int what, int small = 0);   // what: Q_VALUE, Q_UVPW, Q_CHANNELS/Q_RESIDUAL; small: QueryArgs::small
 const void* exchange_kernel_ptr(const Shape& sh);
 const void* prep_kernel_ptr();
 const void* reduce_kernel_ptr();
@@ -248,6 +249,7 @@ int reduce_blocks(const Shape& sh);
 void grid_clip_adam(const ReduceArgs& a, dim3* grid, dim3* block);
 int step_lds_floats(const Shape& sh, int tile_points);
 int query_lds_floats(const Shape& sh, int small = 0);
+int query_waves(const Shape& sh, int small);   // waves per workgroup of a tile kind (QueryArgs::small)
 int step_value_points(int dim, int tile_points);
 void grid_prep(const PrepArgs& a, dim3* grid, dim3* block);
 void grid_reduce(const ReduceArgs& a, dim3* grid, dim3* block);

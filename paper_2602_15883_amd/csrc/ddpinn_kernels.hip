@@ -574,7 +574,7 @@ constexpr int kLdsBytes = 160 * 1024;
 // 2,000 points: 69 against 47 us).
 bool split_fits(int dim, int NW) {
   const int NCB = 2 * dim + 2;
-  return std::max(split_query_lds(dim + 1, NW, std::min(NW, 8), NCB).total, split_step_lds(dim + 1, NW, NCB).total) <= kLdsBytes;
+  return std::max(split_query_lds(dim + 1, NW, std::min(NW, 8), NCB, false).total, split_step_lds(dim + 1, NW, NCB).total) <= kLdsBytes;
 }
 
 static const void* split_step_any(int dim, int tile_points, int act, int NW, int NWS) {
@@ -602,8 +602,11 @@ int step_lds_floats(const Shape& sh, int tile_points) {
   return wide_step_lds_floats(sh);
 }
 
+int query_waves(const Shape& sh, int small) { return small == 3 ? 1 : sh.NWV; }
+
 int query_lds_floats(const Shape& sh, int small) {
-  if (sh.s3) return split_query_lds(sh.D, sh.NW, sh.NWV, small ? sh.dim + 1 : 2 * sh.dim + 2).total / 4;
+  if (sh.s3)
+    return split_query_lds(sh.D, sh.NW, sh.NWV, small == 1 || small == 2 ? sh.dim + 1 : 2 * sh.dim + 2, query_waves(sh, small) == 1).total / 4;
   return wide_query_lds_floats(sh, small);
 }
 
@@ -701,7 +704,7 @@ const void* exchange_kernel_ptr(const Shape& sh) {
 hipError_t launch_query(const QueryArgs& a, int n_wg, hipStream_t s) {
   if (n_wg >= 16) n_wg &= ~7;   // a multiple of the XCD count (see query_kernel)
   const size_t lds = (size_t)a.lds_floats * sizeof(float);
-  const dim3 block(a.sh.NWV * 64);
+  const dim3 block(query_waves(a.sh, a.small) * 64);
   void* args[] = {const_cast<QueryArgs*>(&a)};
   return hipLaunchKernel(query_kernel_ptr(a.sh, a.what, a.small), dim3(n_wg), block, args, lds, s);
 }

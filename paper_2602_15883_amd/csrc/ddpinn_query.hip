@@ -48,12 +48,13 @@ __device__ __forceinline__ void split_forward(const Shape& sh, const float* fr, 
 
 // Up to 128 neurons and one column block per channel (SMALL): the weight
 // fragments and the bias of the next layer are requested before the current one's
-// products, so that a layer's chain holds no fetch from L2 or beyond.
-template <int DIM, int NCB, int MODE, int ACT>
+// products, so that a layer's chain holds no fetch from L2 or beyond.  NKB: K blocks held
+// (all four for every network, the copies of unused ones cost 2D 6x48, 4,000 points 12.7 us against 10.9).
+template <int DIM, int NCB, int MODE, int ACT, int NKB>
 __device__ __forceinline__ void split_forward_small(const Shape& sh, const float* fr, char* lds, const SplitQueryLds& L,
                                                     int w, int lane, int tid, int nthr) {
   using M = ModeCfg<DIM, NCB, MODE>;
-  constexpr int D = DIM + 1, NKB = kMaxWaves / 2;
+  constexpr int D = DIM + 1;
   const int g = lane >> 4, j = lane & 15, Wp = sh.Wp, NW = sh.NW, KB = (NW + 1) >> 1, H = sh.H;
   const LaneSlots ls = lane_slots(lane);
   const uint32_t lane16 = (uint32_t)lane * 16u;
@@ -90,17 +91,131 @@ __device__ __forceinline__ void split_forward_small(const Shape& sh, const float
   __syncthreads();
 }
 
-// WIDE: above 128 neurons (eight waves, some with two row blocks)
-template <int DIM, int NCB, int MODE, int ACT, int WIDE, bool AHEAD = true>
+// One or two row blocks, in one wave: a layer's result is, split, the operand of the next
+// layer's products as it lies in the wave's registers (lane (g, j): neurons 4g + i of each block,
+// column j), so that nothing goes through LDS and no wave waits for another.  With two, lane
+// groups 1 and 2 hold the second block first (k_neuron's order: the weight rows are taken so).
+// One block: through the stack, a wave has too few products to cover it (2D 6x16, 4,000 points: uvpw
+// 14.9 us, 8.5 so, fp32 matrix instructions 11.7; values 10.2, 6.8, 8.1).  Two blocks, full tiles: the stacks
+// of 3D tiles fill the LDS at 10 waves per compute unit (3D 6x17: residuals of 300,000 points 310 us, 183
+// so, 254 on fp32 matrix instructions; 1,000,000 values 232, 153, 197).
+template <int DIM, int NCB, int MODE, int ACT, int R>
+__device__ __forceinline__ void split_forward_alone(const Shape& sh, const float* fr, char* lds, const SplitQueryLds& L,
+                                                    int lane, int tid, int nthr) {
+  using M = ModeCfg<DIM, NCB, MODE>;
+  constexpr int D = DIM + 1;
+  const int g = lane >> 4, j = lane & 15, H = sh.H, Wp = 16 * R;
+  const int flip = R == 2 ? slot_half(g) : 0;              // block r of the lane's results is r ^ flip
+  // byte offset of the weight row that the lane fetches for block r
+  uint32_t row[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    row[r] = (uint32_t)lane * 16u + (R == 2 ? (uint32_t)(r ^ slot_half(j >> 2)) * 12u * kFragFloats : 0u);
+  const float* xin = reinterpret_cast<const float*>(lds + L.xin);
+  const float* wf = fr + sh.f_hid3;
+  const float* bf = fr + sh.f_b + 4 * g;
+  v4f acc[R][NCB], bias[R];
+  Frags<R> f;   // of the next layer
+  auto load = [&](int l) {
+    const float* wl = wf + (size_t)(l - 2) * sh.hid3_layer;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) f.a[r][p] = ldg4u(wl + p * kFragFloats, row[r]);
+      bias[r] = ldg4(bf + (size_t)(l - 1) * Wp + 16 * (r ^ flip));
+    }
+  };
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    input_layer<DIM, NCB, MODE>(acc[r], fr + sh.f_w1, fr + sh.f_b, xin, r ^ flip, g, j);
+  if (H > 1) load(2);
+#pragma unroll
+  for (int r = 0; r < R; ++r) act_forward<DIM, NCB, MODE, ACT>(acc[r]);
+  for (int l = 2; l <= H; ++l) {
+    const Frags<R> a = f;
+    v4f b[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) b[r] = bias[r];
+    if (l < H) load(l + 1);
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+      v2u h[R][3];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        split4(acc[r][cb], h[r]);
+        acc[r][cb] = zero4();
+      }
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          if constexpr (R == 2) {
+            typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+            const v4u u = __builtin_shufflevector(h[0][kPartB[q]], h[1][kPartB[q]], 0, 1, 2, 3);
+            acc[r][cb] = mfma32(__builtin_bit_cast(v8h, a.a[r][kPartA[q]]), __builtin_bit_cast(v8h, u), acc[r][cb]);
+          } else {
+            const v8s a8 = __builtin_bit_cast(v8s, a.a[r][kPartA[q]]);
+            acc[r][cb] = mfma16(__builtin_shufflevector(a8, a8, 0, 1, 2, 3), __builtin_bit_cast(v4s, h[r][kPartB[q]]), acc[r][cb]);
+          }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+      for (int pb = 0; pb < M::NPB; ++pb) acc[r][pb] += b[r];
+      act_forward<DIM, NCB, MODE, ACT>(acc[r]);
+    }
+  }
+  // output layer: each block's sum on its own and over the lane groups in the order in which
+  // output_partials and output_sum take them, so that a point's result is the same in every tile
+  float* ys = reinterpret_cast<float*>(lds + L.ys);
+#pragma unroll
+  for (int o = 0; o < D; ++o) {
+    v4f wo[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) wo[r] = ldg4(fr + sh.f_wo + o * Wp + 16 * (r ^ flip) + 4 * g);
+    const float bo = ldg(fr + sh.f_bo + o);
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+      float t[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        t[r] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[r] = fmaf(wo[r][i], acc[r][cb][i], t[r]);
+      }
+      float y = group_sum(R == 2 && flip ? t[R - 1] : t[0]);
+      if constexpr (R == 2) y += group_sum(flip ? t[0] : t[1]);
+      if (cb < M::NPB) y += bo;
+      if (g == 0) ys[(o * NCB + cb) * 16 + j] = y;
+    }
+  }
+  __syncthreads();
+}
+
+// How the waves share the row blocks: one each; above 128 neurons eight waves, some with two;
+// one wave with one block, or two, in all.  (Instances of their own: a branch on the last ones in the first costs its
+// registers, 3D 6x100, 300,000 values 313 -> 321 us.)
+enum : int { ROWS_EACH = 0, ROWS_WIDE = 1, ROWS_ONE = 2, ROWS_TWO = 3 };
+constexpr bool rows_alone(int rows) { return rows == ROWS_ONE || rows == ROWS_TWO; }
+// waves per SIMD that the registers have to leave room for
+constexpr int waves_per_simd(int rows, int small) {
+  return rows == ROWS_WIDE || (rows == ROWS_EACH && small == 1) ? 2 : rows == ROWS_TWO ? 3 : 4;
+}
+template <int DIM, int NCB, int MODE, int ACT, int ROWS, bool AHEAD = true>
 __device__ __forceinline__ void split_forward_any(const Shape& sh, const float* fr, char* lds, const SplitQueryLds& L,
                                                   int w, int lane, int tid, int nthr) {
-  if constexpr (WIDE) {
+  if constexpr (rows_alone(ROWS)) {
+    split_forward_alone<DIM, NCB, MODE, ACT, ROWS == ROWS_TWO ? 2 : 1>(sh, fr, lds, L, lane, tid, nthr);
+  } else if constexpr (ROWS == ROWS_WIDE) {
     const int rb0 = split_rb0(w, sh.NW, sh.NWV);
     if (split_rb0(w + 1, sh.NW, sh.NWV) - rb0 == 2)
       split_forward<DIM, NCB, MODE, ACT, 2>(sh, fr, lds, L, rb0, w, lane, tid, nthr);
     else split_forward<DIM, NCB, MODE, ACT, 1>(sh, fr, lds, L, rb0, w, lane, tid, nthr);
   } else if constexpr (NCB <= 3 && AHEAD) {
-    split_forward_small<DIM, NCB, MODE, ACT>(sh, fr, lds, L, w, lane, tid, nthr);
+    if (sh.NW <= 2) split_forward_small<DIM, NCB, MODE, ACT, 1>(sh, fr, lds, L, w, lane, tid, nthr);
+    else if (sh.NW <= 4) split_forward_small<DIM, NCB, MODE, ACT, 2>(sh, fr, lds, L, w, lane, tid, nthr);
+    else split_forward_small<DIM, NCB, MODE, ACT, kMaxWaves / 2>(sh, fr, lds, L, w, lane, tid, nthr);
   } else {
     split_forward<DIM, NCB, MODE, ACT, 1>(sh, fr, lds, L, w, w, lane, tid, nthr);
   }
@@ -115,8 +230,9 @@ __device__ __forceinline__ void split_forward_any(const Shape& sh, const float* 
 // (products 229 at the rate of a large bf16 product); fp32 matrix instructions 1,026.
 // SMALL = 2 (values): the same tiles with the weights fetched as they are needed, in half the
 // registers, for requests that fill more of the chip.
-template <int DIM, int MODE, int ACT, int SMALL, int WIDE>
-__global__ __launch_bounds__(512, WIDE || SMALL == 1 ? 2 : 4) void split_query_kernel(const QueryArgs a) {
+template <int DIM, int MODE, int ACT, int SMALL, int ROWS>
+__global__ __launch_bounds__(rows_alone(ROWS) ? 64 : 512, waves_per_simd(ROWS, SMALL))
+void split_query_kernel(const QueryArgs a) {
   constexpr int D = DIM + 1, CF = 2 * DIM + 2;
   constexpr int CMODE = MODE == M_VALUE ? 1 : (MODE == M_GRAD ? DIM + 1 : CF);
   constexpr int NCB = SMALL ? CMODE : CF;
@@ -126,7 +242,7 @@ __global__ __launch_bounds__(512, WIDE || SMALL == 1 ? 2 : 4) void split_query_k
   const Shape& sh = a.sh;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const SplitQueryLds L = split_query_lds(D, sh.NW, sh.NWV, NCB);
+  const SplitQueryLds L = split_query_lds(D, sh.NW, sh.NWV, NCB, rows_alone(ROWS));
   const float* ys = reinterpret_cast<const float*>(qlds + L.ys);
   float* xin = reinterpret_cast<float*>(qlds + L.xin);
   int32_t* pidx = reinterpret_cast<int32_t*>(qlds + L.pidx);
@@ -169,7 +285,7 @@ __global__ __launch_bounds__(512, WIDE || SMALL == 1 ? 2 : 4) void split_query_k
       xin[k] = pidx[pt] >= 0 ? a.x[(size_t)pidx[pt] * D + (k - pt * D)] : 0.f;
     }
     __syncthreads();
-    split_forward_any<DIM, NCB, MODE, ACT, WIDE, SMALL != 2>(sh, a.subs[sub].frag, qlds, L, w, lane, tid, nthr);
+    split_forward_any<DIM, NCB, MODE, ACT, ROWS, SMALL != 2>(sh, a.subs[sub].frag, qlds, L, w, lane, tid, nthr);
     for (int k = tid; k < NPTS; k += nthr) {
       if (pidx[k] < 0) continue;
       const int64_t q = pidx[k];
@@ -205,14 +321,14 @@ __global__ __launch_bounds__(512, WIDE || SMALL == 1 ? 2 : 4) void split_query_k
 // tile per face or a few: a tile's chain of layers bounds it (48 faces of 2,000 points, 2D 6x64: 72
 // us on fp32 matrix instructions, 48 so; the products alone take 13).
 // ---------------------------------------------------------------------------
-template <int DIM, int ACT, int WIDE>
-__global__ __launch_bounds__(512, WIDE ? 2 : 4) void split_exchange_kernel(const ExchangeArgs a) {
+template <int DIM, int ACT, int ROWS>
+__global__ __launch_bounds__(ROWS == ROWS_ONE ? 64 : 512, waves_per_simd(ROWS, 0)) void split_exchange_kernel(const ExchangeArgs a) {
   constexpr int D = DIM + 1, CF = 2 * DIM + 2, NCB = CF, NCOL = 16 * NCB;
   extern __shared__ __align__(16) char qlds[];
   const Shape& sh = a.sh;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const SplitQueryLds L = split_query_lds(D, sh.NW, sh.NWV, NCB);
+  const SplitQueryLds L = split_query_lds(D, sh.NW, sh.NWV, NCB, rows_alone(ROWS));
   const float* ys = reinterpret_cast<const float*>(qlds + L.ys);
   float* xin = reinterpret_cast<float*>(qlds + L.xin);
   for (int t = blockIdx.x; t < a.n_items; t += gridDim.x) {
@@ -234,7 +350,7 @@ __global__ __launch_bounds__(512, WIDE ? 2 : 4) void split_exchange_kernel(const
       xin[k] = v;
     }
     __syncthreads();
-    split_forward_any<DIM, NCB, M_VALUE, ACT, WIDE>(sh, a.subs[it.b].frag, qlds, L, w, lane, tid, nthr);
+    split_forward_any<DIM, NCB, M_VALUE, ACT, ROWS>(sh, a.subs[it.b].frag, qlds, L, w, lane, tid, nthr);
     float* tg = a.targets[it.a];
     for (int k = tid; k < it.count; k += nthr) {
       for (int o = 0; o < D; ++o) {
@@ -250,32 +366,41 @@ __global__ __launch_bounds__(512, WIDE ? 2 : 4) void split_exchange_kernel(const
 // ---------------------------------------------------------------------------
 // instances: one dimension per translation unit
 // ---------------------------------------------------------------------------
-template <int DIM, int MODE, int SMALL, int WIDE>
+template <int DIM, int MODE, int SMALL, int ROWS>
 static const void* ptr_act(int act) {
-  return act == ACT_SIN ? (const void*)split_query_kernel<DIM, MODE, ACT_SIN, SMALL, WIDE>
-                        : (const void*)split_query_kernel<DIM, MODE, ACT_TANH, SMALL, WIDE>;
+  return act == ACT_SIN ? (const void*)split_query_kernel<DIM, MODE, ACT_SIN, SMALL, ROWS>
+                        : (const void*)split_query_kernel<DIM, MODE, ACT_TANH, SMALL, ROWS>;
 }
-template <int DIM, int WIDE>
+template <int DIM, int ROWS>
 static const void* ptr_mode(int mode, int act, int small) {
-  if constexpr (!WIDE) {
-    if (mode == M_VALUE && small == 2) return ptr_act<DIM, M_VALUE, 2, WIDE>(act);
+  if constexpr (ROWS == ROWS_EACH) {
+    if (mode == M_VALUE && small == 2) return ptr_act<DIM, M_VALUE, 2, ROWS>(act);
   }
-  if (mode == M_VALUE) return small ? ptr_act<DIM, M_VALUE, 1, WIDE>(act) : ptr_act<DIM, M_VALUE, 0, WIDE>(act);
-  if (mode == M_GRAD) {
-    // only 2D has a gradient-mode query (u, v, p, omega)
-    if constexpr (DIM == 2) return small ? ptr_act<DIM, M_GRAD, 1, WIDE>(act) : ptr_act<DIM, M_GRAD, 0, WIDE>(act);
+  if constexpr (ROWS != ROWS_TWO) {
+    if (mode == M_VALUE && small) return ptr_act<DIM, M_VALUE, 1, ROWS>(act);
+    if constexpr (DIM == 2)
+      if (mode == M_GRAD && small) return ptr_act<DIM, M_GRAD, 1, ROWS>(act);
   }
-  return ptr_act<DIM, M_PDE, 0, WIDE>(act);
+  if (mode == M_VALUE) return ptr_act<DIM, M_VALUE, 0, ROWS>(act);
+  // only 2D has a gradient-mode query (u, v, p, omega)
+  if constexpr (DIM == 2)
+    if (mode == M_GRAD) return ptr_act<DIM, M_GRAD, 0, ROWS>(act);
+  return ptr_act<DIM, M_PDE, 0, ROWS>(act);
 }
 template <int DIM>
 const void* split_query_ptr(int mode, int act, int small, int NW) {
-  return NW > kMaxWaves ? ptr_mode<DIM, 1>(mode, act, small) : ptr_mode<DIM, 0>(mode, act, small);
+  if (NW == 1) return ptr_mode<DIM, ROWS_ONE>(mode, act, small);
+  if (small == 3) return ptr_mode<DIM, ROWS_TWO>(mode, act, 0);   // (two row blocks)
+  return NW > kMaxWaves ? ptr_mode<DIM, ROWS_WIDE>(mode, act, small) : ptr_mode<DIM, ROWS_EACH>(mode, act, small);
+}
+template <int DIM, int ROWS>
+static const void* ptr_exchange(int act) {
+  return act == ACT_SIN ? (const void*)split_exchange_kernel<DIM, ACT_SIN, ROWS> : (const void*)split_exchange_kernel<DIM, ACT_TANH, ROWS>;
 }
 template <int DIM>
 const void* split_exchange_ptr(int act, int NW) {
-  const bool sin = act == ACT_SIN;
-  if (NW > kMaxWaves) return sin ? (const void*)split_exchange_kernel<DIM, ACT_SIN, 1> : (const void*)split_exchange_kernel<DIM, ACT_TANH, 1>;
-  return sin ? (const void*)split_exchange_kernel<DIM, ACT_SIN, 0> : (const void*)split_exchange_kernel<DIM, ACT_TANH, 0>;
+  if (NW == 1) return ptr_exchange<DIM, ROWS_ONE>(act);
+  return NW > kMaxWaves ? ptr_exchange<DIM, ROWS_WIDE>(act) : ptr_exchange<DIM, ROWS_EACH>(act);
 }
 template const void* split_query_ptr<DDP_DIM>(int, int, int, int);
 template const void* split_exchange_ptr<DDP_DIM>(int, int);

@@ -109,6 +109,13 @@ __device__ __forceinline__ v4f mfma16(v4s a, v4s b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
+// sum over the four lane groups, in every lane
+__device__ __forceinline__ float group_sum(float v) {
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  return v;
+}
+
 // parts of the two operands of the q-th product, smallest products first
 __device__ constexpr int kPartA[6] = {2, 0, 1, 1, 0, 0};
 __device__ constexpr int kPartB[6] = {0, 2, 1, 0, 1, 0};
@@ -357,14 +364,15 @@ __device__ __forceinline__ void output_sum(const float* part, int n_part, const 
 // LDS of a query workgroup, in bytes.  The activation stack also takes, once
 // the last hidden layer's products have read it, the output layer's partial
 // sums (at most 1 KiB per row block and column block) and the outputs ys behind them.
+// alone: one wave has all row blocks and needs neither stack nor partial sums.
 struct SplitQueryLds { int part_floats, stack, ys, xin, pidx, total; };
-__host__ __device__ inline SplitQueryLds split_query_lds(int D, int NW, int NWV, int NCB) {
+__host__ __device__ inline SplitQueryLds split_query_lds(int D, int NW, int NWV, int NCB, bool alone) {
   SplitQueryLds L;
   const int NCOL = 16 * NCB;
-  L.part_floats = 4 * NWV * D * NCOL;
+  L.part_floats = alone ? 0 : 4 * NWV * D * NCOL;
   L.stack = 0;
   L.ys = 4 * L.part_floats;
-  int o = NW * NCB * kUnits3;
+  int o = alone ? 4 * D * NCOL : NW * NCB * kUnits3;
   L.xin = o;  o += 4 * NCOL * D;
   L.pidx = o; o += 4 * NCOL;
   L.total = o;

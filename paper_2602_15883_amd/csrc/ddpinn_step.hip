@@ -38,13 +38,6 @@
 
 namespace ddp {
 
-// sum over the four lane groups, in every lane
-__device__ __forceinline__ float group_sum(float v) {
-  v += __shfl_xor(v, 16, 64);
-  v += __shfl_xor(v, 32, 64);
-  return v;
-}
-
 __device__ __forceinline__ v4s lds_read_tr(const char* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS v4s*)(const LDS_AS char*)p);
 }

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import workloads as wl
-from parity import rel_report
+from parity import assert_close, channel_tolerances, rel_report
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -47,3 +47,40 @@ def test_range_counters_of_many_subdomains(pkg, monkeypatch, dim, W, n_sub):
                 assert rel_report(gp[s], gg[s])[1] <= 64 * 2.0 ** -24, s
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("dim,W,act", [(2, 3, "tanh"), (2, 16, "sin"), (3, 16, "tanh"), (2, 17, "tanh"), (3, 24, "sin"),
+                                       (2, 32, "sin"), (3, 32, "tanh"), (2, 33, "tanh"), (3, 48, "tanh"), (2, 64, "tanh")])
+def test_small_networks_in_every_tile(pkg, orc, dim, W, act):
+    """Networks of one to four row blocks: sizes on both sides of every change of the
+    query's tile (16 points, the same in half the registers, full, full in one wave).
+    A point's result is bitwise the same in all of them, and the oracle's."""
+    H = 3
+    print(f"tiles dim={dim} W={W} act={act}", flush=True)
+    pb = wl.tiny(dim=dim, width=W, depth=H, n_pde=530_001, seed=W)
+    pb.activation = act
+    x = np.ascontiguousarray(pb.subs[0].pde_x)
+    pb.subs[0].pde_x = x[:50]
+    xt = torch.from_numpy(x).cuda()
+    orc.set_activation(act)
+    ctx = pkg.context_from_problem(pb, device="cuda")
+    try:
+        ref = orc.channels(dim, W, H, pb.subs[0].theta, x[:600])
+        whats = {"value": (1, 100, 4097, 17_000, 60_000, 140_000, 320_000), "residual": (16, 3001, 60_000)}
+        if dim == 2:
+            whats["uvpw"] = (1, 450, 13_000, 30_000, 45_001, 120_000)
+        for what, sizes in whats.items():
+            full = ctx.query(xt, sub=0, what=what)
+            assert bool(torch.isfinite(full).all()), what
+            for n in sizes:
+                assert torch.equal(ctx.query(xt[:n].contiguous(), sub=0, what=what), full[:n]), (what, n)
+            if what != "residual":
+                assert_close(full[:600, :dim + 1].cpu().numpy(), ref[:, 0], 1e-5, what)
+        ch = ctx.query(xt[:600].contiguous(), sub=0, what="channels").cpu().numpy().reshape(600, 2 * dim + 2, dim + 1)
+        for c, t in enumerate(channel_tolerances(dim)):
+            assert_close(ch[:, c], ref[:, c], t, f"channel {c}")
+        assert torch.equal(ctx.query(xt[:60_000].contiguous(), sub=0, what="channels")[:600].cpu(),
+                           torch.from_numpy(ch.reshape(600, -1)))
+    finally:
+        ctx.close()
+        orc.set_activation("tanh")
