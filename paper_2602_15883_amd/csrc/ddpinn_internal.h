@@ -11,7 +11,7 @@ constexpr int kMaxWidth = 256;
 constexpr int kMaxWaves = 8;    // waves per workgroup of the network kernels
 constexpr int kMaxDepth = 16;
 constexpr int kMaxSub = 4096;
-constexpr int kSlabChunk = 16;   // slabs summed by one thread of the reduction
+constexpr int kSlabChunk = 16;   // slabs in flight per wave of the reduction
 
 // Per-subdomain device descriptor (copied into the workspace at create).
 struct SubDev {

@@ -93,15 +93,18 @@ __global__ void prep_kernel(const PrepArgs a) {
 
 // ---------------------------------------------------------------------------
 // Gradient reduction and Adam.  One launch: the slabs of a subdomain are
-// summed in a fixed order (chunks of kSlabChunk slabs, then the chunks in
-// order); without clipping Adam follows in the same thread, which also writes
-// the parameter's kernel copies, so that neither the gradient nor theta is read again.
+// summed in a fixed order (a wave takes every kReduceGroups-th chunk of kSlabChunk slabs, then
+// the waves' sums) in 64 bits and rounded once: the slabs largely cancel, and a sum in 32 bits
+// was up to three quarters of a gradient's error (2D 4x32, 200,000 points, 512 slabs: 1.6e-7 of the
+// gradient's norm, 0.84e-7 so; 3D 5x96, 20,000 points: 1.34 and 0.85e-7).  Without clipping Adam
+// follows in the same thread, which also writes the parameter's kernel copies, so that neither
+// the gradient nor theta is read again.
 // With clipping a second launch applies Adam, each block adding up the same
 // norm from the blocks' sums of squares.
-// A block takes 64 consecutive slab positions (256 bytes of each slab) and
-// kReduceGroups chunks at a time; the kernel is bound by the reads of the slabs
+// A block takes 64 consecutive slab positions (256 bytes of each slab); the kernel
+// is bound by the reads of the slabs, of which a wave has sixteen in flight
 // (2D 4x50, 2,000 points, 128 slabs of 58 KB: slab sum 4.8, gradient 9.9, Adam 4.7 and copies
-// 4.1 us as four launches, 5.9 us so).
+// 4.1 us as four launches, 5.8 us so; 3D 8x200, 256 slabs of 1.2 MB: 64 us).
 // ---------------------------------------------------------------------------
 
 // row and column positions of element e of a layer's dW in the slab: tiles [row
@@ -189,35 +192,36 @@ __device__ __forceinline__ void adam_update(const ReduceArgs& a, const SubDev& s
   write_copies(a.sh, sd.frag, pos, x);
 }
 
-constexpr int kReduceGroups = 8;   // chunks summed at a time by a block
-constexpr int kReducePos = 64;     // slab positions of a block
+constexpr int kReduceGroups = 8;   // waves of a block
+constexpr int kReducePos = kWave;  // slab positions of a block
 
 __global__ __launch_bounds__(kReduceGroups * kReducePos) void reduce_kernel(const ReduceArgs a) {
   const Shape& sh = a.sh;
-  const int s = blockIdx.y, lane = threadIdx.x % kReducePos, grp = threadIdx.x / kReducePos;
+  const int s = blockIdx.y, lane = threadIdx.x % kReducePos;
+  const int grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kReducePos);   // the wave
   const int64_t pos = (int64_t)blockIdx.x * kReducePos + lane;
   const int k0 = a.seg_begin[s], k1 = a.seg_begin[s + 1];
-  __shared__ float part[kReduceGroups][kReducePos];
-  float tot = 0.f;
-  for (int b = k0; b < k1; b += kReduceGroups * kSlabChunk) {
-    const int c0 = b + grp * kSlabChunk;
+  __shared__ double part[kReduceGroups][kReducePos];
+  double acc = 0.0;
+  auto add = [&](int c0, auto whole) {
     float v[kSlabChunk];
 #pragma unroll
     for (int q = 0; q < kSlabChunk; ++q)
-      v[q] = (c0 + q < k1) ? a.slabs[(size_t)(c0 + q) * sh.slab_floats + pos] : 0.f;
-    float acc = 0.f;
+      v[q] = decltype(whole)::value || c0 + q < k1 ? ldg(a.slabs + (size_t)(c0 + q) * sh.slab_floats + pos) : 0.f;
 #pragma unroll
-    for (int q = 0; q < kSlabChunk; ++q) acc += v[q];
-    part[grp][lane] = acc;
-    __syncthreads();
-    if (grp == 0) {
-#pragma unroll
-      for (int q = 0; q < kReduceGroups; ++q)
-        if (b + q * kSlabChunk < k1) tot += part[q][lane];
-    }
-    __syncthreads();
-  }
+    for (int q = 0; q < kSlabChunk; q += 4)
+      acc += ((double)v[q] + (double)v[q + 1]) + ((double)v[q + 2] + (double)v[q + 3]);
+  };
+  int c0 = k0 + grp * kSlabChunk;
+  for (; c0 + kSlabChunk <= k1; c0 += kReduceGroups * kSlabChunk) add(c0, std::true_type{});
+  if (c0 < k1) add(c0, std::false_type{});
+  part[grp][lane] = acc;
+  __syncthreads();
   if (grp != 0) return;   // one wave from here on
+  acc = 0.0;
+#pragma unroll
+  for (int q = 0; q < kReduceGroups; ++q) acc += part[q][lane];
+  const float tot = (float)acc;
   const SubDev& sd = a.subs[s];
   const int64_t p = slab_param(sh, pos);
   if (p >= 0) {

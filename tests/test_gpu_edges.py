@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import workloads as wl
-from parity import assert_close, channel_tolerances, rel_report
+from parity import assert_close, channel_tolerances, oracle_loss_grad, rel_report
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -81,6 +81,28 @@ def test_small_networks_in_every_tile(pkg, orc, dim, W, act):
             assert_close(ch[:, c], ref[:, c], t, f"channel {c}")
         assert torch.equal(ctx.query(xt[:60_000].contiguous(), sub=0, what="channels")[:600].cpu(),
                            torch.from_numpy(ch.reshape(600, -1)))
+    finally:
+        ctx.close()
+        orc.set_activation("tanh")
+
+
+@pytest.mark.parametrize("dim,W,H,act,ranges", [(2, 32, 4, "tanh", 8), (2, 40, 3, "sin", 4), (3, 64, 3, "tanh", 8)])
+def test_gradient_of_many_slabs(pkg, orc, dim, W, H, act, ranges):
+    """Several thousand gradient slabs: their sum adds no error to theirs.  A slab's own
+    is that of a chain of 24 to 32 accumulations of growing partial sums (0.3 * 2^-23 of
+    each, added as independent errors: 1.2e-7) and of the values it is made of
+    (0.5e-7 and more); a sum of thousands in 32 bits adds 3e-7."""
+    print(f"slabs dim={dim} W={W} H={H} act={act}", flush=True)
+    pb = wl.tiny(dim=dim, width=W, depth=H, n_pde=120_000, n_obs=200, n_gh=50, n_anc=1, seed=W)
+    pb.activation = act
+    orc.set_activation(act)
+    ctx = pkg.context_from_problem(pb, device="cuda", ranges_per_wg=ranges)
+    try:
+        assert ctx.launch_info()["n_segments"] >= 2000
+        loss, g = ctx.step(1, update=False, want_grad=True)
+        Lr, gr = oracle_loss_grad(orc, pb)
+        assert rel_report(loss.cpu().numpy()[0], Lr)[1] <= 2e-7
+        assert rel_report(g.cpu().numpy()[0], gr)[1] <= 2e-7, rel_report(g.cpu().numpy()[0], gr)
     finally:
         ctx.close()
         orc.set_activation("tanh")
