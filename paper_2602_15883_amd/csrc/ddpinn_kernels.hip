@@ -58,7 +58,7 @@ __global__ void prep_kernel(const PrepArgs a) {
       x[q] = (r >= 0 && k >= 0) ? (trans ? th[sh.p_w[l] + (int64_t)k * W + r] : th[sh.p_w[l] + (int64_t)r * W + k]) : 0.f;
     }
     uint32_t* o = reinterpret_cast<uint32_t*>(fr + sh.f_hid3) + (size_t)m * per * 3 + (size_t)t * 768 + lane * 4 + e2;
-    o[0] = split_step(x[0], x[1]);
+    o[0] = split_first(x[0], x[1]);
     o[256] = split_step(x[0], x[1]);
     o[512] = pack_bf16(x[0], x[1]);
     return;
@@ -165,7 +165,7 @@ __device__ __forceinline__ void write_copies(const Shape& sh, float* fr, int64_t
   }
   float x = v, y = 0.f;
   uint32_t part[3];
-  part[0] = split_step(x, y);
+  part[0] = split_first(x, y);
   part[1] = split_step(x, y);
   part[2] = pack_bf16(x, y);
   const int KB = (sh.NW + 1) >> 1, kb = c >> 5, n = c & 31, g = (n >> 2) & 3;

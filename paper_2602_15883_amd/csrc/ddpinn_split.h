@@ -3,7 +3,7 @@
 //
 // Every fp32 operand x is written as x = h + m + l with h = bf16(x),
 // m = bf16(x - h), l = x - h - m (round to nearest even): 8 + 8 + 8 significand
-// bits hold all 24 of x, so the split itself loses nothing.  Of the nine partial products
+// bits hold all 24 of x, so the split itself loses nothing (see Range).  Of the nine partial products
 // the six of weight 2^-16 and above are formed, smallest first,
 //   l.h, h.l, m.m, m.h, h.m, h.h,
 // on v_mfma_f32_16x16x32_bf16 into one fp32 accumulator; the three left out
@@ -16,9 +16,11 @@
 // MI355X is 2207 / 6 = 368 TFLOP/s of fp32 products against 149 for the fp32
 // instruction (both measured, all compute units).
 //
-// The exponent range is that of fp32 (bf16 has the same), so no operand is
-// scaled.  An infinite operand gives NaN (inf - inf in the split) where fp32
-// arithmetic might give an infinity.
+// Range.  No operand is scaled.  The split is exact from 2^-110 in magnitude (below, a third part
+// can be under bf16's smallest, 2^-133, and what is under it is lost: an absolute error of less than
+// 2^-133 per operand, where fp32 holds down to 2^-149).  A weight is exact up to the largest fp32; of the
+// other operands one above 2^128 - 2^119 (3.396e38), which rounds to a bf16 infinity, gives NaN, and so does any
+// infinite operand (inf - inf in the split), where fp32 arithmetic might give an infinity or saturate.
 //
 // The kernels keep the operands of one side, the activations (or Zbar), in an LDS
 // stack of parts, 6 bytes per value, and stream the weights as fragments.  A stack
@@ -87,6 +89,17 @@ __device__ __forceinline__ uint32_t split_step(float& a, float& b) {
   const uint32_t u = __builtin_bit_cast(uint32_t, h);
   a -= __builtin_bit_cast(float, u << 16);
   b -= __builtin_bit_cast(float, u & 0xffff0000u);
+  return u;
+}
+// The first step for the weight copies: a finite operand that would round to a bf16 infinity
+// takes the largest bf16 instead (its remainder fits the other parts).
+__device__ __forceinline__ uint32_t split_first(float& a, float& b) {
+  constexpr float top = 0x1.fep+127f;
+  float x = a > top ? top : a < -top ? -top : a, y = b > top ? top : b < -top ? -top : b;
+  const float dx = a - x, dy = b - y;
+  const uint32_t u = split_step(x, y);
+  a = x + dx;
+  b = y + dy;
   return u;
 }
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {

@@ -146,3 +146,36 @@ def test_adam_leaves_the_weight_copies_current(dim, W, H, act, clip):
         assert not torch.equal(before, after)
     finally:
         ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dim,W", [(2, 16), (3, 30), (2, 40), (3, 100), (2, 150)])
+def test_weights_up_to_the_largest_fp32(orc, dim, W):
+    """Finite weights above the largest bf16 (3.39e38), whose neurons saturate: values,
+    a step on value points and the copies it leaves behind stay finite."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2602_15883_amd as P
+    print(f"large weights dim={dim} W={W}", flush=True)
+    H, top = 3, float(np.finfo(np.float32).max)
+    pb = wl.tiny(dim=dim, width=W, depth=H, n_pde=300, n_obs=40, n_gh=0, n_anc=0, seed=W)
+    s = pb.subs[0]
+    x, s.pde_x = np.ascontiguousarray(s.pde_x), s.pde_x[:0]
+    D = dim + 1
+    w2 = W * D + W                            # W_2, then b_2, then W_3
+    s.theta[w2] = top
+    s.theta[w2 + (W - 1) * W + 2] = -top
+    s.theta[w2 + W * W + W + W + 1] = 3.3961e38
+    ref = orc.channels(dim, W, H, s.theta, x)[:, 0]
+    pb.lr = 0.0
+    ctx = P.context_from_problem(pb, device="cuda")
+    try:
+        xt = torch.from_numpy(x).cuda()
+        assert_close(ctx.query(xt, sub=0, what="value").cpu().numpy(), ref, 1e-5, "value")
+        loss, g = ctx.step(1, want_grad=True)
+        Lr, gr = oracle_loss_grad(orc, pb)
+        assert rel_report(loss.cpu().numpy()[0], Lr)[1] <= 1e-5
+        assert bool(torch.isfinite(g).all())
+        assert_close(ctx.query(xt, sub=0, what="value").cpu().numpy(), ref, 1e-5, "value after the update")
+    finally:
+        ctx.close()
