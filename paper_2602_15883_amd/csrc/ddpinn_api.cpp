@@ -416,8 +416,7 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   auto occ_of = [&](int tp, int* occ) -> pinn_status {
     const int lf = step_lds_floats(sh, tp);
     const void* k = step_kernel_ptr(sh, tp);
-    // 32-point tiles hold twice the registers: at most 4 waves (Wp <= 64)
-    if (!k || (int64_t)lf * 4 > max_lds || (tp == 32 && c->threads > 256)) { *occ = 0; return PINN_OK; }
+    if (!k || (int64_t)lf * 4 > max_lds) { *occ = 0; return PINN_OK; }
     int nb = 0;
     HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, c->threads, (size_t)lf * 4));
     *occ = nb;
@@ -430,8 +429,8 @@ pinn_status pinn_create(const pinn_config* cfg, const pinn_subdomain* subs, void
   if (tp == 0) tp = 16;
   const int occ = (tp == 32) ? occ32 : occ16;
   if (occ < 1) {
-    if (tp == 32 && sh.NW > kMaxWaves)
-      return fail(PINN_E_UNSUPPORTED, "width %d: only 16-point tiles above %d neurons", cfg->width, 16 * kMaxWaves);
+    if (tp == 32 && sh.NW > 4)   // twice the registers per wave: at most four waves
+      return fail(PINN_E_UNSUPPORTED, "width %d: only 16-point tiles above 64 neurons", cfg->width);
     return fail(PINN_E_UNSUPPORTED, "tile of %d points needs %d B of LDS per workgroup (device limit %d B)", tp,
                 step_lds_floats(sh, tp) * 4, max_lds);
   }

@@ -106,3 +106,12 @@ def test_gradient_of_many_slabs(pkg, orc, dim, W, H, act, ranges):
     finally:
         ctx.close()
         orc.set_activation("tanh")
+
+
+@pytest.mark.parametrize("dim,W", [(2, 65), (2, 100), (3, 128), (2, 150), (3, 240)])
+def test_a_refused_32_point_tile_names_its_limit(pkg, dim, W):
+    pb = wl.tiny(dim=dim, width=W, depth=2, n_pde=40, seed=W)
+    with pytest.raises(pkg.PinnError, match="only 16-point tiles above 64 neurons") as e:
+        pkg.context_from_problem(pb, device="cuda", tile_points=32)
+    assert e.value.status == pkg.abi.PINN_E_UNSUPPORTED
+    pkg.context_from_problem(wl.tiny(dim=dim, width=64, depth=2, n_pde=40, seed=W), device="cuda", tile_points=32).close()
