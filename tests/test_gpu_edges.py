@@ -5,6 +5,7 @@ import pytest
 
 import workloads as wl
 from parity import assert_close, channel_tolerances, oracle_loss_grad, rel_report
+from test_split_scheme import BOUND_GRAD
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -115,3 +116,72 @@ def test_a_refused_32_point_tile_names_its_limit(pkg, dim, W):
         pkg.context_from_problem(pb, device="cuda", tile_points=32)
     assert e.value.status == pkg.abi.PINN_E_UNSUPPORTED
     pkg.context_from_problem(wl.tiny(dim=dim, width=64, depth=2, n_pde=40, seed=W), device="cuda", tile_points=32).close()
+
+
+@pytest.mark.parametrize("dim,W,act", [(2, 80, "sin"), (2, 100, "tanh"), (3, 112, "tanh"), (3, 128, "sin")])
+def test_values_are_the_same_in_every_tile(pkg, dim, W, act):
+    """Five to eight row blocks: small tiles, those of half the registers and full ones."""
+    print(f"values dim={dim} W={W} act={act}", flush=True)
+    pb = wl.tiny(dim=dim, width=W, depth=3, n_pde=60_001, seed=W)
+    pb.activation = act
+    x = torch.from_numpy(np.ascontiguousarray(pb.subs[0].pde_x)).cuda()
+    pb.subs[0].pde_x = pb.subs[0].pde_x[:50]
+    ctx = pkg.context_from_problem(pb, device="cuda")
+    try:
+        full = ctx.query(x, sub=0, what="value")
+        for n in (100, 4096, 4097, 9000, 20_000, 32_768):
+            assert torch.equal(ctx.query(x[:n].contiguous(), sub=0, what="value"), full[:n]), n
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("dim,W,H,act,npde", [(2, 16, 2, "tanh", 31), (2, 33, 3, "sin", 1000), (3, 17, 3, "tanh", 65),
+                                              (3, 48, 2, "sin", 33), (2, 50, 4, "tanh", 2000), (2, 64, 3, "tanh", 40_003),
+                                              (3, 64, 2, "tanh", 20_000)])
+def test_32_point_tiles_against_oracle(pkg, orc, dim, W, H, act, npde):
+    print(f"32-point dim={dim} W={W} H={H} act={act} n={npde}", flush=True)
+    pb = wl.tiny(dim=dim, width=W, depth=H, n_pde=npde, n_obs=5 + npde // 9, n_gh=23, n_anc=2, seed=W + H)
+    pb.activation = act
+    orc.set_activation(act)
+    ctx = pkg.context_from_problem(pb, device="cuda", tile_points=32, guard_bytes=4096)
+    try:
+        assert ctx.launch_info()["tile_points"] == 32
+        Lr, gr = oracle_loss_grad(orc, pb)
+        for kw in ({}, {"per_subdomain": True}):
+            loss, g = ctx.step(1, update=False, want_grad=True, **kw)
+            assert rel_report(loss.cpu().numpy()[0], Lr)[1] <= BOUND_GRAD
+            assert rel_report(g.cpu().numpy()[0], gr)[1] <= BOUND_GRAD, rel_report(g.cpu().numpy()[0], gr)
+        ctx.step(1)
+        torch.cuda.synchronize()
+        assert ctx.check_guards() == 0
+    finally:
+        ctx.close()
+        orc.set_activation("tanh")
+
+
+@pytest.mark.parametrize("dim,W,act,npde", [(3, 96, "tanh", 5000), (2, 80, "sin", 5000), (2, 65, "tanh", 7001),
+                                            (3, 144, "tanh", 5000), (2, 208, "sin", 5000), (2, 32, "tanh", 9000)])
+def test_workgroups_of_four_waves_write_in_their_regions(pkg, dim, W, act, npde):
+    """Two workgroups of four waves per compute unit, some with two row blocks and
+    a dW block of another wave; two row blocks per wave of eight; several small
+    workgroups per compute unit: no byte outside a region of the workspace."""
+    print(f"guards dim={dim} W={W} act={act}", flush=True)
+    pb = wl.tiny(dim=dim, width=W, depth=3, n_pde=npde, n_obs=150, n_gh=30, n_anc=2, seed=W)
+    pb.activation = act
+    ctx = pkg.context_from_problem(pb, device="cuda", guard_bytes=4096)
+    try:
+        if 64 < W <= 96:
+            assert ctx.launch_info()["threads"] == 256
+        ctx.step(1, update=False, want_grad=True)
+        ctx.step(1)
+        ctx.step(2, time_kernel=True)
+        ctx.kernel_time()
+        ctx.step(3, update=False, want_grad=True, per_subdomain=True)
+        x = torch.from_numpy(np.ascontiguousarray(pb.subs[0].pde_x)).cuda()
+        for what in ("value", "residual", "channels"):
+            for n in (1, 500, npde):
+                ctx.query(x[:n].contiguous(), sub=0, what=what)
+        torch.cuda.synchronize()
+        assert ctx.check_guards() == 0
+    finally:
+        ctx.close()
