@@ -332,7 +332,6 @@ __device__ __forceinline__ void residuals(F Y, float nu, float (&r)[DIM + 1]) {
 // Wp/4.  This is a permutation of the hidden neurons with zero weights at the
 // padded positions (whose activations are 0), so the network is unchanged.
 // ---------------------------------------------------------------------------
-__host__ __device__ inline int hid_pos(const Shape& sh, int n) { return (n / sh.Kq) * (sh.Wp / 4) + n % sh.Kq; }
 __host__ __device__ inline int hid_neuron(const Shape& sh, int p) {
   const int seg = sh.Wp / 4, g = p / seg, s = p - g * seg, n = g * sh.Kq + s;
   return (s < sh.Kq && n < sh.W) ? n : -1;

@@ -59,7 +59,7 @@ struct Shape {
   int32_t NWS;                    // waves per workgroup of the step: NWV, or 4 (step_halves)
   int32_t s3;                     // the kernels on bf16 triples (ddpinn_split.h), else ddpinn_wide.hip
   int32_t Kq;                     // fp32 kernels: ceil(W/4), K-steps of the hidden-layer GEMMs (hidden
-                                  // neurons are stored at permuted positions, see hid_pos); else Wp/4
+                                  // neurons are stored at permuted positions, see hid_neuron); else Wp/4
   int32_t pad_;
   // fragment buffer (per subdomain)
   int64_t f_hid;   // fp32 kernels: hidden layer l (2..H), forward A-fragments at f_hid + (l-2)*2*Wp*Wp,

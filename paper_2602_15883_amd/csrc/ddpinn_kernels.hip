@@ -144,8 +144,8 @@ __device__ __forceinline__ int64_t slab_param(const Shape& sh, int64_t pos) {
 }
 
 // The copies that queries and exchanges read of the parameter at slab position pos
-// (prep_kernel's layout).  The step's own copies (the transposed ones and, above 128
-// neurons, the fp32 fragments) are rebuilt by prep_kernel at the start of every step.
+// (prep_kernel's layout).  The step's own copies (the transposed ones and W_{H+1}'s triples) are
+// rebuilt by prep_kernel at the start of every step.
 __device__ __forceinline__ void write_copies(const Shape& sh, float* fr, int64_t pos, float v) {
   const int Wp = sh.Wp;
   if (pos >= sh.s_b) {

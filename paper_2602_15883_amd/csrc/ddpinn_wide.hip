@@ -812,12 +812,11 @@ __device__ __forceinline__ void forward_tile(const Shape& sh, const float* fr, f
 }
 
 // SMALL: one 16-point block instead of CF column blocks (value mode); for
-// requests too small to fill the chip.
+// requests too small to fill the chip (32,000 values of 6x224: 217 us, 330 with full tiles; 6x256: 254 and 370).
 template <int DIM, int MODE, int ACT, int SMALL>
 __global__ __launch_bounds__(512) void query_kernel(const QueryArgs a) {
   constexpr int D = DIM + 1, CF = 2 * DIM + 2;
-  constexpr int CMODE = MODE == M_VALUE ? 1 : (MODE == M_GRAD ? DIM + 1 : CF);
-  constexpr int NCB = SMALL ? CMODE : CF;
+  constexpr int NCB = SMALL ? 1 : CF;
   using M = ModeCfg<DIM, NCB, MODE>;
   constexpr int NPTS = M::NPTS, NCOL = 16 * NCB;
   extern __shared__ float lds[];
@@ -878,13 +877,6 @@ __global__ __launch_bounds__(512) void query_kernel(const QueryArgs a) {
       auto Y = [&](int ch, int o) { return ys[o * NCOL + (ch * M::NPB + pb) * 16 + jj]; };
       if (a.what == Q_VALUE) {
         for (int o = 0; o < D; ++o) a.out[q * D + o] = Y(0, o);
-      } else if (a.what == Q_UVPW) {
-        if constexpr (MODE == M_GRAD && DIM == 2) {
-          a.out[q * 4 + 0] = Y(0, 0);
-          a.out[q * 4 + 1] = Y(0, 1);
-          a.out[q * 4 + 2] = Y(0, 2);
-          a.out[q * 4 + 3] = Y(1, 1) - Y(2, 0);   // v_x - u_y
-        }
       } else if (a.what == Q_CHANNELS) {
         if constexpr (MODE == M_PDE)
           for (int ch = 0; ch < CF; ++ch)
