@@ -34,7 +34,6 @@ Only one GPU is used: --gpus above 1 exits with a message.
 from __future__ import annotations
 
 import argparse
-import hashlib
 import json
 import os
 import sys
@@ -96,17 +95,10 @@ def make_problem(name, seed=0):
             "cylinder2d_paper": wl.cylinder2d_paper, "cylinder3d_paper": wl.cylinder3d_paper}[name](seed)
 
 
-def kernel_source_hash():
-    h = hashlib.sha256()
-    for f in ("ddpinn_kernels.hip", "ddpinn_internal.h"):
-        with open(os.path.join(ROOT, "paper_2602_15883_amd", "csrc", f), "rb") as fh:
-            h.update(fh.read())
-    return h.hexdigest()[:16]
-
-
 def traffic_from_profiles(workload):
     """HBM bytes per launch of the fused kernel from committed rocprofv3
     counter runs, if they were taken on the current kernel source."""
+    from profiling import kernel_source_hash
     path = os.path.join(ROOT, "profiles", "traffic.json")
     try:
         with open(path) as f:

@@ -24,6 +24,7 @@ import glob
 import hashlib
 import json
 import os
+import re
 import sys
 from collections import defaultdict
 
@@ -37,11 +38,25 @@ def _csvs(d, suffix):
     return sorted(glob.glob(os.path.join(d, "**", "*" + suffix), recursive=True))
 
 
-def kernel_source_hash() -> str:
-    h = hashlib.sha256()
-    for f in ("ddpinn_kernels.hip", "ddpinn_internal.h"):
-        with open(os.path.join(CSRC, f), "rb") as fh:
-            h.update(fh.read())
+# what determines the step's launches: the kernels, the launch rules, the buffers' layout
+STEP_SOURCES = ("ddpinn_step.hip", "ddpinn_split.h", "ddpinn_device.h", "ddpinn_wide.hip", "ddpinn_internal.h",
+                "ddpinn_kernels.hip", "ddpinn_api.cpp")
+
+
+def code_of(text: str) -> str:
+    """C++ source without its comments and line breaks (no comment sign stands in
+    a string of these sources)."""
+    return " ".join(re.sub(r"//[^\n]*|/\*.*?\*/", " ", text, flags=re.S).split())
+
+
+def kernel_source_hash(csrc: str = CSRC) -> str:
+    """Of the code, not the comments, of STEP_SOURCES and of the compiler flags."""
+    sys.path.insert(0, ROOT)
+    from paper_2602_15883_amd.build_lib import DEVICE_FLAGS
+    h = hashlib.sha256(" ".join(DEVICE_FLAGS).encode())
+    for f in STEP_SOURCES:
+        with open(os.path.join(csrc, f)) as fh:
+            h.update(code_of(fh.read()).encode())
     return h.hexdigest()[:16]
 
 
