@@ -104,7 +104,7 @@ def candidates(width: int) -> List[dict]:
             continue
         for bpc in (1, 2, 3, 4):
             for prio in (True, False):
-                for rpw in ((0,) if bpc == 1 else (2, 4, 8)):
+                for rpw in ((0,) if bpc == 1 else (1, 2, 4, 8)):
                     out.append({"tile_points": tp, "blocks_per_cu": bpc, "gemm_priority": prio,
                                 "ranges_per_wg": rpw})
     return out
