@@ -206,8 +206,14 @@ __global__ __launch_bounds__(kReduceGroups * kReducePos) void reduce_kernel(cons
   auto add = [&](int c0, auto whole) {
     float v[kSlabChunk];
 #pragma unroll
-    for (int q = 0; q < kSlabChunk; ++q)
-      v[q] = decltype(whole)::value || c0 + q < k1 ? ldg(a.slabs + (size_t)(c0 + q) * sh.slab_floats + pos) : 0.f;
+    for (int q = 0; q < kSlabChunk; ++q) {   // (past the last slab the last one, which is not added)
+      const int k = decltype(whole)::value || c0 + q < k1 ? c0 + q : k1 - 1;
+      v[q] = ldg(a.slabs + (size_t)k * sh.slab_floats + pos);
+    }
+    if (!decltype(whole)::value) {
+#pragma unroll
+      for (int q = 0; q < kSlabChunk; ++q) v[q] = c0 + q < k1 ? v[q] : 0.f;
+    }
 #pragma unroll
     for (int q = 0; q < kSlabChunk; q += 4)
       acc += ((double)v[q] + (double)v[q + 1]) + ((double)v[q + 2] + (double)v[q + 3]);
