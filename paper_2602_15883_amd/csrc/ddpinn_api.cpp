@@ -862,14 +862,23 @@ pinn_status pinn_query(pinn_ctx* c, const float* x, int64_t n, int32_t sub, uint
   const int CF = 2 * sh.dim + 2;
   // requests too small to fill the chip take 16-point tiles: a tile's chain of
   // layers is the latency, and smaller tiles shorten it.  They stay ahead for a few times what the
-  // compute units hold.  Values (one column block instead of 2 dim + 2): up to 64 waves per
+  // compute units hold.  Of one network: values (one column block instead of 2 dim + 2) up to 64 waves per
   // compute unit (2D 6x128: 34,000 points 60 us against 61 with full tiles, 50,000 points 83 and 66; 2D 6x32:
-  // 125,000 points 28 and 39, 200,000 43 and 39); uvpw (three column blocks instead of six): up to
+  // 125,000 points 28 and 39, 200,000 43 and 39), uvpw (three column blocks instead of six) up to
   // two and a half times the resident workgroups, at least three per compute unit (2D 6x32: 34,000 points
-  // 18.4 and 21.0, 60,000 29.3 and 25.0; 2D 6x128: 12,000 points 44 and 50, 16,000 58 and 54).  One row block: see split_forward_alone
-  // (2D 6x16: 300,000 values 25 and 35)
-  const int64_t rounds = what == PINN_Q_VALUE ? (sh.NW == 1 ? 128 : 64 / sh.NWV)
-                       : what == PINN_Q_UVPW ? std::max(3, 5 * c->query_occ_small[1] / 2) : 0;
+  // 18.4 and 21.0, 60,000 29.3 and 25.0; 2D 6x128: 12,000 points 44 and 50, 16,000 58 and 54), one row block: see
+  // split_forward_alone (2D 6x16: 300,000 values 25 and 35).  Of several networks, where more tiles fetch
+  // weights that no other has fetched, half of that for values and about the resident workgroups for uvpw (4
+  // networks 2D 6x24, 37,000 values 27 and 39, 16 networks 2D 6x64, 45,000 values 52 and 45; uvpw, 19,000 points, 4
+  // networks 2D 6x24 25 and 31, 13,782 points, 16 networks 2D 6x64 37 and 34)
+  int64_t rounds = 0;
+  if (what <= PINN_Q_UVPW) {
+    const int nets = sub >= 0 ? 1 : c->n_sub, resident = c->query_occ_small[what];
+    if (what == PINN_Q_VALUE)
+      rounds = nets > 1 ? std::max(std::max(8, resident), 32 / sh.NWV) : sh.NW == 1 ? 128 : 64 / sh.NWV;
+    else
+      rounds = nets > 8 ? std::max(3, resident) : nets > 1 ? std::max(sh.NW <= 4 ? 4 : 3, resident + 1) : std::max(3, 5 * resident / 2);
+  }
   const bool small = n <= 16 * rounds * c->num_cu;
   // values beyond two waves per SIMD: the kernel of half the registers, of which more workgroups are
   // resident (2D 6x48, 16,000 points 9.0 us, 9.8 with the other, 4,500 points 11.6 and 10.9; 2D 6x80, 4,500 points
